@@ -27,6 +27,7 @@
 #include <atomic>
 #include <cstdlib>
 #include <fstream>
+#include <functional>
 #include <iterator>
 #include <thread>
 #include <sys/stat.h>
@@ -302,6 +303,131 @@ std::string gen_dot(const Env &e, const PassOp &op, int R, const std::vector<Gen
 
 bool is_diag(const PassOp &op) { return op.kind == K_D1 || op.kind == K_D2; }
 
+// X gates as index maps.  X and CNOT only permute a stage's amplitudes, by a
+// map that is affine over GF(2) in the index bits.  The X-type ops of a stage
+// that can move to its front (past the ops before them) are applied by loading
+// the registers from permuted LDS addresses, those that can move to its end by
+// storing to permuted ones: a compile-time renaming of the registers and, for
+// controls outside the stage, an xor of the item's LDS base (sw is linear over
+// xor), instead of four selects per amplitude and state.  The VQE ansatz's
+// reverse passes (CNOT ring, RY, RZ; 16 qubits) spent 257 of 3.1k VALU
+// instructions on the selects; every CNOT of its stages moves.  With the
+// Z-type gradients of a run taken together (diag_grads) those passes, bound by
+// VALU issue, take 37 ms per step at 4096 rows instead of 46 ms.
+struct RegMap {
+    // bit j of the new index: parity(index & row[j]) ^ (cst >> j & 1) ^ the
+    // bits (tile position, global position) of out[j]
+    uint32_t row[4] = {1, 2, 4, 8};
+    uint32_t cst = 0;
+    std::set<std::pair<uint8_t, uint8_t>> out[4];
+    void add(const PassOp &op)  // the X-type op applied after the map
+    {
+        const int t = op.s0;
+        if (!op.ctrl) {
+            cst ^= 1u << t;
+            return;
+        }
+        if (!op.cval) cst ^= 1u << t;
+        auto flip = [&](const std::pair<uint8_t, uint8_t> &b) {
+            if (!out[t].erase(b)) out[t].insert(b);
+        };
+        if (op.s1 == kFixed) {
+            flip({op.l1, op.p1});
+            return;
+        }
+        row[t] ^= row[op.s1];
+        cst ^= ((cst >> op.s1) & 1u) << t;
+        for (auto &b : out[op.s1]) flip(b);
+    }
+    uint32_t lin(uint32_t k, int R) const
+    {
+        uint32_t v = 0;
+        for (int j = 0; j < R; j++) v |= (uint32_t)(__builtin_popcount(k & row[j]) & 1) << j;
+        return v;
+    }
+    uint32_t lin_inv(uint32_t v, int R) const
+    {
+        for (uint32_t k = 0; k < (1u << R); k++)
+            if (lin(k, R) == v) return k;
+        return 0;
+    }
+    bool identity(int R) const
+    {
+        bool id = cst == 0;
+        for (int j = 0; j < R; j++) id = id && row[j] == 1u << j && out[j].empty();
+        return id;
+    }
+};
+
+// The ops of a stage that stay (in order), and the index maps of those moved
+// to its front and to its end.  An X-type op passes an op on other bits; its
+// control also passes a diagonal op or a control.
+struct StageOps {
+    std::vector<const PassOp *> ops;
+    RegMap lead, trail;
+};
+bool is_xop(const PassOp &op) { return op.kind == K_M1 && (op.hint & kHintX) && op.ngrad == 0; }
+StageOps stage_ops(const Pass &ps, const Stage &st, bool forward)
+{
+    auto reg = [](uint8_t b) { return b == kFixed ? 0u : 1u << b; };
+    // register bits an op touches at all, and those it is not diagonal on
+    auto touch = [&](const PassOp &op, uint32_t *any, uint32_t *nd) {
+        const bool diag = op.kind == K_D1 || op.kind == K_D2;
+        const bool two = op.kind == K_M2 || op.kind == K_P2 || op.kind == K_F2;
+        const bool has1 = two || op.kind == K_D2 || (op.kind == K_M1 && op.ctrl);
+        *any |= reg(op.s0) | (has1 ? reg(op.s1) : 0u);
+        if (!diag) *nd |= reg(op.s0) | (two ? reg(op.s1) : 0u);
+    };
+    auto split = [&](const std::vector<const PassOp *> &in, std::vector<const PassOp *> *moved,
+                     std::vector<const PassOp *> *kept) {
+        uint32_t any = 0, nd = 0;
+        for (const PassOp *op : in) {
+            const bool mv = is_xop(*op) && !(any & reg(op->s0)) && !(op->ctrl && (nd & reg(op->s1)));
+            (mv ? moved : kept)->push_back(op);
+            if (!mv) touch(*op, &any, &nd);
+        }
+    };
+    StageOps r;
+    std::vector<const PassOp *> all, lead, rest, trail, kept;
+    for (int oi = st.op_begin; oi < st.op_end; oi++) all.push_back(&ps.ops[oi - ps.op_offset]);
+    split(all, &lead, &rest);
+    std::reverse(rest.begin(), rest.end());
+    split(rest, &trail, &kept);
+    std::reverse(kept.begin(), kept.end());
+    std::reverse(trail.begin(), trail.end());
+    for (const PassOp *op : lead) r.lead.add(*op);
+    for (const PassOp *op : trail) r.trail.add(*op);
+    // diagonal ops move past the non-diagonal ones on other qubits again, now
+    // that the moved ops are out of the way (the planner orders the whole
+    // stage): later in forward stages, earlier in reverse ones
+    auto meet = [](const PassOp &a, const PassOp &b) {
+        auto qs = [](const PassOp &op, int *q) {
+            q[0] = op.p0;
+            q[1] = op.p1;
+            return op.kind == K_D1 || (op.kind == K_M1 && !op.ctrl) ? 1 : 2;
+        };
+        int qa[2], qb[2];
+        const int na = qs(a, qa), nb = qs(b, qb);
+        for (int i = 0; i < na; i++)
+            for (int j = 0; j < nb; j++)
+                if (qa[i] == qb[j]) return true;
+        return false;
+    };
+    auto diag = [](const PassOp *op) { return op->kind == K_D1 || op->kind == K_D2; };
+    const int n = (int)kept.size();
+    if (forward) {
+        for (int k = n - 2; k >= 0; k--)
+            for (int i = k; i + 1 < n && diag(kept[i]) && !diag(kept[i + 1]) && !meet(*kept[i], *kept[i + 1]); i++)
+                std::swap(kept[i], kept[i + 1]);
+    } else {
+        for (int k = 1; k < n; k++)
+            for (int i = k; i > 0 && diag(kept[i]) && !diag(kept[i - 1]) && !meet(*kept[i], *kept[i - 1]); i--)
+                std::swap(kept[i], kept[i - 1]);
+    }
+    r.ops = kept;
+    return r;
+}
+
 // The entry of diagonal op `op` (matrix at offset mat) that multiplies
 // register k of a stage, as an expression; "" when it is exactly 1.  Bits of
 // the op outside the stage select per item.
@@ -401,11 +527,12 @@ std::vector<CutClass> cut_classes(const Group &g, const Pass &ps, int *ntab)
     *ntab = 0;
     for (const Stage &st : ps.stages) {
         if (st.dense) continue;
-        for (int oi = st.op_begin; oi < st.op_end; oi++) {
-            if (!is_diag(ps.ops[oi - ps.op_offset])) continue;
+        const StageOps so = stage_ops(ps, st, true);
+        for (size_t oi = 0; oi < so.ops.size(); oi++) {
+            if (!is_diag(*so.ops[oi])) continue;
             std::vector<const PassOp *> run;
-            int oe = oi;
-            for (; oe < st.op_end && is_diag(ps.ops[oe - ps.op_offset]); oe++) run.push_back(&ps.ops[oe - ps.op_offset]);
+            size_t oe = oi;
+            for (; oe < so.ops.size() && is_diag(*so.ops[oe]); oe++) run.push_back(so.ops[oe]);
             std::vector<CutClass> cls;
             std::vector<const PassOp *> rest;
             split_run(&g, run, &cls, &rest);
@@ -621,22 +748,48 @@ std::string diag_run(const Env &e, const std::vector<const PassOp *> &run, int R
     return o.str();
 }
 
-// item loop header of a stage: base index of the item and the swizzled
-// LDS offsets of its 2^R registers
-void stage_head(std::ostream &o, const Env &e, const Stage &st, std::vector<uint32_t> &off)
+// item loop header of a stage: base index of the item, the swizzled LDS
+// offsets its 2^R registers are loaded from (off_in[k], relative to `sl`) and
+// stored to (off_out[k], relative to `ss`), with the stage's leading and
+// trailing X-type ops in them
+void stage_head(std::ostream &o, const Env &e, const Stage &st, const StageOps &so, std::vector<uint32_t> &off_in,
+                std::vector<uint32_t> &off_out)
 {
     const int R = st.r;
-    off.assign(1u << R, 0);
-    for (uint32_t k = 0; k < (1u << R); k++) {
+    auto off = [&](uint32_t k) {
         uint32_t x = 0;
         for (int j = 0; j < R; j++)
             if ((k >> j) & 1) x |= 1u << st.bits[j];
-        off[k] = host_sw(x);  // sw is linear over xor: sw(base | x) = sw(base) ^ sw(x)
+        return host_sw(x);  // sw is linear over xor: sw(base | x) = sw(base) ^ sw(x)
+    };
+    off_in.assign(1u << R, 0);
+    off_out.assign(1u << R, 0);
+    for (uint32_t k = 0; k < (1u << R); k++) {
+        off_in[k] = off(so.lead.lin_inv(k, R));
+        off_out[k] = off(so.trail.lin(k, R));
     }
     o << "    for (uint32_t item = tid; item < " << (1u << (e.t - R)) << "u; item += " << e.nt << "u) {\n";
     o << "        uint32_t base = item;\n";
     for (int j = 0; j < R; j++) o << "        base = ins0(base, " << (int)st.bits[j] << ");\n";
     o << "        const uint32_t sb = sw(base);\n";
+    // the part of a map that depends on bits outside the stage, as an xor of
+    // the base: register k holds index map(k') with k' = lin_inv(k ^ w) when
+    // loading, and goes to lin(k) ^ w when storing
+    auto base_of = [&](const char *name, const RegMap &m, bool load) {
+        std::map<std::pair<uint8_t, uint8_t>, uint32_t> w;
+        for (int j = 0; j < R; j++)
+            for (auto &b : m.out[j]) w[b] |= 1u << j;
+        o << "        const uint32_t " << name << " = sb";
+        const uint32_t c = off(load ? m.lin_inv(m.cst, R) : m.cst);
+        if (c) o << " ^ " << c << "u";
+        for (auto &kv : w) {
+            const std::string v = bit(e, kv.first.first, kv.first.second);
+            if (v != "0u") o << " ^ ((0u - " << v << ") & " << off(load ? m.lin_inv(kv.second, R) : kv.second) << "u)";
+        }
+        o << ";\n";
+    };
+    base_of("sl", so.lead, true);
+    base_of("ss", so.trail, false);
     // an offset of 0 the compiler cannot see through, taken anew per item:
     // matrix reads offset by it stay inside the item loop instead of being
     // hoisted above it, where every matrix of the stage would be live at once
@@ -766,56 +919,54 @@ std::string const_m1_code(const ConstM1 &cm, const PassOp &op, int R)
 void forward_stage(std::ostream &o, const Env &e, const Pass &ps, const Stage &st, const std::string &scale = "")
 {
     const int R = st.r, NR = 1 << R;
-    std::vector<uint32_t> off;
+    // (a dense stage's matrix holds all of its ops)
+    const StageOps so = st.dense ? StageOps() : stage_ops(ps, st, true);
+    std::vector<uint32_t> off_in, off_out;
     o << "    {\n";
-    stage_head(o, e, st, off);
+    stage_head(o, e, st, so, off_in, off_out);
     o << "        double2 v[" << NR << "];\n";
-    for (int k = 0; k < NR; k++) o << "        v[" << k << "] = up2(lp[sb ^ " << off[k] << "u]);\n";
-    if (st.dense) {
-        o << "        rdense<" << R << ">(v, " << e.G << " + (z_ + " << st.mat << "));\n";
-    } else {
-        for (int oi = st.op_begin; oi < st.op_end; oi++) {
-            const PassOp &op = ps.ops[oi - ps.op_offset];
-            if (is_diag(op)) {
-                std::vector<const PassOp *> run;
-                int oe = oi;
-                for (; oe < st.op_end && is_diag(ps.ops[oe - ps.op_offset]); oe++)
-                    run.push_back(&ps.ops[oe - ps.op_offset]);
-                if (e.cuts) {
-                    // phase classes first (diagonal ops commute), then the rest
-                    std::vector<CutClass> cls;
-                    std::vector<const PassOp *> rest;
-                    split_run(e.fgrp, run, &cls, &rest);
-                    if (!cls.empty()) {
-                        for (size_t ci = 0; ci < cls.size(); ci++)
-                            o << "        " << cut_apply(e, (*e.cuts)[e.cut_next++], st) << "\n";
-                        const std::string c = rest.size() > 1 ? diag_run(e, rest, R, {"v"}) : "";
-                        if (!c.empty())
-                            o << "        " << c << "\n";
-                        else
-                            for (const PassOp *ro : rest) o << "        " << apply(e, *ro, R, ro->mat - e.mbase, "v") << "\n";
-                        oi = oe - 1;
-                        continue;
-                    }
-                }
-                const std::string c = run.size() > 1 ? diag_run(e, run, R, {"v"}) : "";
-                if (!c.empty()) {
-                    o << "        " << c << "\n";
+    for (int k = 0; k < NR; k++) o << "        v[" << k << "] = up2(lp[sl ^ " << off_in[k] << "u]);\n";
+    if (st.dense) o << "        rdense<" << R << ">(v, " << e.G << " + (z_ + " << st.mat << "));\n";
+    for (size_t oi = 0; oi < so.ops.size(); oi++) {
+        const PassOp &op = *so.ops[oi];
+        if (is_diag(op)) {
+            std::vector<const PassOp *> run;
+            size_t oe = oi;
+            for (; oe < so.ops.size() && is_diag(*so.ops[oe]); oe++) run.push_back(so.ops[oe]);
+            if (e.cuts) {
+                // phase classes first (diagonal ops commute), then the rest
+                std::vector<CutClass> cls;
+                std::vector<const PassOp *> rest;
+                split_run(e.fgrp, run, &cls, &rest);
+                if (!cls.empty()) {
+                    for (size_t ci = 0; ci < cls.size(); ci++)
+                        o << "        " << cut_apply(e, (*e.cuts)[e.cut_next++], st) << "\n";
+                    const std::string c = rest.size() > 1 ? diag_run(e, rest, R, {"v"}) : "";
+                    if (!c.empty())
+                        o << "        " << c << "\n";
+                    else
+                        for (const PassOp *ro : rest) o << "        " << apply(e, *ro, R, ro->mat - e.mbase, "v") << "\n";
                     oi = oe - 1;
                     continue;
                 }
             }
-            ConstM1 cm;
-            if (e.fgrp && const_m1(*e.fgrp, op, &cm)) {
-                o << "        " << const_m1_code(cm, op, R) << "\n";
+            const std::string c = run.size() > 1 ? diag_run(e, run, R, {"v"}) : "";
+            if (!c.empty()) {
+                o << "        " << c << "\n";
+                oi = oe - 1;
                 continue;
             }
-            o << "        " << apply(e, op, R, op.mat - e.mbase, "v") << "\n";
         }
+        ConstM1 cm;
+        if (e.fgrp && const_m1(*e.fgrp, op, &cm)) {
+            o << "        " << const_m1_code(cm, op, R) << "\n";
+            continue;
+        }
+        o << "        " << apply(e, op, R, op.mat - e.mbase, "v") << "\n";
     }
     if (!scale.empty())
         for (int k = 0; k < NR; k++) o << "        v[" << k << "].x *= " << scale << "; v[" << k << "].y *= " << scale << ";\n";
-    for (int k = 0; k < NR; k++) o << "        lp[sb ^ " << off[k] << "u] = down2(v[" << k << "]);\n";
+    for (int k = 0; k < NR; k++) o << "        lp[ss ^ " << off_out[k] << "u] = down2(v[" << k << "]);\n";
     o << "    }\n    }\n    __syncthreads();\n";
 }
 
@@ -827,12 +978,109 @@ std::string pass_scale(const Env &e, const Pass &ps)
     double s = 1.0;
     for (const Stage &st : ps.stages) {
         if (st.dense) continue;
-        for (int oi = st.op_begin; oi < st.op_end; oi++) {
+        for (const PassOp *op : stage_ops(ps, st, true).ops) {
             ConstM1 cm;
-            if (const_m1(*e.fgrp, ps.ops[oi - ps.op_offset], &cm)) s *= cm.d;
+            if (const_m1(*e.fgrp, *op, &cm)) s *= cm.d;
         }
     }
     return s == 1.0 ? "" : dbl(s);
+}
+
+// Sums of the diagonal generators of a run on the registers before it.  Every
+// term is Im sum_k +-conj(f_k) v_k with signs of a Z mask on register bits
+// (and per item of bits outside the stage): the products q_k are formed once
+// and the sign sums by a partial Walsh transform over the register bits that
+// follows only the masks needed (two FMAs per amplitude and one to two adds,
+// instead of two FMAs per amplitude and parameter).  Adds to g[gk ...];
+// false (nothing written) when an op of the run has another generator.
+bool diag_grads(std::ostream &o, const Env &e, const std::vector<const PassOp *> &run, int R, int gk)
+{
+    struct Use {
+        int g;
+        double c;
+        std::string sign;  // per item: 1 flips the sign ("" = none)
+    };
+    std::map<int, std::vector<Use>> by;  // Z mask on register bits -> its uses
+    for (const PassOp *op : run) {
+        const bool r0 = op->s0 != kFixed, r1 = op->kind == K_D2 && op->s1 != kFixed;
+        for (int j = 0; j < op->ngrad; j++, gk++) {
+            std::vector<GenTerm> gt;
+            if (!op_generator(*e.grp, *op, j, &gt)) return false;
+            for (const GenTerm &tm : gt) {
+                if (tm.x != 0) return false;
+                if (tm.z == 0) continue;  // <f|v> is real (see gen_dot)
+                int m = 0;
+                std::string sign;
+                auto item = [&](uint8_t l, uint8_t p) {
+                    const std::string b = bit(e, l, p);
+                    sign = sign.empty() ? b : sign + " ^ " + b;
+                };
+                if (tm.z & 1) {
+                    if (r0) m |= 1 << op->s0;
+                    else item(op->l0, op->p0);
+                }
+                if (tm.z & 2) {
+                    if (r1) m ^= 1 << op->s1;
+                    else item(op->l1, op->p1);
+                }
+                by[m].push_back(Use{gk, tm.c, sign});
+            }
+        }
+    }
+    if (by.empty()) return true;
+    auto use = [&](int m, const std::string &a) {
+        for (const Use &u : by[m]) {
+            const std::string w = dbl(u.c) + " * " + a;
+            if (u.sign.empty()) o << " g[" << u.g << "] += " << w << ";";
+            else o << " g[" << u.g << "] += ((" << u.sign << ") ? -(" << w << ") : " << w << ");";
+        }
+    };
+    o << "        {";
+    if (by.size() == 1) {  // one mask: its signs in the FMAs, two chains
+        const int m = by.begin()->first;
+        o << " double a_ = 0.0, b_ = 0.0;";
+        for (int k = 0; k < (1 << R); k++) {
+            const bool neg = __builtin_popcount(m & k) & 1;
+            o << " a_ = fma(" << (neg ? "-" : "") << "f[" << k << "].x, v[" << k << "].y, a_); b_ = fma(" << (neg ? "" : "-")
+              << "f[" << k << "].y, v[" << k << "].x, b_);";
+        }
+        use(m, "(a_ + b_)");
+        o << " }\n";
+        return true;
+    }
+    std::vector<std::string> q;
+    for (int k = 0; k < (1 << R); k++) {
+        q.push_back("q" + N(k) + "_");
+        o << " const double " << q.back() << " = fma(f[" << k << "].x, v[" << k << "].y, -f[" << k << "].y * v[" << k
+          << "].x);";
+    }
+    int fresh = 0;
+    std::function<void(std::vector<std::string>, int, const std::vector<int> &)> walsh =
+        [&](std::vector<std::string> a, int bits, const std::vector<int> &masks) {
+            if (masks.empty()) return;
+            if (bits == 0) {
+                use(masks[0], a[0]);
+                return;
+            }
+            const size_t h = a.size() / 2;
+            for (int d = 0; d < 2; d++) {
+                std::vector<int> ms;
+                for (int m : masks)
+                    if (((m >> (bits - 1)) & 1) == d) ms.push_back(m);
+                if (ms.empty()) continue;
+                std::vector<std::string> b;
+                for (size_t i = 0; i < h; i++) {
+                    b.push_back("w" + N(fresh++) + "_");
+                    o << " const double " << b.back() << " = " << a[i] << (d ? " - " : " + ") << a[i + h] << ";";
+                }
+                walsh(b, bits - 1, ms);
+            }
+        };
+    std::vector<int> masks;
+    for (auto &kv : by) masks.push_back(kv.first);
+    walsh(q, R, masks);
+    o << " }\n";
+    return true;
 }
 
 // A reverse stage on the tiles lp (psi) and lf (phi); the gradient partials
@@ -841,55 +1089,44 @@ std::string pass_scale(const Env &e, const Pass &ps)
 void reverse_stage(std::ostream &o, const Env &e, const Pass &ps, const Stage &st)
 {
     const int R = st.r, NR = 1 << R;
-    std::vector<uint32_t> off;
+    const StageOps so = stage_ops(ps, st, false);
+    std::vector<uint32_t> off_in, off_out;
     std::vector<std::pair<int, int>> grads;  // (register, gradient slot)
-    for (int oi = st.op_begin; oi < st.op_end; oi++) {
-        const PassOp &op = ps.ops[oi - ps.op_offset];
-        for (int j = 0; j < op.ngrad; j++) grads.emplace_back((int)grads.size(), op.gslot[j]);
-    }
+    for (const PassOp *op : so.ops)
+        for (int j = 0; j < op->ngrad; j++) grads.emplace_back((int)grads.size(), op->gslot[j]);
     o << "    {\n";
     if (!grads.empty()) o << "    double g[" << grads.size() << "] = {};\n";
-    stage_head(o, e, st, off);
+    stage_head(o, e, st, so, off_in, off_out);
     o << "        double2 v[" << NR << "], f[" << NR << "];\n";
     for (int k = 0; k < NR; k++)
-        o << "        v[" << k << "] = up2(lp[sb ^ " << off[k] << "u]); f[" << k << "] = up2(lf[sb ^ " << off[k]
+        o << "        v[" << k << "] = up2(lp[sl ^ " << off_in[k] << "u]); f[" << k << "] = up2(lf[sl ^ " << off_in[k]
           << "u]);\n";
     int gk = 0;
-    for (int oi = st.op_begin; oi < st.op_end; oi++) {
-        const PassOp &op = ps.ops[oi - ps.op_offset];
+    for (size_t oi = 0; oi < so.ops.size(); oi++) {
+        const PassOp &op = *so.ops[oi];
         // A run of diagonal ops whose gradients all come from diagonal
         // generators: the ops commute with each other and with the
         // generators, so Im<f|G|v> is the same before every op of the run;
         // all its gradients are taken first, then the run is applied to v
-        // and f as one diagonal.
+        // and f as one diagonal where that is cheaper.
         if (is_diag(op) && e.grp) {
             std::vector<const PassOp *> run;
-            std::vector<std::string> dots;
             int gkr = gk;
-            for (int oe = oi; oe < st.op_end && is_diag(ps.ops[oe - ps.op_offset]); oe++) {
-                const PassOp &ro = ps.ops[oe - ps.op_offset];
-                std::vector<std::string> od;
-                bool ok = true;
-                for (int j = 0; j < ro.ngrad && ok; j++) {
-                    std::vector<GenTerm> gt;
-                    ok = op_generator(*e.grp, ro, j, &gt);
-                    for (const GenTerm &tm : gt) ok = ok && tm.x == 0;
-                    const std::string c = ok ? gen_dot(e, ro, R, gt, "g[" + N(gkr + j) + "]") : "";
-                    ok = ok && !c.empty();
-                    od.push_back(c);
-                }
-                if (!ok) break;
-                run.push_back(&ro);
-                dots.insert(dots.end(), od.begin(), od.end());
-                gkr += ro.ngrad;
+            for (size_t oe = oi; oe < so.ops.size() && is_diag(*so.ops[oe]); oe++) {
+                run.push_back(so.ops[oe]);
+                gkr += so.ops[oe]->ngrad;
             }
-            const std::string c = run.size() > 1 ? diag_run(e, run, R, {"v", "f"}) : "";
-            if (!c.empty()) {
-                for (const std::string &d : dots) o << "        " << d << "\n";
-                o << "        " << c << "\n";
+            std::ostringstream d;
+            if (diag_grads(d, e, run, R, gk)) {
+                o << d.str();
+                const std::string c = run.size() > 1 ? diag_run(e, run, R, {"v", "f"}) : "";
+                if (!c.empty()) o << "        " << c << "\n";
+                else
+                    for (const PassOp *ro : run)
+                        for (const char *a : {"v", "f"}) o << "        " << apply(e, *ro, R, ro->mat - e.mbase, a) << "\n";
                 if (e.pin) o << "        __builtin_amdgcn_sched_barrier(0);\n";
                 gk = gkr;
-                oi = oi + (int)run.size() - 1;
+                oi += run.size() - 1;
                 continue;
             }
         }
@@ -917,7 +1154,7 @@ void reverse_stage(std::ostream &o, const Env &e, const Pass &ps, const Stage &s
         if (e.pin) o << "        __builtin_amdgcn_sched_barrier(0);\n";
     }
     for (int k = 0; k < NR; k++)
-        o << "        lp[sb ^ " << off[k] << "u] = down2(v[" << k << "]); lf[sb ^ " << off[k] << "u] = down2(f[" << k
+        o << "        lp[ss ^ " << off_out[k] << "u] = down2(v[" << k << "]); lf[ss ^ " << off_out[k] << "u] = down2(f[" << k
           << "]);\n";
     o << "    }\n";
     for (auto &gs : grads) {

@@ -1,0 +1,57 @@
+"""Generated kernels (specialize) against the oracle on circuits that mix the
+ops their stages treat specially: X and CNOT gates turned into index maps of a
+stage's loads and stores (controls inside and outside the stage and the tile,
+chains, plain X, targets and controls touched before and after) and Z-type
+gradients taken together, among rotations and diagonal gates that keep them
+from moving.  Sizes: resident circuits, states of one tile and of several."""
+import pytest
+
+from gpu_util import compare, gpu_outputs, oracle_outputs, say
+from paper_2003_02989_amd import workloads as wl
+from paper_2003_02989_amd.circuits import Circuit, sym
+
+pytestmark = pytest.mark.gpu
+
+POOLS = {
+    "x": ["X", "CNOT", "CNOT", "CNOT", "RY", "RZ", "RZ", "CZPOW"],
+    "mixed": ["X", "CNOT", "CNOT", "RX", "RY", "RZ", "ZZPOW", "RZZ", "XXPOW", "H", "SWAP", "CZ", "CNOTPOW"],
+}
+
+
+def batch(pool, n, gates, seed, B=3):
+    rng = wl.rng_for(seed)
+    c = wl.random_circuit(rng, n, gates, 7, ops=POOLS[pool])
+    obs = wl.random_observables(rng, n, 1, max_terms=8, max_weight=min(n, 4))
+    theta = rng.uniform(-3.2, 3.2, size=(B, 7)).astype("float32")
+    up = rng.standard_normal((B, 1)).astype("float32")
+    return wl.Workload(f"{pool}_n{n}", [c] * B, 7, theta, [obs] * B, up)
+
+
+@pytest.mark.parametrize("pool", sorted(POOLS))
+@pytest.mark.parametrize("n,gates", [(3, 40), (6, 90), (10, 120), (13, 160), (15, 220)])
+def test_generated_against_oracle(pool, n, gates):
+    w = batch(pool, n, gates, 9100 + n)
+    say(w.name)
+    compare(gpu_outputs(w, specialize=True), oracle_outputs(w))
+
+
+@pytest.mark.parametrize("n", [5, 14])
+def test_cnot_chains(n):
+    # a ring both ways round, X between, no op in some stages but permutations
+    c = Circuit(n)
+    for q in range(n):
+        c.add("RY", q, [sym(q % 4, 0.7 + 0.1 * q, 0.2)])
+    for q in range(n):
+        c.add("CNOT", (q, (q + 1) % n))
+    for q in range(0, n, 3):
+        c.add("X", q)
+    for q in reversed(range(n)):
+        c.add("CNOT", ((q + 1) % n, q))
+    for q in range(n):
+        c.add("RZ", q, [sym((q + 1) % 4, 1.0 - 0.05 * q)])
+        c.add("CNOT", (q, (q + 2) % n))
+    rng = wl.rng_for(77)
+    obs = wl.random_observables(rng, n, 1, max_terms=6, max_weight=3)
+    theta = rng.uniform(-3, 3, size=(2, 4)).astype("float32")
+    w = wl.Workload(f"chain_n{n}", [c] * 2, 4, theta, [obs] * 2, rng.standard_normal((2, 1)).astype("float32"))
+    compare(gpu_outputs(w, specialize=True), oracle_outputs(w))
