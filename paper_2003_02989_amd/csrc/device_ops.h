@@ -393,21 +393,6 @@ template <int R, int J, class MT> __device__ __forceinline__ void rm1r(double2 *
         a[kk] = make_double2(fma(m10, x.x, m11 * y.x), fma(m10, x.y, m11 * y.y));
     }
 }
-// dense 2x2 with real diagonal and imaginary off-diagonal entries (RX and its
-// products; their real parts, resp. imaginary parts, are exactly 0) on
-// register bit J: half the arithmetic of rm1
-template <int R, int J, class MT> __device__ __forceinline__ void rm1x(double2 *a, MT m)
-{
-    const double d0 = m[0].x, o01 = m[1].y, o10 = m[2].y, d1 = m[3].x;
-#pragma unroll
-    for (int k = 0; k < (1 << R); k++) {
-        if ((k >> J) & 1) continue;
-        const int kk = k | (1 << J);
-        const double2 x = a[k], y = a[kk];
-        a[k] = make_double2(fma(d0, x.x, -o01 * y.y), fma(d0, x.y, o01 * y.x));
-        a[kk] = make_double2(fma(d1, y.x, -o10 * x.y), fma(d1, y.y, o10 * x.x));
-    }
-}
 template <int R, int J, class MT> __device__ __forceinline__ double rm1r_dot(const double2 *a, const double2 *f, MT dm)
 {
     const double m00 = dm[0].x, m01 = dm[1].x, m10 = dm[2].x, m11 = dm[3].x;
@@ -421,6 +406,53 @@ template <int R, int J, class MT> __device__ __forceinline__ double rm1r_dot(con
         s += m00 * zdotr(f[k], x) + m01 * zdotr(f[k], y) + m10 * zdotr(f[kk], x) + m11 * zdotr(f[kk], y);
     }
     return s;
+}
+
+// Rotations as three shears w = (p, s) (see shear_of), in place: a pair of
+// real components (x, y) becomes (c x - s y, s x + c y).
+__device__ __forceinline__ void shear3(double &x, double &y, double p, double s)
+{
+    x = fma(p, y, x);
+    y = fma(s, x, y);
+    x = fma(p, y, x);
+}
+// [[c, -s], [s, c]] on register bit J
+template <int R, int J> __device__ __forceinline__ void rrot(double2 *a, double2 w)
+{
+#pragma unroll
+    for (int k = 0; k < (1 << R); k++) {
+        if ((k >> J) & 1) continue;
+        const int kk = k | (1 << J);
+        shear3(a[k].x, a[kk].x, w.x, w.y);
+        shear3(a[k].y, a[kk].y, w.x, w.y);
+    }
+}
+// c - i s on the pair (a, b): a' = c a - i s b, b' = c b - i s a
+__device__ __forceinline__ void shear3i(double2 &a, double2 &b, double p, double s)
+{
+    shear3(a.x, b.y, -p, -s);
+    shear3(a.y, b.x, p, s);
+}
+// [[c, -is], [-is, c]] on register bit J
+template <int R, int J> __device__ __forceinline__ void rrotx(double2 *a, double2 w)
+{
+#pragma unroll
+    for (int k = 0; k < (1 << R); k++) {
+        if ((k >> J) & 1) continue;
+        shear3i(a[k], a[k | (1 << J)], w.x, w.y);
+    }
+}
+// c I - i s P on register bits (LO, HI), P = XX (SG = 1) or YY (SG = -1: its
+// entry on |00>, |11> is -1)
+template <int R, int LO, int HI, int SG> __device__ __forceinline__ void rrotp(double2 *a, double2 w)
+{
+#pragma unroll
+    for (int k = 0; k < (1 << R); k++) {
+        if (((k >> LO) & 1) || ((k >> HI) & 1)) continue;
+        const int kL = k | (1 << LO), kH = k | (1 << HI), k11 = kL | kH;
+        shear3i(a[k], a[k11], SG * w.x, SG * w.y);
+        shear3i(a[kL], a[kH], w.x, w.y);
+    }
 }
 
 // dense 2x2 on register bit J applied where `on` (a control outside the
@@ -584,22 +616,6 @@ template <int R, int LO, int HI> __device__ __forceinline__ void rp2(double2 *a,
         a[k11] = zmul2(ca, v11, bs, v00);
         a[kL] = zmul2(ca, vL, cb, vH);
         a[kH] = zmul2(ca, vH, cb, vL);
-    }
-}
-// rp2 with a real and b imaginary (XX^t without its global phase, and its
-// products): half the arithmetic
-template <int R, int LO, int HI> __device__ __forceinline__ void rp2x(double2 *a, double2 ca, double2 cb, double sg)
-{
-    const double p = ca.x, q = cb.y, qs = sg * cb.y;
-#pragma unroll
-    for (int k = 0; k < (1 << R); k++) {
-        if (((k >> LO) & 1) || ((k >> HI) & 1)) continue;
-        const int kL = k | (1 << LO), kH = k | (1 << HI), k11 = kL | kH;
-        const double2 v00 = a[k], vL = a[kL], vH = a[kH], v11 = a[k11];
-        a[k] = make_double2(fma(p, v00.x, -qs * v11.y), fma(p, v00.y, qs * v11.x));
-        a[k11] = make_double2(fma(p, v11.x, -qs * v00.y), fma(p, v11.y, qs * v00.x));
-        a[kL] = make_double2(fma(p, vL.x, -q * vH.y), fma(p, vL.y, q * vH.x));
-        a[kH] = make_double2(fma(p, vH.x, -q * vL.y), fma(p, vH.y, q * vL.x));
     }
 }
 template <int R, int LO, int HI> __device__ __forceinline__ double rp2_dot(const double2 *a, const double2 *f, double2 ca, double2 cb, double sg)

@@ -157,8 +157,10 @@ std::string apply(const Env &e, const PassOp &op, int R, int mat, const std::str
     }
     switch (op.kind) {
     case K_M1:
+        if (op.hint & kHintRot)
+            return std::string((op.hint & kHintReal) ? "rrot<" : "rrotx<") + Rs + ", " + N(op.s0) + ">(" + v + ", " +
+                   ent(mat + 4) + ");";
         if (!op.ctrl && (op.hint & kHintReal)) return "rm1r<" + Rs + ", " + N(op.s0) + ">(" + v + ", " + m + ");";
-        if (!op.ctrl && (op.hint & kHintRX)) return "rm1x<" + Rs + ", " + N(op.s0) + ">(" + v + ", " + m + ");";
         if (!op.ctrl) return "rm1<" + Rs + ", " + N(op.s0) + ">(" + v + ", " + m + ");";
         if (op.s1 != kFixed) return "rm1c<" + Rs + ", " + N(op.s0) + ", " + N(op.s1) + ">(" + v + ", " + m + ");";
         return "rm1_on<" + Rs + ", " + N(op.s0) + ">(" + v + ", " + m + ", " + bit(e, op.l1, op.p1) + " == " +
@@ -172,9 +174,9 @@ std::string apply(const Env &e, const PassOp &op, int R, int mat, const std::str
                    ((op.hint & kHintRX) ? "true" : "false") + ">(" + v + ", " + m + ");";
         return "rf2<" + Rs + ", " + N(op.s0) + ", " + N(op.s1) + ">(" + v + ", " + m + ");";
     case K_P2:
-        return std::string((op.hint & kHintRX) ? "rp2x<" : "rp2<") + Rs + ", " + N(std::min(op.s0, op.s1)) + ", " +
-               N(std::max(op.s0, op.s1)) + ">(" + v + ", " + ent(mat) + ", " + ent(mat + 1) + ", " +
-               (op.ptype == 2 ? "-1.0" : "1.0") + ");";
+        // (always a rotation: XX^t, YY^t and their products)
+        return "rrotp<" + Rs + ", " + N(std::min(op.s0, op.s1)) + ", " + N(std::max(op.s0, op.s1)) + ", " +
+               (op.ptype == 2 ? "-1" : "1") + ">(" + v + ", " + ent(mat + 2) + ");";
     default: return diag_call(e, op, R, mat, false, v) + ";";
     }
 }

@@ -290,10 +290,42 @@ __device__ __forceinline__ void resolve(const BuildCtx &c, const GateDev &gd, do
     for (int j = 0; j < gd.np; j++) eta[j] = slot_value(c, gd.slot0 + j);
 }
 
+// Half turns of a forward rotation task: rint(phi / pi) of its angle phi (the
+// sum over its members, all about one axis), the matrix being cos phi I - i
+// sin phi G.
+__device__ __forceinline__ int rot_turns(const BuildTask &bt, const BuildCtx &c)
+{
+    double phi = 0.0;  // in units of pi
+    for (int mi = 0; mi < bt.mem_count; mi++) {
+        const GateDev gd = c.gates[c.members[bt.mem_begin + mi].gate];
+        const double eta = gd.np ? slot_value(c, gd.slot0) : 0.5;  // sqrt X, sqrt Y: G^(1/2)
+        phi += gd.op == OP_RX || gd.op == OP_RY ? eta * (0.5 / 3.14159265358979323846) : 0.5 * eta;
+    }
+    return (int)((long long)rint(phi) & 1);
+}
+
+// Rotation [[c, -s], [s, c]] up to its sign as three shears: with c >= 0 it is
+// [1 p; 0 1] [1 0; s 1] [1 p; 0 1], p = -s / (1 + c), |p| <= 1: three FMAs per
+// pair and component, in place, where the matrix takes two multiplies and two
+// FMAs into new registers (QAOA cost, 20 qubits x 256 rows: the VALU-bound
+// passes 7.1 -> 6.7 ms per step; VQE forward passes, 16 qubits x 4096 rows,
+// 16.8 -> 14.8 ms together with the X index maps).  A rotation with c < 0 is taken as minus the one by
+// the angle less pi; `odd` says so (forward tasks: from the angle itself, so
+// that the row's phase, which takes these signs up, counts the same ones).
+__device__ __forceinline__ double2 shear_of(double c, double s, bool odd)
+{
+    if (odd) {
+        c = -c;
+        s = -s;
+    }
+    return make_double2(-s / (1.0 + c), s);
+}
+
 // One build task for one row: symbol resolution eta = scale*theta + offset
 // and the fused product / dagger / derivative, all in float64.  D is the
 // matrix dimension; fixed at compile time so every array stays in registers.
-template <int D> __device__ __forceinline__ void build_task_d(const BuildTask &bt, const BuildCtx &c, double2 *out)
+// Returns 1 when its shears leave out a sign that belongs to the row's phase.
+template <int D> __device__ __forceinline__ int build_task_d(const BuildTask &bt, const BuildCtx &c, double2 *out)
 {
     cd acc[16], g[16];
 #pragma unroll
@@ -362,12 +394,17 @@ template <int D> __device__ __forceinline__ void build_task_d(const BuildTask &b
 #pragma unroll
         for (int i = 0; i < D * D; i++) out[i] = make_double2(acc[i].x, acc[i].y);
     }
+    if (bt.kind == BT_DERIV || bt.which == BX_NONE) return 0;
+    const bool fwd = bt.kind == BT_PRODUCT;
+    const double cr = acc[0].x, sr = D == 4 ? -out[1].y : bt.which == BX_REAL ? acc[D].x : -acc[D].y;
+    const bool odd = fwd ? rot_turns(bt, c) != 0 : cr < 0.0;
+    out[D == 4 ? 2 : 4] = shear_of(cr, sr, odd);
+    return fwd && odd;
 }
 
-__device__ __forceinline__ void build_task(const BuildTask &bt, const BuildCtx &c, double2 *out)
+__device__ __forceinline__ int build_task(const BuildTask &bt, const BuildCtx &c, double2 *out)
 {
-    if (bt.dim == 2) build_task_d<2>(bt, c, out);
-    else build_task_d<4>(bt, c, out);
+    return bt.dim == 2 ? build_task_d<2>(bt, c, out) : build_task_d<4>(bt, c, out);
 }
 
 // --------------------------------------------------- matrix build kernel
@@ -390,15 +427,22 @@ __global__ __launch_bounds__(256) void k_build_mats(BuildArgs a)
                a.slot_scale + (a.uniform ? 0 : (int64_t)src * a.n_slots),
                a.slot_off + (a.uniform ? 0 : (int64_t)src * a.n_slots), a.explicit_mats,
                a.theta + (int64_t)b * a.S, a.noise_seed, b, shift, a.x_eps};
+    int odd = 0;
     if (ti < a.task_end) {
         const BuildTask bt = a.tasks[ti];
-        build_task(bt, c, a.mats + (int64_t)row * a.mat_stride + bt.out);
+        odd = build_task(bt, c, a.mats + (int64_t)row * a.mat_stride + bt.out);
     }
     if (a.phase_out < 0 || blockIdx.x != 0) return;
     // the row's global phase (block 0 of the row; its thread 0 built the
     // product-init matrix at phase_out), reduced in a fixed order
     __shared__ double part[4];
-    double ph = 0.0;
+    // (signs the shears of forward rotations leave out: this block's tasks,
+    // then the tasks of the row's other blocks)
+    for (int j = ti + blockDim.x; j < a.rot_end; j += blockDim.x) {
+        const BuildTask bt = a.tasks[j];
+        if (bt.kind == BT_PRODUCT && bt.which != BX_NONE) odd += rot_turns(bt, c);
+    }
+    double ph = odd * 3.14159265358979323846;
     for (int j = threadIdx.x; j < a.n_phase; j += blockDim.x) {
         const PhaseTerm pt = a.phase_terms[j];
         ph += pt.slot >= 0 ? pt.c * slot_value(c, pt.slot) : pt.c;
@@ -435,7 +479,8 @@ __global__ __launch_bounds__(256) void k_copy_source(BuildArgs a, int nrows)
 // row (a move's list holds a task or two); the row's global phase, as in
 // k_build_mats, multiplied into the product-init task when it heads the
 // list, else the change of the moved parameters' phase terms multiplied into
-// the copied product-init matrix.
+// the copied product-init matrix.  (The signs of the rotations' shears are
+// left out: derived rows only give expectations.)
 __global__ __launch_bounds__(256) void k_build_list(BuildArgs a, int nrows)
 {
     const int row = blockIdx.x * blockDim.x + threadIdx.x;

@@ -320,6 +320,7 @@ struct Planner {
         g.mat_block += entries;
         return o;
     }
+    // which: the derivative's parameter, or the TaskExtra entry of other tasks
     int add_task(uint8_t kind, int dim, int storage, int which, const std::vector<Member> &mem)
     {
         BuildTask bt{};
@@ -327,7 +328,8 @@ struct Planner {
         bt.dim = (uint8_t)dim;
         bt.diag = (uint8_t)storage;
         bt.which = (uint8_t)which;
-        bt.out = alloc(storage == 1 ? dim : storage == 4 ? 6 : storage >= 2 ? 2 : dim * dim);
+        bt.out = alloc((storage == 1 ? dim : storage == 4 ? 6 : storage >= 2 ? 2 : dim * dim) +
+                       (kind != BT_DERIV && which != BX_NONE));
         bt.mem_begin = (int32_t)g.members.size();
         bt.mem_count = (int32_t)mem.size();
         for (const auto &m : mem) g.members.push_back(m);
@@ -410,6 +412,7 @@ int op_cost(const PassOp &op, int dispatch)
     if (generated && op.kind == K_D1) c = 2 * (2 - __builtin_popcount(op.hint & 3u));
     if (generated && op.kind == K_D2) c = 4 - __builtin_popcount(op.hint & 15u);
     if (op.kind == K_M1) c = op.ctrl || (op.hint & (kHintReal | kHintRX)) ? 4 : 8;
+    if (op.kind == K_M1 && (op.hint & kHintRot)) c = 3;
     if (op.kind == K_M2) c = 16;
     if (op.kind == K_F2) {
         c = (op.hint & kHintRX) ? 4 : 6;
@@ -421,7 +424,7 @@ int op_cost(const PassOp &op, int dispatch)
             c = (ph + blk + 3) / 4;
         }
     }
-    if (op.kind == K_P2) c = 8;
+    if (op.kind == K_P2) c = (op.hint & kHintRot) ? 3 : 8;
     return c + dispatch;
 }
 
@@ -797,6 +800,32 @@ uint8_t op_hint(const Group &g, const PassOp &op, const std::vector<Member> &mem
     return 0;
 }
 
+// The shears a generated kernel applies an op fusing `mem` with: rotations
+// about one axis (RY, Y^t, sqrt Y: real; RX, X^t, sqrt X: RX-form; XX^t and
+// YY^t: pairs).
+TaskExtra op_shears(const Group &g, const PassOp &op, const std::vector<Member> &mem)
+{
+    if (op.kind == K_P2) return (op.hint & kHintRX) ? BX_RX : BX_NONE;
+    if (op.kind != K_M1 || op.ctrl) return BX_NONE;
+    bool y = true, x = true;
+    for (const Member &m : mem) {
+        const int o = g.gates[m.gate].op;
+        y = y && (o == OP_RY || o == OP_YPOW || o == OP_SQRTY);
+        x = x && (o == OP_RX || o == OP_XPOW || o == OP_SQRTX);
+    }
+    return y ? BX_REAL : x ? BX_RX : BX_NONE;
+}
+
+// Every parameter of every member is a constant, the same on every row.
+bool constant_op(const Group &g, const std::vector<Member> &mem)
+{
+    if (!g.uniform_slots && g.rows.size() > 1) return false;
+    for (const Member &m : mem)
+        for (int j = 0; j < g.gates[m.gate].np; j++)
+            if (g.slot_sym[g.gates[m.gate].slot0 + j] >= 0) return false;
+    return true;
+}
+
 // Generator terms of gate `opcode` w.r.t. its parameter `which`, in the op
 // frame: a controlled gate's op has its target as q0 and its control as q1,
 // every other two-qubit op keeps the gate's qubit order (q0 the first).
@@ -1052,9 +1081,14 @@ void plan_group(Group &g, const Options &opt, int S)
         }
         ps.mat_begin = pi == 0 ? 0 : g.mat_block;
         for (auto &ob : ops) {
-            int ti = P.add_task(BT_PRODUCT, op_dim(ob.op), storage_of(ob.op), 0, ob.mem);
-            ob.op.mat = g.tasks[ti].out;
             ob.op.hint = op_hint(g, ob.op, ob.mem);
+            // (constant single-qubit ops are written out by the generated
+            // kernels with their structure, cheaper than shears)
+            const bool written = ob.op.kind == K_M1 && constant_op(g, ob.mem);
+            const TaskExtra ex = opt.specialize && !written ? op_shears(g, ob.op, ob.mem) : BX_NONE;
+            if (ex != BX_NONE) ob.op.hint |= kHintRot;
+            int ti = P.add_task(BT_PRODUCT, op_dim(ob.op), storage_of(ob.op), ex, ob.mem);
+            ob.op.mat = g.tasks[ti].out;
             if (ob.op.kind == K_F2 && ob.mem.size() == 1 && fsim_swap_block(g, ob.mem[0].gate))
                 ob.op.hint |= kHintSwap;
             ps.ops.push_back(ob.op);
@@ -1108,9 +1142,11 @@ void plan_group(Group &g, const Options &opt, int S)
             PassOp op = base_op(g, ps.geom, gi, n);
             const int dim = op_dim(op), diag = storage_of(op);
             Member m{gi, 0, (uint8_t)(cls == C_CTRL ? FORM_CBLOCK : FORM_FULL), {0, 0}};
-            int ti = P.add_task(BT_DAGGER, dim, diag, 0, {m});
-            op.mat = g.tasks[ti].out;
             op.hint = op_hint(g, op, {m});  // W^dagger keeps the structure of W
+            const TaskExtra ex = opt.specialize ? op_shears(g, op, {m}) : BX_NONE;
+            if (ex != BX_NONE) op.hint |= kHintRot;
+            int ti = P.add_task(BT_DAGGER, dim, diag, ex, {m});
+            op.mat = g.tasks[ti].out;
             op.ngrad = 0;
             for (int j = 0; j < g.gates[gi].np; j++) {
                 int slot = g.gates[gi].slot0 + j;
@@ -1152,8 +1188,17 @@ void plan_group(Group &g, const Options &opt, int S)
             st.mat = g.mat_block;
             g.mat_block += 1 << (2 * st.r);
             g.dense_stages.push_back({(int)(&ps - g.fwd.data()), (int)(&st - ps.stages.data())});
+            // (the stage's matrix is built from the op matrices, signs included)
+            for (int k = st.op_begin - ps.op_offset; k < st.op_end - ps.op_offset; k++) {
+                PassOp &op = ps.ops[k];
+                if ((op.kind != K_M1 && op.kind != K_P2) || !(op.hint & kHintRot)) continue;
+                op.hint &= (uint8_t)~kHintRot;
+                g.tasks[task_at.at(op.mat)].which = BX_NONE;
+            }
         }
     }
+    for (int ti = g.fwd_tasks.begin; ti < g.fwd_tasks.end; ti++)
+        g.rot = g.rot || (g.tasks[ti].kind == BT_PRODUCT && g.tasks[ti].which != BX_NONE);
     off = 0;
     for (Pass &ps : g.rev) {
         ps.op_offset = off;

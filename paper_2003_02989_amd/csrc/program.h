@@ -104,6 +104,7 @@ struct Group {
     int32_t fwd_mat_end = 0;                    // forward matrices (with the product init) end here
     std::vector<std::pair<int, int>> dense_stages;  // (forward pass, stage) with a stage matrix
     std::vector<PhaseTerm> phase_terms;         // the row's global phase, linear in the parameters
+    bool rot = false;                           // forward rotations run as shears (their signs join the phase)
     std::vector<Occurrence> occurrences;        // symbolic blob parameters, in gate and parameter order
 };
 

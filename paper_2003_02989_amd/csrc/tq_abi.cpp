@@ -382,8 +382,9 @@ void build_mats(tq_program p, size_t gi, const float *theta, int begin, int end,
     a.phase_list = rr.phase_list;
     // the first qubit's product-init matrix (built by the range's first
     // task) carries the row's global phase
-    const bool init = g.n > 0 && begin == g.fwd_tasks.begin && end > begin && !g.phase_terms.empty();
+    const bool init = g.n > 0 && begin == g.fwd_tasks.begin && end > begin && (!g.phase_terms.empty() || g.rot);
     a.phase_out = init ? g.init_mat[0] : -1;
+    a.rot_end = g.rot ? g.fwd_tasks.end : 0;
     a.n_phase = (int32_t)g.phase_terms.size();
     a.phase_terms = (const PhaseTerm *)gd.phase_terms.p;
     a.noise_seed = p->noise_seed;
@@ -2034,7 +2035,7 @@ tq_status tq_program_describe(tq_program prog, char *buf, size_t cap, size_t *ne
             for (size_t t = 0; t < g.tasks.size(); t++) {
                 const BuildTask &bt = g.tasks[t];
                 o << (t ? "," : "") << "[" << (int)bt.kind << "," << (int)bt.dim << "," << (int)bt.diag << ","
-                  << (int)bt.which << "," << bt.out << ",[";
+                  << (bt.kind == BT_DERIV ? (int)bt.which : 0) << "," << bt.out << ",[";
                 for (int m = 0; m < bt.mem_count; m++) {
                     const Member &mb = g.members[bt.mem_begin + m];
                     o << (m ? "," : "") << "[" << mb.gate << "," << (int)mb.swapped << "," << (int)mb.form << "]";

@@ -79,9 +79,17 @@ struct BuildTask {
     uint8_t dim;    // 2 or 4
     uint8_t diag;   // storage: 0 dense, 1 diagonal (dim entries), 2 / 3 the pair (a, b) of
                     // a I + b XX / a I + b YY, 4 the six entries of an excitation-preserving 4x4
-    uint8_t which;  // BT_DERIV parameter index
+    uint8_t which;  // BT_DERIV: parameter index; else what follows the matrix (TaskExtra)
     int32_t out;    // offset (complex entries) in the row's matrix block
     int32_t mem_begin, mem_count;
+};
+
+// The entry a product or dagger task of a generated kernel appends to its
+// matrix: the shears of a rotation (see shear_of in the builder).
+enum TaskExtra : uint8_t {
+    BX_NONE = 0,
+    BX_REAL = 1,    // rotation [[c, -s], [s, c]]
+    BX_RX = 2,      // [[c, -is], [-is, c]], or the pair (c, -is) of c I - i s P
 };
 
 // Kinds of ops a tile pass applies.
@@ -106,6 +114,9 @@ constexpr uint8_t kHintRX = 64;
 // sine within 1e-15 of 1 in every row: its diagonal entries, ~6e-17, are
 // taken as 0 and the off-diagonal ones as exactly -i)
 constexpr uint8_t kHintSwap = 128;
+// K_M1, K_P2, ops of generated kernels: a rotation whose shears follow its
+// matrix (BX_REAL with kHintReal, else BX_RX)
+constexpr uint8_t kHintRot = 1;
 struct PassOp {
     uint8_t kind;
     uint8_t l0, l1;   // local bit of q0 / q1 in the tile, kFixed if outside

@@ -3,7 +3,10 @@ ops their stages treat specially: X and CNOT gates turned into index maps of a
 stage's loads and stores (controls inside and outside the stage and the tile,
 chains, plain X, targets and controls touched before and after) and Z-type
 gradients taken together, among rotations and diagonal gates that keep them
-from moving.  Sizes: resident circuits, states of one tile and of several."""
+from moving; and rotations applied as shears, at the angles where a shear
+changes sign or its entries are extreme.  Sizes: resident circuits, states
+of one tile and of several."""
+import numpy as np
 import pytest
 
 from gpu_util import compare, gpu_outputs, oracle_outputs, say
@@ -54,4 +57,29 @@ def test_cnot_chains(n):
     obs = wl.random_observables(rng, n, 1, max_terms=6, max_weight=3)
     theta = rng.uniform(-3, 3, size=(2, 4)).astype("float32")
     w = wl.Workload(f"chain_n{n}", [c] * 2, 4, theta, [obs] * 2, rng.standard_normal((2, 1)).astype("float32"))
+    compare(gpu_outputs(w, specialize=True), oracle_outputs(w))
+
+
+@pytest.mark.parametrize("n", [4, 13, 14])
+def test_rotation_shears_at_special_angles(n):
+    # multiples of pi/2 and their neighbours, many turns, tiny angles: states
+    # compare with their phase (a sign left out by a shear joins the row's
+    # phase), and fused rotations about one axis take the sum of their angles
+    pi = np.pi
+    angles = [0.0, pi / 2, pi, -pi, 3 * pi / 2, 2 * pi, -2 * pi, 3 * pi, 4 * pi, 1e-7, pi - 1e-6, pi + 1e-6, 41.3, -57.9]
+    rng = wl.rng_for(31 + n)
+    c = Circuit(n)
+    for q in range(n):
+        c.add("H", q)
+        c.add("CZ", (q, (q + 1) % n))
+    for j, op in enumerate(["RY", "RX", "YPOW", "XPOW"] * 2):
+        for q in range(n):
+            c.add(op, q, [sym((j + q) % 5, 1.0 if op[0] == "R" else 1.0 / pi)])
+            if q % 3 == 0:  # a second rotation about the same axis fuses
+                c.add(op, q, [sym((j + q + 1) % 5, -0.5)])
+        c.add("XXPOW" if j % 2 else "YYPOW", (j % n, (j + 2) % n), [sym(j % 5, 1.0 / pi)])
+        c.add("CNOT", (j % n, (j + 1) % n))
+    theta = rng.choice(angles, size=(6, 5)).astype("float32")
+    obs = wl.random_observables(rng, n, 1, max_terms=6, max_weight=3)
+    w = wl.Workload(f"angles_n{n}", [c] * 6, 5, theta, [obs] * 6, np.ones((6, 1), "float32"))
     compare(gpu_outputs(w, specialize=True), oracle_outputs(w))
