@@ -26,6 +26,13 @@ template <class T> __device__ __forceinline__ T cget(const T *p, int64_t i)
     return v;
 }
 
+// A pointer known to point into device memory (one read from an argument
+// table would otherwise be accessed with flat instructions).
+template <class T> __device__ __forceinline__ T *as_global(T *p)
+{
+    return (T *)(__attribute__((address_space(1))) T *)p;
+}
+
 __device__ __forceinline__ double2 up2(float2 a) { return make_double2((double)a.x, (double)a.y); }
 __device__ __forceinline__ float2 down2(double2 a) { return make_float2((float)a.x, (float)a.y); }
 __device__ __forceinline__ double2 zmul(double2 a, double2 b)
@@ -171,7 +178,7 @@ __device__ __forceinline__ void tile_copy(const TileCtx &tc, float2 *lds, float2
     }
 }
 
-__device__ void build_hi_off(const TileGeom &g, uint64_t *hi_off)
+template <class G> __device__ __forceinline__ void build_hi_off(const G &g, uint64_t *hi_off)
 {
     for (int j = threadIdx.x; j < (1 << g.h); j += blockDim.x) {
         uint64_t o = 0;
@@ -1196,9 +1203,11 @@ __device__ __forceinline__ float2 h_elem(uint32_t l, uint64_t fb, const TermDev 
 // The resident computation in three parts around the forward and reverse
 // register stages (which the generic kernel loops over and a specialised
 // kernel spells out).  acc: one accumulator row per wave (terms, then
-// gradient slots); lp/lf: psi/phi of the row in LDS.
-template <class MT>
-__device__ __forceinline__ void resident_begin(const ResArgs &a, MT M, double *acc, float2 *lp, int tid, int nt)
+// gradient slots); lp/lf: psi/phi of the row in LDS.  a: the group's ResArgs
+// (kernel argument or table entry); c: the call's pointers (a ResCall, or the
+// ResArgs again).
+template <class A, class MT>
+__device__ __forceinline__ void resident_begin(const A &a, MT M, double *acc, float2 *lp, int tid, int nt)
 {
     const int n = a.n;
     const uint32_t T = 1u << n;
@@ -1213,7 +1222,9 @@ __device__ __forceinline__ void resident_begin(const ResArgs &a, MT M, double *a
 }
 
 // state output, expectation terms, and (adjoint) phi = H_g psi
-__device__ __forceinline__ void resident_middle(const ResArgs &a, double *acc, float2 *lp, float2 *lf, int row, int tid, int nt)
+template <class A, class C>
+__device__ __forceinline__ void resident_middle(const A &a, const C &c, double *acc, float2 *lp, float2 *lf, int row,
+                                                int tid, int nt)
 {
     const int n = a.n;
     const uint32_t T = 1u << n;
@@ -1223,8 +1234,8 @@ __device__ __forceinline__ void resident_middle(const ResArgs &a, double *acc, f
     // table and the HBM partner pointer are never used (valid LDS addresses
     // are passed instead of null pointers)
     TileCtx tc{reinterpret_cast<const uint64_t *>(acc), T - 1, n};
-    if (a.state_out) {
-        float2 *out = a.state_out + (int64_t)a.out_rows[row] * a.out_stride;
+    if (c.state_out) {
+        float2 *out = c.state_out + (int64_t)a.out_rows[row] * a.out_stride;
         for (uint32_t l = tid; l < T; l += nt) out[l] = lp[sw(l)];
     }
     const TermDev *terms = a.terms ? a.terms + cget(a.row_term_begin, row) : nullptr;
@@ -1233,15 +1244,16 @@ __device__ __forceinline__ void resident_middle(const ResArgs &a, double *acc, f
         double v = wave_sum(term_tile_sum(cget(terms, k), tc, lp, lp, 0, n, tid, nt));
         if (lane == 0) acc[wave * a.nacc + k] += v;
     }
-    if (a.grad) {
-        const float *up = a.upstream + (int64_t)b * a.K;
+    if (c.grad) {
+        const float *up = c.upstream + (int64_t)b * a.K;
         for (uint32_t l = tid; l < T; l += nt) lf[sw(l)] = h_elem(l, 0, terms, nterm, up, lp, tc, lp);
         __syncthreads();
     }
 }
 
 // outputs: expectations and gradients, reduced over the waves in a fixed order
-__device__ __forceinline__ void resident_end(const ResArgs &a, double *acc, int row, int tid, int nt)
+template <class A, class C>
+__device__ __forceinline__ void resident_end(const A &a, const C &c, double *acc, int row, int tid, int nt)
 {
     __syncthreads();
     const int b = cget(a.rows, row);
@@ -1253,16 +1265,16 @@ __device__ __forceinline__ void resident_end(const ResArgs &a, double *acc, int 
         for (int w = 0; w < nw; w++) s += acc[w * a.nacc + j];
         return s;
     };
-    if (a.exp_out)
+    if (c.exp_out)
         for (int k = tid; k < a.K; k += nt) {
             double sum = 0;
             for (int ti = 0; ti < nterm; ti++) {
                 const TermDev tm = cget(terms, ti);
                 if (tm.k == k) sum += tm.coeff * total(ti);
             }
-            a.exp_out[(int64_t)b * a.K + k] = (float)sum;
+            c.exp_out[(int64_t)b * a.K + k] = (float)sum;
         }
-    if (a.grad) {
+    if (c.grad) {
         const double *scale = a.slot_scale + (a.uniform ? 0 : (int64_t)row * a.n_slots);
         for (int s = tid; s < a.S; s += nt) {
             double sum = 0;
@@ -1270,7 +1282,7 @@ __device__ __forceinline__ void resident_end(const ResArgs &a, double *acc, int 
                 const int gs = a.sym_gslots[k];
                 sum += 2.0 * scale[a.gslot_slot[gs]] * total(a.gacc + gs);
             }
-            a.grad[(int64_t)b * a.S + s] = (float)sum;
+            c.grad[(int64_t)b * a.S + s] = (float)sum;
         }
     }
 }
@@ -1293,9 +1305,11 @@ struct PassCtx {
     int row, w, a1;
 };
 
-__device__ __forceinline__ PassCtx pass_setup(const PassArgs &a, unsigned char *smem)
+// state: the states' array; bid: the workgroup's number among the group's
+template <class A>
+__device__ __forceinline__ PassCtx pass_setup(const A &a, float2 *state, int bid, unsigned char *smem)
 {
-    const TileGeom &g = a.g;
+    const auto &g = a.g;
     const int t = g.t;
     PassCtx c;
     c.lds = reinterpret_cast<float2 *>(smem);
@@ -1304,9 +1318,9 @@ __device__ __forceinline__ PassCtx pass_setup(const PassArgs &a, unsigned char *
     c.p1 = c.lm + (a.mat_end - a.mat_begin);
     c.a1 = t / 2;
     c.p2 = c.p1 + (1 << c.a1);
-    c.row = blockIdx.x / a.wg_per_row;
-    c.w = blockIdx.x % a.wg_per_row;
-    c.st = a.state + (int64_t)cget(a.rows, c.row) * a.row_stride;
+    c.row = bid / a.wg_per_row;
+    c.w = bid % a.wg_per_row;
+    c.st = as_global(state) + (int64_t)cget(a.rows, c.row) * a.row_stride;
     build_hi_off(g, c.hi_off);
     stage_mats(c.lm, a.mats + (int64_t)c.row * a.mat_stride, a.mat_begin, a.mat_end);
     __syncthreads();
@@ -1333,9 +1347,9 @@ __device__ __forceinline__ PassCtx pass_setup(const PassArgs &a, unsigned char *
 }
 
 // the tile with fixed bits fb into LDS (generated product state in the first pass)
-__device__ __forceinline__ void pass_load(const PassArgs &a, const PassCtx &c, uint64_t fb)
+template <class A> __device__ __forceinline__ void pass_load(const A &a, const PassCtx &c, uint64_t fb)
 {
-    const TileGeom &g = a.g;
+    const auto &g = a.g;
     const int T = 1 << g.t;
     if (a.product_init) {
         const double2 *M = c.lm;
@@ -1353,7 +1367,7 @@ __device__ __forceinline__ void pass_load(const PassArgs &a, const PassCtx &c, u
     }
 }
 
-__device__ __forceinline__ void pass_store(const PassArgs &a, const PassCtx &c, uint64_t fb)
+template <class A> __device__ __forceinline__ void pass_store(const A &a, const PassCtx &c, uint64_t fb)
 {
     TileCtx tc{c.hi_off, (1u << a.g.c) - 1, a.g.c};
     tile_copy<false>(tc, c.lds, c.st, fb, 1 << a.g.t);
@@ -1368,9 +1382,9 @@ struct RevCtx {
     int row, w;
 };
 
-__device__ __forceinline__ RevCtx rev_setup(const RevArgs &a, unsigned char *smem)
+template <class A> __device__ __forceinline__ RevCtx rev_setup(const A &a, int bid, unsigned char *smem)
 {
-    const TileGeom &g = a.g;
+    const auto &g = a.g;
     const uint32_t T = 1u << g.t;
     RevCtx c;
     c.lp = reinterpret_cast<float2 *>(smem);
@@ -1378,11 +1392,11 @@ __device__ __forceinline__ RevCtx rev_setup(const RevArgs &a, unsigned char *sme
     c.hi_off = reinterpret_cast<uint64_t *>(c.lf + T);
     c.lm = reinterpret_cast<double2 *>(c.hi_off + (1 << g.h));
     c.acc = reinterpret_cast<double *>(c.lm + (a.mat_end - a.mat_begin));
-    c.row = blockIdx.x / a.wg_per_row;
-    c.w = blockIdx.x % a.wg_per_row;
+    c.row = bid / a.wg_per_row;
+    c.w = bid % a.wg_per_row;
     const int b = cget(a.rows, c.row);
-    c.sp = a.psi + (int64_t)b * a.row_stride;
-    c.sf = a.phi + (int64_t)b * a.row_stride;
+    c.sp = as_global(a.psi) + (int64_t)b * a.row_stride;
+    c.sf = as_global(a.phi) + (int64_t)b * a.row_stride;
     build_hi_off(g, c.hi_off);
     stage_mats(c.lm, a.mats + (int64_t)c.row * a.mat_stride, a.mat_begin, a.mat_end);
     for (int j = threadIdx.x; j < 4 * a.gcount; j += blockDim.x) c.acc[j] = 0;
@@ -1390,14 +1404,14 @@ __device__ __forceinline__ RevCtx rev_setup(const RevArgs &a, unsigned char *sme
     return c;
 }
 
-__device__ __forceinline__ void rev_load(const RevArgs &a, const RevCtx &c, uint64_t fb)
+template <class A> __device__ __forceinline__ void rev_load(const A &a, const RevCtx &c, uint64_t fb)
 {
     TileCtx tc{c.hi_off, (1u << a.g.c) - 1, a.g.c};
     tile_copy<true>(tc, c.lp, c.sp, fb, 1 << a.g.t);
     tile_copy<true>(tc, c.lf, c.sf, fb, 1 << a.g.t);
 }
 
-__device__ __forceinline__ void rev_store(const RevArgs &a, const RevCtx &c, uint64_t fb)
+template <class A> __device__ __forceinline__ void rev_store(const A &a, const RevCtx &c, uint64_t fb)
 {
     if (!a.store) return;
     TileCtx tc{c.hi_off, (1u << a.g.c) - 1, a.g.c};
@@ -1406,7 +1420,7 @@ __device__ __forceinline__ void rev_store(const RevArgs &a, const RevCtx &c, uin
 }
 
 // the workgroup's gradient partials, waves summed in a fixed order
-__device__ __forceinline__ void rev_finish(const RevArgs &a, const RevCtx &c)
+template <class A> __device__ __forceinline__ void rev_finish(const A &a, const RevCtx &c)
 {
     double *out = a.gpart + ((int64_t)c.row * a.wg_per_row + c.w) * a.n_gslots + a.gbase;
     for (int j = threadIdx.x; j < a.gcount; j += blockDim.x)

@@ -1226,12 +1226,12 @@ std::string resident_source(const Group &g)
         for (size_t si = 0; si < ps.stages.size(); si++)
             forward_stage(o, e, ps, ps.stages[si], si + 1 == ps.stages.size() ? scale : "");
     }
-    o << "    resident_middle(a, acc, lp, lf, blockIdx.x, tid, " << nt << ");\n"
+    o << "    resident_middle(a, a, acc, lp, lf, blockIdx.x, tid, " << nt << ");\n"
          "    if (a.grad) {\n";
     for (const Pass &ps : g.rev)
         for (const Stage &st : ps.stages) reverse_stage(o, e, ps, st);
     o << "    }\n"
-         "    resident_end(a, acc, blockIdx.x, tid, " << nt << ");\n"
+         "    resident_end(a, a, acc, blockIdx.x, tid, " << nt << ");\n"
          "}\n"
          "} // namespace tq\n";
     return o.str();
@@ -1331,7 +1331,7 @@ std::string pass_kernel_source(const Group &g, int pass)
     o << "extern \"C\" __global__ __launch_bounds__(256, " << minwg << ") void tq_fwd_" << pass
       << "(PassArgs a)\n{\n"
          "    extern __shared__ __align__(16) unsigned char smem[];\n"
-         "    const PassCtx c = pass_setup(a, smem);\n"
+         "    const PassCtx c = pass_setup(a, a.state, blockIdx.x, smem);\n"
          // op matrices through the scalar cache (SGPR operands of the FMAs),
          // not from the LDS copy: the stages' LDS traffic is the tile alone
          "    const SMat M = smat(a.mats + (int64_t)c.row * a.mat_stride + a.mat_begin);\n"
@@ -1430,7 +1430,7 @@ std::string rev_pass_kernel_source(const Group &g, int pass)
     o << "extern \"C\" __global__ __launch_bounds__(256, 2) void tq_rev_" << pass
       << "(RevArgs a)\n{\n"
          "    extern __shared__ __align__(16) unsigned char smem[];\n"
-         "    const RevCtx c = rev_setup(a, smem);\n"
+         "    const RevCtx c = rev_setup(a, blockIdx.x, smem);\n"
          // matrices through the scalar cache, as in the forward passes
          "    const SMat M = smat(a.mats + (int64_t)c.row * a.mat_stride + a.mat_begin);\n"
          "    float2 *lp = c.lp, *lf = c.lf;\n"

@@ -214,6 +214,31 @@ struct ResArgs {
     float *grad;
 };
 
+// The pointers of one call on a batch of different structures; the argument
+// tables of the merged launches hold everything else.
+struct ResCall {
+    const float *theta;
+    uint64_t noise_seed;
+    float2 *state_out;      // simulated states (NULL: into the workspace)
+    float *exp_out;
+    const float *upstream;
+    float *grad;
+};
+// The tail [from, to) of the simulated states of a structure's rows.
+struct ZeroArgs {
+    int64_t row_stride;
+    const int32_t *rows;
+    int64_t from, to;
+};
+constexpr int kZeroBlock = 4096;  // amplitudes one workgroup clears
+// The steps that merged launches run.
+enum BatchKind { BK_BUILD, BK_STAGE, BK_RESIDENT, BK_PASS, BK_PAULI, BK_PAULI_REDUCE, BK_REV, BK_GRAD_REDUCE, BK_ZERO };
+// One workgroup of a merged launch: its argument block in the table and its
+// number among the workgroups of that block.
+struct BatchBlock {
+    int32_t arg, block;
+};
+
 struct GradReduceArgs {
     const int32_t *rows;
     const double *gpart;

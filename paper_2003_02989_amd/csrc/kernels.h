@@ -27,7 +27,7 @@ hipError_t profile_read(int64_t *launches, double *total_ms);
 // an opcode without that matrix).
 int gate_table_host(int op, const double *eta, const double *ex, int form, int deriv, int which, double *out);
 size_t pass_lds_bytes(const TileGeom &g, bool product_init, int nmat);
-size_t resident_lds_bytes(int n, int nacc, bool adjoint);
+size_t resident_lds_bytes(int n, int nacc, bool adjoint, int waves = kThreads / 64);
 hipError_t launch_resident(const ResArgs &a, int nrows, hipStream_t s);
 hipError_t launch_build(const BuildArgs &a, int nrows, hipStream_t s);
 // derived rows: the source rows' blocks copied, then the listed tasks of each
@@ -59,6 +59,11 @@ hipError_t launch_row_gather(const RowGatherArgs &a, hipStream_t s);
 // shot counts and estimates of the sampled expectation (a.nrows rows)
 hipError_t launch_sampled(const SampledArgs &a, hipStream_t s);
 hipError_t launch_shift_grad(const ShiftGradArgs &a, int nrows, hipStream_t s);
+// A merged launch of step `kind` (see BatchKind): nblocks workgroups, each with
+// its argument block of `table`; p, phi: the Pauli kernel's amplitudes per
+// thread and whether it forms phi; threads: of the resident kernel.
+hipError_t launch_batch(int kind, const void *table, const BatchBlock *blocks, int nblocks, size_t lds, int threads,
+                        int p, bool phi, const ResCall &c, hipStream_t s);
 hipError_t launch_zero_tail(float2 *state, int64_t row_stride, const int32_t *rows, int nrows, int64_t from,
                             int64_t to, hipStream_t s);
 

@@ -409,10 +409,10 @@ __device__ __forceinline__ int build_task(const BuildTask &bt, const BuildCtx &c
 
 // --------------------------------------------------- matrix build kernel
 // One thread per (row, task); the result goes to the row's matrix block.
-__global__ __launch_bounds__(256) void k_build_mats(BuildArgs a)
+template <class A>
+__device__ __forceinline__ void build_rows(const A &a, const float *theta, uint64_t noise_seed, int row, int bx)
 {
-    const int row = blockIdx.y;
-    const int ti = blockIdx.x * blockDim.x + threadIdx.x + a.task_begin;
+    const int ti = bx * blockDim.x + threadIdx.x + a.task_begin;
     // derived rows take the symbols, parameter tables and trajectory of
     // their source row, plus their parameter moves
     int src = row;
@@ -426,13 +426,13 @@ __global__ __launch_bounds__(256) void k_build_mats(BuildArgs a)
     BuildCtx c{a.members, a.gates, a.slot_sym,
                a.slot_scale + (a.uniform ? 0 : (int64_t)src * a.n_slots),
                a.slot_off + (a.uniform ? 0 : (int64_t)src * a.n_slots), a.explicit_mats,
-               a.theta + (int64_t)b * a.S, a.noise_seed, b, shift, a.x_eps};
+               theta + (int64_t)b * a.S, noise_seed, b, shift, a.x_eps};
     int odd = 0;
     if (ti < a.task_end) {
         const BuildTask bt = a.tasks[ti];
         odd = build_task(bt, c, a.mats + (int64_t)row * a.mat_stride + bt.out);
     }
-    if (a.phase_out < 0 || blockIdx.x != 0) return;
+    if (a.phase_out < 0 || bx != 0) return;
     // the row's global phase (block 0 of the row; its thread 0 built the
     // product-init matrix at phase_out), reduced in a fixed order
     __shared__ double part[4];
@@ -459,6 +459,11 @@ __global__ __launch_bounds__(256) void k_build_mats(BuildArgs a)
             out[i] = make_double2(co * v.x - s * v.y, co * v.y + s * v.x);
         }
     }
+}
+
+__global__ __launch_bounds__(256) void k_build_mats(BuildArgs a)
+{
+    build_rows(a, a.theta, a.noise_seed, blockIdx.y, blockIdx.x);
 }
 
 // Derived rows of the batched shift rules, one wavefront per row (four rows
@@ -524,9 +529,9 @@ __global__ __launch_bounds__(256) void k_build_list(BuildArgs a, int nrows)
     }
 }
 
-__global__ __launch_bounds__(64) void k_build_stage(StageBuildArgs a)
+template <class A> __device__ __forceinline__ void build_stage(const A &a, int row, int si)
 {
-    const int si = blockIdx.x, row = blockIdx.y, j = threadIdx.x;
+    const int j = threadIdx.x;
     const Stage st = cget(a.stages, cget(a.list, si));
     if (j >= (1 << st.r)) return;
     double2 *block = a.mats + (int64_t)row * a.mat_stride;
@@ -540,13 +545,12 @@ __global__ __launch_bounds__(64) void k_build_stage(StageBuildArgs a)
     default: build_stage_r<1>(st, a.ops, block, out, j); break;
     }
 }
-
+__global__ __launch_bounds__(64) void k_build_stage(StageBuildArgs a) { build_stage(a, blockIdx.y, blockIdx.x); }
 
 // ------------------------------------------------------- forward pass
-__global__ __launch_bounds__(256) void k_pass(PassArgs a)
+template <class A> __device__ __forceinline__ void run_pass(const A &a, float2 *state, int bid, unsigned char *smem)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const PassCtx c = pass_setup(a, smem);
+    const PassCtx c = pass_setup(a, state, bid, smem);
     const SMat G = smat(a.mats + (int64_t)c.row * a.mat_stride);
     const int64_t ntiles = (int64_t)1 << a.tiles_log2;
     for (int64_t tile = c.w; tile < ntiles; tile += a.wg_per_row) {
@@ -561,6 +565,11 @@ __global__ __launch_bounds__(256) void k_pass(PassArgs a)
         pass_store(a, c, fb);
         __syncthreads();
     }
+}
+__global__ __launch_bounds__(256) void k_pass(PassArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    run_pass(a, a.state, blockIdx.x, smem);
 }
 
 // ------------------------------------------------ Pauli sums on tiles
@@ -583,11 +592,12 @@ __device__ __forceinline__ int xcd_block(int bid, int nb)
 // Re(conj(psi_l) d(l) psi_{l ^ x}) to the group's observable and
 // g_k d(l) psi_{l ^ x} to phi_l.  Accumulation is in fp64; each workgroup
 // reduces its expectation partials in a fixed order.
-template <int P, bool kPhi>
-__global__ __launch_bounds__(256) void k_pauli(PauliArgs a)
+// bid, nb: the workgroup's number and the workgroups of the launch (or of its
+// argument block); upstream: the call's gradients
+template <int P, bool kPhi, class A>
+__device__ __forceinline__ void run_pauli(const A &a, const float *upstream, int bid0, int nb, unsigned char *smem)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const TileGeom &g = a.g;
+    const auto &g = a.g;
     const int T = 1 << g.t;
     float2 *la = reinterpret_cast<float2 *>(smem);
     uint64_t *hi_off = reinterpret_cast<uint64_t *>(la + T);
@@ -595,13 +605,13 @@ __global__ __launch_bounds__(256) void k_pauli(PauliArgs a)
     double *esum = red + 4 * kPauliChunk;                           // [k_count]
     float2 *lb = reinterpret_cast<float2 *>(esum + a.k_count);      // partner tile (when any xF != 0)
 
-    const int bid = xcd_block(blockIdx.x, gridDim.x);
+    const int bid = xcd_block(bid0, nb);
     const int row = bid / a.wg_per_row, w = bid % a.wg_per_row;
     const int b = cget(a.rows, row);
-    const float2 *ps = a.psi + (int64_t)b * a.row_stride;
+    const float2 *ps = as_global(a.psi) + (int64_t)b * a.row_stride;
     const PChunk *chunks = a.chunks + cget(a.row_chunk_begin, row);
     const int nchunks = cget(a.row_chunk_count, row);
-    const float *up = kPhi ? a.upstream + (int64_t)a.brows[row] * a.K : nullptr;
+    const float *up = kPhi ? upstream + (int64_t)a.brows[row] * a.K : nullptr;
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
     const bool active = tid < T;
     const int kend = a.k_begin + a.k_count;
@@ -704,7 +714,7 @@ __global__ __launch_bounds__(256) void k_pauli(PauliArgs a)
             __syncthreads();
         }
         if (kPhi && active) {
-            float2 *ph = a.phi + (int64_t)b * a.row_stride;
+            float2 *ph = as_global(a.phi) + (int64_t)b * a.row_stride;
 #pragma unroll
             for (int r = 0; r < P; r++) {
                 const uint64_t i = tile_index(tc, fb, tid + 256 * r);
@@ -718,13 +728,17 @@ __global__ __launch_bounds__(256) void k_pauli(PauliArgs a)
     double *out = a.partial + ((int64_t)row * a.wg_per_row + w) * a.k_count;
     for (int j = tid; j < a.k_count; j += blockDim.x) out[j] = esum[j];
 }
+template <int P, bool kPhi> __global__ __launch_bounds__(256) void k_pauli(PauliArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    run_pauli<P, kPhi>(a, a.upstream, blockIdx.x, gridDim.x, smem);
+}
 
 // out[b, k] = sum over the row's workgroups of their partials: one block per
 // (row, observable), strided sums then a tree, all in a fixed order.
-__global__ __launch_bounds__(256) void k_pauli_reduce(PauliReduceArgs a)
+template <class A> __device__ __forceinline__ void pauli_reduce(const A &a, float *dst, int row, int j)
 {
     __shared__ double red[256];
-    const int row = blockIdx.x, j = blockIdx.y;
     const double *p = a.partial + (int64_t)row * a.wg_per_row * a.k_count + j;
     double s = 0;
     for (int w = threadIdx.x; w < a.wg_per_row; w += blockDim.x) s += p[(int64_t)w * a.k_count];
@@ -734,7 +748,11 @@ __global__ __launch_bounds__(256) void k_pauli_reduce(PauliReduceArgs a)
         if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
         __syncthreads();
     }
-    if (threadIdx.x == 0) a.out[(int64_t)a.rows[row] * a.K + a.k_begin + j] = (float)red[0];
+    if (threadIdx.x == 0) dst[(int64_t)a.rows[row] * a.K + a.k_begin + j] = (float)red[0];
+}
+__global__ __launch_bounds__(256) void k_pauli_reduce(PauliReduceArgs a)
+{
+    pauli_reduce(a, a.out, blockIdx.x, blockIdx.y);
 }
 
 // ------------------------------------------ diagonal Pauli sums in HBM
@@ -854,10 +872,9 @@ __global__ __launch_bounds__(256) void k_pauli_diag(DiagArgs a)
 
 // ------------------------------------------------------ reverse pass
 // psi and phi tiles side by side in LDS; the pass's matrices too.
-__global__ __launch_bounds__(256, 2) void k_rev_pass(RevArgs a)
+template <class A> __device__ __forceinline__ void run_rev_pass(const A &a, int bid, unsigned char *smem)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const RevCtx c = rev_setup(a, smem);
+    const RevCtx c = rev_setup(a, bid, smem);
     const int64_t ntiles = (int64_t)1 << a.tiles_log2;
     for (int64_t tile = c.w; tile < ntiles; tile += a.wg_per_row) {
         const uint64_t fb = pdep64((uint64_t)tile, a.g.fixed_mask);
@@ -874,11 +891,15 @@ __global__ __launch_bounds__(256, 2) void k_rev_pass(RevArgs a)
     }
     rev_finish(a, c);
 }
+__global__ __launch_bounds__(256, 2) void k_rev_pass(RevArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    run_rev_pass(a, blockIdx.x, smem);
+}
 
 // grad[b, s] = sum over gradient slots of s: 2 * scale * sum_w gpart
-__global__ void k_grad_reduce(GradReduceArgs a)
+template <class A> __device__ __forceinline__ void grad_reduce(const A &a, float *grad, int row)
 {
-    const int row = blockIdx.x;
     const int b = cget(a.rows, row);
     const double *scale = a.slot_scale + (a.uniform ? 0 : (int64_t)row * a.n_slots);
     const double *p = a.gpart + (int64_t)row * a.wg_per_row * a.n_gslots;
@@ -890,9 +911,10 @@ __global__ void k_grad_reduce(GradReduceArgs a)
             for (int w = 0; w < a.wg_per_row; w++) v += p[(int64_t)w * a.n_gslots + gs];
             sum += 2.0 * scale[a.gslot_slot[gs]] * v;
         }
-        a.grad[(int64_t)b * a.S + s] = (float)sum;
+        grad[(int64_t)b * a.S + s] = (float)sum;
     }
 }
+__global__ void k_grad_reduce(GradReduceArgs a) { grad_reduce(a, a.grad, blockIdx.x); }
 
 // ---------------------------------------------------- resident circuits
 // Small circuits (psi, phi and every matrix of the row fit in LDS): one
@@ -900,29 +922,102 @@ __global__ void k_grad_reduce(GradReduceArgs a)
 // gates, expectations, H_g, reverse sweep, gradient reduction -- in one
 // launch, on the matrices k_build_mats wrote.  At most 128 registers per
 // thread, so that four rows share a CU.  Outputs are reduced in a fixed order.
-__global__ __launch_bounds__(256, 4) void k_resident(ResArgs a)
+template <class A, class C>
+__device__ __forceinline__ void run_resident(const A &a, const C &c, int row, unsigned char *smem)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t T = 1u << a.n;
-    double *acc = reinterpret_cast<double *>(smem);              // [4][nacc]
-    float2 *lp = reinterpret_cast<float2 *>(acc + 4 * a.nacc);   // [T]
-    float2 *lf = lp + T;                                         // [T] (adjoint)
-    const SMat M = smat(a.mats + (int64_t)blockIdx.x * a.mat_stride);
     const int tid = threadIdx.x, nt = blockDim.x;
+    double *acc = reinterpret_cast<double *>(smem);                    // [waves][nacc]
+    float2 *lp = reinterpret_cast<float2 *>(acc + (nt / 64) * a.nacc);  // [T]
+    float2 *lf = lp + T;                                               // [T] (adjoint)
+    const SMat M = smat(a.mats + (int64_t)row * a.mat_stride);
     resident_begin(a, M, acc, lp, tid, nt);
     for (int si = 0; si < a.nfstages; si++) {
         const Stage st = cget(a.fstages, si);
         run_stage_any(st, a.fops, M, 0, M, lp, a.n, 0, tid, nt);
         __syncthreads();
     }
-    resident_middle(a, acc, lp, lf, blockIdx.x, tid, nt);
-    if (a.grad)
+    resident_middle(a, c, acc, lp, lf, row, tid, nt);
+    if (c.grad)
         for (int si = 0; si < a.nrstages; si++) {
             const Stage st = cget(a.rstages, si);
             run_rev_stage_any<kStageBitsRevResident>(st, a.rops, M, 0, lp, lf, a.n, 0, acc, a.nacc, -a.gacc, tid, nt);
             __syncthreads();
         }
-    resident_end(a, acc, blockIdx.x, tid, nt);
+    resident_end(a, c, acc, row, tid, nt);
+}
+__global__ __launch_bounds__(256, 4) void k_resident(ResArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    run_resident(a, a, blockIdx.x, smem);
+}
+
+// ------------------------------------------------- merged launches
+// A batch of many circuit structures (the paper's ops take any batch of
+// circuits) would launch every step once per structure, each launch a row or
+// two wide.  The same step of all structures is one launch instead: the
+// workgroup takes its structure's argument block from a table that is read
+// through the scalar cache, and the call's own pointers from `c`.  45
+// structures of 2..13 qubits, adjoint: 5.7 ms as 140 launches, 0.41 ms as 11
+// (the resident circuits 149 us, bound by the largest one's chain of stages).
+template <class T> using TableArg = const __attribute__((address_space(4))) T;
+template <class T> __device__ __forceinline__ TableArg<T> &table_arg(const void *table, int i)
+{
+    return reinterpret_cast<TableArg<T> *>(reinterpret_cast<uintptr_t>(table))[i];
+}
+
+__global__ __launch_bounds__(256) void k_build_batch(const void *table, const BatchBlock *blocks, ResCall c)
+{
+    const BatchBlock bb = cget(blocks, blockIdx.x);
+    TableArg<BuildArgs> &a = table_arg<BuildArgs>(table, bb.arg);
+    const int nx = (a.task_end - a.task_begin + 255) / 256;
+    build_rows(a, c.theta, c.noise_seed, bb.block / nx, bb.block % nx);
+}
+__global__ __launch_bounds__(64) void k_stage_batch(const void *table, const BatchBlock *blocks, ResCall)
+{
+    const BatchBlock bb = cget(blocks, blockIdx.x);
+    TableArg<StageBuildArgs> &a = table_arg<StageBuildArgs>(table, bb.arg);
+    build_stage(a, bb.block / a.nlist, bb.block % a.nlist);
+}
+template <int NT>
+__global__ __launch_bounds__(NT, 4) void k_resident_batch(const void *table, const BatchBlock *blocks, ResCall c)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const BatchBlock bb = cget(blocks, blockIdx.x);
+    run_resident(table_arg<ResArgs>(table, bb.arg), c, bb.block, smem);
+}
+__global__ __launch_bounds__(256) void k_pass_batch(const void *table, const BatchBlock *blocks, ResCall c)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const BatchBlock bb = cget(blocks, blockIdx.x);
+    TableArg<PassArgs> &a = table_arg<PassArgs>(table, bb.arg);
+    run_pass(a, c.state_out ? c.state_out : a.state, bb.block, smem);
+}
+template <int P, bool kPhi>
+__global__ __launch_bounds__(256) void k_pauli_batch(const void *table, const BatchBlock *blocks, ResCall c)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const BatchBlock bb = cget(blocks, blockIdx.x);
+    // (1: the workgroup keeps its number; a structure's tiles share an XCD's
+    // L2 only by chance, its few rows fit any)
+    run_pauli<P, kPhi>(table_arg<PauliArgs>(table, bb.arg), c.upstream, bb.block, 1, smem);
+}
+__global__ __launch_bounds__(256) void k_pauli_reduce_batch(const void *table, const BatchBlock *blocks, ResCall c)
+{
+    const BatchBlock bb = cget(blocks, blockIdx.x);
+    TableArg<PauliReduceArgs> &a = table_arg<PauliReduceArgs>(table, bb.arg);
+    pauli_reduce(a, c.exp_out, bb.block / a.k_count, bb.block % a.k_count);
+}
+__global__ __launch_bounds__(256, 2) void k_rev_batch(const void *table, const BatchBlock *blocks, ResCall)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const BatchBlock bb = cget(blocks, blockIdx.x);
+    run_rev_pass(table_arg<RevArgs>(table, bb.arg), bb.block, smem);
+}
+__global__ void k_grad_reduce_batch(const void *table, const BatchBlock *blocks, ResCall c)
+{
+    const BatchBlock bb = cget(blocks, blockIdx.x);
+    grad_reduce(table_arg<GradReduceArgs>(table, bb.arg), c.grad, bb.block);
 }
 
 // ------------------------------------------------------------- sampling
@@ -1199,6 +1294,17 @@ __global__ void k_shift_grad(ShiftGradArgs a)
     a.grad[b * a.S + s] = (float)sum;
 }
 
+__global__ __launch_bounds__(256) void k_zero_batch(const void *table, const BatchBlock *blocks, ResCall c)
+{
+    const BatchBlock bb = cget(blocks, blockIdx.x);
+    TableArg<ZeroArgs> &a = table_arg<ZeroArgs>(table, bb.arg);
+    const int nx = (int)((a.to - a.from + kZeroBlock - 1) / kZeroBlock);
+    float2 *st = c.state_out + (int64_t)cget(a.rows, bb.block / nx) * a.row_stride;
+    const int64_t from = a.from + (int64_t)(bb.block % nx) * kZeroBlock;
+    const int64_t to = from + kZeroBlock < a.to ? from + kZeroBlock : a.to;
+    for (int64_t i = from + threadIdx.x; i < to; i += 256) st[i] = make_float2(0.f, 0.f);
+}
+
 __global__ void k_zero_tail(float2 *state, int64_t row_stride, const int32_t *rows, int64_t from, int64_t to)
 {
     const int row = blockIdx.y;
@@ -1423,9 +1529,9 @@ hipError_t launch_rev_pass(const RevArgs &a, int nrows, hipStream_t s)
     return hipGetLastError();
 }
 
-size_t resident_lds_bytes(int n, int nacc, bool adjoint)
+size_t resident_lds_bytes(int n, int nacc, bool adjoint, int waves)
 {
-    return sizeof(double) * 4 * (size_t)nacc + sizeof(float2) * ((size_t)1 << n) * (adjoint ? 2 : 1);
+    return sizeof(double) * waves * (size_t)nacc + sizeof(float2) * ((size_t)1 << n) * (adjoint ? 2 : 1);
 }
 
 hipError_t launch_resident(const ResArgs &a, int nrows, hipStream_t s)
@@ -1437,6 +1543,55 @@ hipError_t launch_resident(const ResArgs &a, int nrows, hipStream_t s)
     prof::Scope ps("resident", s);
     hipLaunchKernelGGL(k_resident, dim3(nrows), dim3(kThreads), lds, s, a);
     return hipGetLastError();
+}
+
+template <class K>
+hipError_t launch_batch_k(K kernel, const char *name, int threads, const void *table, const BatchBlock *blocks,
+                          int nblocks, size_t lds, const ResCall &c, hipStream_t s)
+{
+    hipError_t e = set_lds(kernel, lds);
+    if (e != hipSuccess) return e;
+    prof::Scope ps(name, s);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)nblocks), dim3(threads), lds, s, table, blocks, c);
+    return hipGetLastError();
+}
+
+template <int P>
+hipError_t launch_pauli_batch(bool phi, const void *table, const BatchBlock *blocks, int nblocks, size_t lds,
+                              const ResCall &c, hipStream_t s)
+{
+    return phi ? launch_batch_k(k_pauli_batch<P, true>, "pauli", 256, table, blocks, nblocks, lds, c, s)
+               : launch_batch_k(k_pauli_batch<P, false>, "pauli", 256, table, blocks, nblocks, lds, c, s);
+}
+
+hipError_t launch_batch(int kind, const void *table, const BatchBlock *blocks, int nblocks, size_t lds, int threads,
+                        int p, bool phi, const ResCall &c, hipStream_t s)
+{
+    if (nblocks <= 0) return hipSuccess;
+    switch (kind) {
+    case BK_BUILD: return launch_batch_k(k_build_batch, "build", 256, table, blocks, nblocks, lds, c, s);
+    case BK_STAGE: return launch_batch_k(k_stage_batch, "build", 64, table, blocks, nblocks, lds, c, s);
+    case BK_RESIDENT:
+        if (threads == 1024)
+            return launch_batch_k(k_resident_batch<1024>, "resident", 1024, table, blocks, nblocks, lds, c, s);
+        return launch_batch_k(k_resident_batch<256>, "resident", 256, table, blocks, nblocks, lds, c, s);
+    case BK_PASS: return launch_batch_k(k_pass_batch, "pass", 256, table, blocks, nblocks, lds, c, s);
+    case BK_PAULI:
+        switch (p) {
+        case 1: return launch_pauli_batch<1>(phi, table, blocks, nblocks, lds, c, s);
+        case 2: return launch_pauli_batch<2>(phi, table, blocks, nblocks, lds, c, s);
+        case 4: return launch_pauli_batch<4>(phi, table, blocks, nblocks, lds, c, s);
+        case 8: return launch_pauli_batch<8>(phi, table, blocks, nblocks, lds, c, s);
+        case 16: return launch_pauli_batch<16>(phi, table, blocks, nblocks, lds, c, s);
+        default: return hipErrorInvalidValue;
+        }
+    case BK_PAULI_REDUCE:
+        return launch_batch_k(k_pauli_reduce_batch, "pauli_reduce", 256, table, blocks, nblocks, lds, c, s);
+    case BK_REV: return launch_batch_k(k_rev_batch, "rev_pass", 256, table, blocks, nblocks, lds, c, s);
+    case BK_GRAD_REDUCE: return launch_batch_k(k_grad_reduce_batch, "grad_reduce", 256, table, blocks, nblocks, lds, c, s);
+    case BK_ZERO: return launch_batch_k(k_zero_batch, "zero", 256, table, blocks, nblocks, lds, c, s);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_grad_reduce(const GradReduceArgs &a, int nrows, hipStream_t s)

@@ -12,6 +12,7 @@
 #include <cstring>
 #include <memory>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "../../include/tq.h"
@@ -156,6 +157,76 @@ struct GroupDev {
     }
 };
 
+// Merged launches over the structure groups of a program (table-driven
+// kernels): every step of every group, recorded once by running the groups'
+// own launch code with a recorder in place of the stream, then launched per
+// step for all groups together.  The argument tables hold pointers to the
+// program's plan, tables and fixed workspaces; a call adds its own (ResCall).
+struct BatchPlan {
+    struct Launch {
+        int kind, nblocks, threads, p;
+        bool phi;
+        size_t lds, table, blocks;  // offsets in `buf`
+    };
+    bool ready = false;
+    std::vector<char> covered;  // groups the launches cover
+    std::vector<Launch> launches;
+    DevBuf buf, partial, gpart;
+    void release()
+    {
+        for (DevBuf *b : {&buf, &partial, &gpart}) b->release();
+    }
+};
+
+struct BatchRec {
+    // step order within a group: kind phases, then the pass (or observable
+    // chunk) index, then the kind again (reduce after its sweep)
+    struct Key {
+        int phase, index, kind, p;
+        bool phi;
+        bool operator<(const Key &o) const
+        {
+            return std::tie(phase, index, kind, p, phi) < std::tie(o.phase, o.index, o.kind, o.p, o.phi);
+        }
+    };
+    struct Bucket {
+        std::vector<char> table;
+        std::vector<std::pair<int, int64_t>> args;  // workgroups and weight (heaviest first) of each block
+        size_t lds = 0;
+    };
+    std::map<Key, Bucket> buckets;
+    size_t partial = 0, gpart = 0;  // bytes
+
+    template <class Args> void add(int phase, int index, int kind, const Args &a, int nblocks, size_t lds, int64_t weight,
+                                   int p = 0, bool phi = false)
+    {
+        if (nblocks <= 0) return;
+        Bucket &b = buckets[Key{phase, index, kind, p, phi}];
+        const char *c = reinterpret_cast<const char *>(&a);
+        b.table.insert(b.table.end(), c, c + sizeof a);
+        b.args.emplace_back(nblocks, weight);
+        b.lds = std::max(b.lds, lds);
+    }
+    // a region of a workspace, as its byte offset (the base is added once
+    // the workspace's size is known)
+    static double *region(size_t &total, size_t bytes)
+    {
+        double *at = reinterpret_cast<double *>(total);
+        total += (bytes + 255) & ~(size_t)255;
+        return at;
+    }
+};
+
+// The merged launches of one observable set.
+struct ObsBatch {
+    BatchPlan exp, adj;
+    void release()
+    {
+        exp.release();
+        adj.release();
+    }
+};
+
 } // namespace
 
 struct tq_observables_s {
@@ -188,10 +259,22 @@ struct tq_program_s {
     size_t psi_total = 0, mat_total = 0;
     uint64_t obs_id = 0;
     std::vector<std::unique_ptr<ObsGroupDev>> obs_dev;
+    std::unique_ptr<ObsBatch> obs_batch;
+    BatchPlan state_batch;
     // tables of the observable sets used before the current one (most
     // recent last), kept so that calls alternating between a few sets do
     // not rebuild them
-    std::vector<std::pair<uint64_t, std::vector<std::unique_ptr<ObsGroupDev>>>> obs_kept;
+    struct Kept {
+        uint64_t id;
+        std::vector<std::unique_ptr<ObsGroupDev>> groups;
+        std::unique_ptr<ObsBatch> batch;
+        void release()
+        {
+            for (auto &o : groups) o->release();
+            if (batch) batch->release();
+        }
+    };
+    std::vector<Kept> obs_kept;
     uint64_t noise_seed = 0;  // seed of the channels' per-row draws
 
     ~tq_program_s()
@@ -204,8 +287,9 @@ struct tq_program_s {
                 b->release();
         }
         for (auto &o : obs_dev) o->release();
-        for (auto &k : obs_kept)
-            for (auto &o : k.second) o->release();
+        if (obs_batch) obs_batch->release();
+        state_batch.release();
+        for (auto &k : obs_kept) k.release();
         for (DevBuf *b : {&psi, &phi, &mats, &partial, &gpart, &levels, &xpsi, &xmats, &xout, &xident, &xterm,
                           &xcounts})
             b->release();
@@ -330,6 +414,7 @@ struct RunRows {
     // observable tables of each launch row (NULL: the group's own, by group row)
     const int32_t *term_begin = nullptr, *term_count = nullptr, *cbegin = nullptr, *ccount = nullptr,
                   *dcbegin = nullptr, *dccount = nullptr;
+    BatchRec *rec = nullptr;             // record the launches instead of making them
 };
 
 RunRows own_rows(tq_program p, size_t gi)
@@ -392,6 +477,9 @@ void build_mats(tq_program p, size_t gi, const float *theta, int begin, int end,
         if (begin != g.fwd_tasks.begin || end != g.fwd_tasks.end)
             fail(TQ_E_INVALID, "derived rows build the forward matrices only");
         hip_check(launch_build_derived(a, rr.n, rr.max_list, s), "derived matrix build launch");
+    } else if (rr.rec) {
+        const int nx = (end - begin + kThreads - 1) / kThreads;
+        rr.rec->add(0, 0, BK_BUILD, a, rr.n * nx, 0, 0);
     } else {
         hip_check(launch_build(a, rr.n, s), "matrix build launch");
     }
@@ -404,7 +492,8 @@ void build_mats(tq_program p, size_t gi, const float *theta, int begin, int end,
         sb.ops = (const PassOp *)gd.fwd_ops.p;
         sb.mats = a.mats;
         sb.mat_stride = a.mat_stride;
-        hip_check(launch_build_stage(sb, rr.n, s), "stage matrix build launch");
+        if (rr.rec) rr.rec->add(1, 0, BK_STAGE, sb, rr.n * sb.nlist, 0, 0);
+        else hip_check(launch_build_stage(sb, rr.n, s), "stage matrix build launch");
     }
 }
 
@@ -441,7 +530,10 @@ void forward(tq_program p, size_t gi, float2 *state, int64_t row_stride, const i
             hip_check(e, "specialised pass launch");
             continue;
         }
-        hip_check(launch_pass(a, nrows, s), "pass launch");
+        if (rr.rec)
+            rr.rec->add(3, (int)pi, BK_PASS, a, nrows * a.wg_per_row,
+                        pass_lds_bytes(a.g, a.product_init != 0, a.mat_end - a.mat_begin), a.nstages);
+        else hip_check(launch_pass(a, nrows, s), "pass launch");
     }
 }
 
@@ -467,11 +559,12 @@ void ensure_obs(tq_program p, const ObsData &od)
 {
     if (p->obs_id == od.id) return;
     for (size_t i = 0; i < p->obs_kept.size(); i++)
-        if (p->obs_kept[i].first == od.id) {
-            auto tables = std::move(p->obs_kept[i].second);
+        if (p->obs_kept[i].id == od.id) {
+            auto kept = std::move(p->obs_kept[i]);
             p->obs_kept.erase(p->obs_kept.begin() + i);
-            if (p->obs_id) p->obs_kept.emplace_back(p->obs_id, std::move(p->obs_dev));
-            p->obs_dev = std::move(tables);
+            if (p->obs_id) p->obs_kept.push_back({p->obs_id, std::move(p->obs_dev), std::move(p->obs_batch)});
+            p->obs_dev = std::move(kept.groups);
+            p->obs_batch = std::move(kept.batch);
             p->obs_id = od.id;
             return;
         }
@@ -616,13 +709,14 @@ void ensure_obs(tq_program p, const ObsData &od)
         out.push_back(std::move(og));
     }
     if (p->obs_id) {
-        p->obs_kept.emplace_back(p->obs_id, std::move(p->obs_dev));
+        p->obs_kept.push_back({p->obs_id, std::move(p->obs_dev), std::move(p->obs_batch)});
         if (p->obs_kept.size() > kObsKept) {
-            for (auto &old : p->obs_kept.front().second) old->release();
+            p->obs_kept.front().release();
             p->obs_kept.erase(p->obs_kept.begin());
         }
     }
     p->obs_dev = std::move(out);
+    p->obs_batch = std::make_unique<ObsBatch>();
     p->obs_id = od.id;
 }
 
@@ -819,8 +913,12 @@ void pauli_group(tq_program p, size_t gi, const float2 *psi, float2 *phi, const 
         a.k_begin = k0;
         a.k_count = std::min(kmax, K - k0);
         a.phi_accumulate = k0 > 0;
-        a.partial = (double *)p->partial.ensure(sizeof(double) * (size_t)slots * a.k_count);
-        hip_check(launch_pauli(a, nrows, og.partner, s), "Pauli kernel launch");
+        const size_t bytes = sizeof(double) * (size_t)slots * a.k_count;
+        a.partial = rr.rec ? BatchRec::region(rr.rec->partial, bytes) : (double *)p->partial.ensure(bytes);
+        if (rr.rec)
+            rr.rec->add(4, k0, BK_PAULI, a, (int)slots, pauli_lds_bytes(a.g, a.k_count, og.partner), 0,
+                        a.g.t <= 8 ? 1 : 1 << (a.g.t - 8), a.phi != nullptr);
+        else hip_check(launch_pauli(a, nrows, og.partner, s), "Pauli kernel launch");
         if (out) {
             PauliReduceArgs r{};
             r.rows = a.brows;
@@ -830,7 +928,8 @@ void pauli_group(tq_program p, size_t gi, const float2 *psi, float2 *phi, const 
             r.k_begin = k0;
             r.k_count = a.k_count;
             r.out = out;
-            hip_check(launch_pauli_reduce(r, nrows, s), "Pauli reduce launch");
+            if (rr.rec) rr.rec->add(4, k0, BK_PAULI_REDUCE, r, nrows * r.k_count, 0, 0);
+            else hip_check(launch_pauli_reduce(r, nrows, s), "Pauli reduce launch");
         }
     }
 }
@@ -843,6 +942,9 @@ constexpr size_t kResidentLds = 150 * 1024;
 // the specialised resident kernel is launched with at most the default
 // dynamic LDS window
 constexpr size_t kResidentSpecLds = 64 * 1024;
+// merged resident launches of at most this many rows (two per CU) take
+// sixteen wavefronts per row instead of four
+constexpr int64_t kBatchWide = 512;
 
 bool resident(tq_program p, size_t gi, bool adjoint, int tmax)
 {
@@ -861,9 +963,13 @@ bool resident(tq_program p, size_t gi, bool adjoint, int tmax)
 // Launch the resident kernel of group gi: the one specialised for the
 // group's structure when the program asks for it and its LDS fits the
 // default window, else the precompiled one.
-void run_resident(tq_program p, size_t gi, const ResArgs &a, int nrows, hipStream_t s)
+void run_resident(tq_program p, size_t gi, const ResArgs &a, int nrows, hipStream_t s, const RunRows &rr)
 {
     const Group &g = *p->pd->groups[gi];
+    if (rr.rec) {  // (LDS: set from the table when the thread count is known)
+        rr.rec->add(2, 0, BK_RESIDENT, a, nrows, 0, ((int64_t)1 << g.n) * (a.nfstages + 2 * a.nrstages));
+        return;
+    }
     const size_t lds = resident_lds_bytes(a.n, a.nacc, a.grad != nullptr);
     if (p->pd->opt.specialize && lds <= kResidentSpecLds) {
         std::string log;
@@ -924,7 +1030,7 @@ void forward_to_ws(tq_program p, size_t gi, const float *theta, float2 *psi, hip
         a.state_out = psi;
         a.out_stride = (int64_t)1 << g.n;
         a.out_rows = rr.ident;
-        run_resident(p, gi, a, rr.n, s);
+        run_resident(p, gi, a, rr.n, s, rr);
         return;
     }
     build_mats(p, gi, theta, g.fwd_tasks.begin, g.fwd_tasks.end, s, rr);
@@ -1055,26 +1161,194 @@ SampledArgs sampled_args(tq_observables o, int reps, uint64_t seed)
     return a;
 }
 
+// The launches of one group's rows of tq_expectation, tq_simulate_state and
+// tq_adjoint_grad (K > 0 there, and S > 0 for the gradient).
+void expectation_group(tq_program prog, size_t gi, const float *theta, int K, float *out, hipStream_t s, const RunRows &rr)
+{
+    const Group &g = *prog->pd->groups[gi];
+    float2 *psi = psi_ws(prog) + prog->gdev[gi]->psi_off;
+    if (resident(prog, gi, false, prog->obs_dev[gi]->tmax)) {
+        ResArgs a = resident_args(prog, gi, theta, false, s, rr);
+        resident_terms(prog, gi, a, K, out, rr);
+        run_resident(prog, gi, a, rr.n, s, rr);
+        return;
+    }
+    build_mats(prog, gi, theta, g.fwd_tasks.begin, g.fwd_tasks.end, s, rr);
+    forward(prog, gi, psi, (int64_t)1 << g.n, rr.ident, s, rr);
+    pauli_group(prog, gi, psi, nullptr, nullptr, K, out, s, rr);
+}
+
+void state_group(tq_program prog, size_t gi, const float *theta, float2 *states, hipStream_t s, const RunRows &rr)
+{
+    const ProgramData &pd = *prog->pd;
+    const Group &g = *pd.groups[gi];
+    GroupDev &gd = *prog->gdev[gi];
+    const int64_t stride = (int64_t)1 << pd.nmax;
+    if (resident(prog, gi, false, 0)) {
+        ResArgs a = resident_args(prog, gi, theta, false, s, rr);
+        a.state_out = states;
+        a.out_stride = stride;
+        a.out_rows = (const int32_t *)gd.rows.p;
+        run_resident(prog, gi, a, rr.n, s, rr);
+    } else {
+        build_mats(prog, gi, theta, g.fwd_tasks.begin, g.fwd_tasks.end, s, rr);
+        forward(prog, gi, states, stride, (const int32_t *)gd.rows.p, s, rr);
+    }
+    if (g.n >= pd.nmax) return;
+    const int64_t from = (int64_t)1 << g.n;
+    if (rr.rec) {
+        const ZeroArgs z{stride, (const int32_t *)gd.rows.p, from, stride};
+        rr.rec->add(8, 0, BK_ZERO, z, rr.n * (int)((stride - from + kZeroBlock - 1) / kZeroBlock), 0, 0);
+    } else {
+        hip_check(launch_zero_tail(states, stride, (const int32_t *)gd.rows.p, rr.n, from, stride, s), "zero tail launch");
+    }
+}
+
+// (declared here, defined with the reverse sweep below)
+void adjoint_group(tq_program prog, size_t gi, const float *theta, int K, const float *upstream, float *grad,
+                   float *expectations, hipStream_t s, const RunRows &rr);
+
+enum BatchMode { BM_STATE, BM_EXP, BM_ADJ };
+
+// Whether group gi joins the merged launches of a mode: everything but the
+// Z-only expectation kernel of larger states (diag_group).
+bool batch_covers(tq_program p, size_t gi, int mode)
+{
+    if (mode == BM_STATE) return true;
+    const ObsGroupDev &og = *p->obs_dev[gi];
+    return resident(p, gi, mode == BM_ADJ, og.tmax) || mode == BM_ADJ || !og.diag;
+}
+
+// Record the merged launches of a mode on first use.
+void ensure_batch(tq_program p, BatchPlan &bp, int mode, int K)
+{
+    if (bp.ready) return;
+    const size_t G = p->pd->groups.size();
+    BatchRec rec;
+    std::vector<char> covered(G, 0);
+    // (placeholders for the pointers that each call brings; never read)
+    float *some = reinterpret_cast<float *>(sizeof(float4));
+    for (size_t gi = 0; gi < G; gi++) {
+        if (!batch_covers(p, gi, mode)) continue;
+        covered[gi] = 1;
+        RunRows rr = own_rows(p, gi);
+        rr.rec = &rec;
+        if (mode == BM_STATE) state_group(p, gi, some, (float2 *)some, nullptr, rr);
+        if (mode == BM_EXP) expectation_group(p, gi, some, K, some, nullptr, rr);
+        if (mode == BM_ADJ) adjoint_group(p, gi, some, K, some, some, some, nullptr, rr);
+    }
+    bp.release();
+    bp.launches.clear();
+    char *partial = rec.partial ? (char *)bp.partial.ensure(rec.partial) : nullptr;
+    char *gpart = rec.gpart ? (char *)bp.gpart.ensure(rec.gpart) : nullptr;
+    std::vector<char> host;
+    auto align = [&] { host.resize((host.size() + 63) & ~(size_t)63); };
+    for (auto &kv : rec.buckets) {
+        BatchRec::Bucket &b = kv.second;
+        const size_t n = b.args.size(), size = b.table.size() / n;
+        BatchPlan::Launch l{};
+        l.kind = kv.first.kind;
+        l.p = kv.first.p;
+        l.phi = kv.first.phi;
+        l.threads = kThreads;
+        l.lds = b.lds;
+        int64_t blocks = 0;
+        for (auto &ar : b.args) blocks += ar.first;
+        if (blocks > ((int64_t)1 << 30)) fail(TQ_E_UNSUPPORTED, "too many workgroups in one launch");
+        auto base = [](double *&at, char *b0) { at = reinterpret_cast<double *>(b0 + reinterpret_cast<size_t>(at)); };
+        for (size_t i = 0; i < n; i++) {
+            char *at = b.table.data() + i * size;
+            if (l.kind == BK_PAULI) base(reinterpret_cast<PauliArgs *>(at)->partial, partial);
+            if (l.kind == BK_REV) base(reinterpret_cast<RevArgs *>(at)->gpart, gpart);
+            if (l.kind == BK_PAULI_REDUCE) {
+                PauliReduceArgs *r = reinterpret_cast<PauliReduceArgs *>(at);
+                r->partial = reinterpret_cast<double *>(partial + reinterpret_cast<size_t>(r->partial));
+            }
+            if (l.kind == BK_GRAD_REDUCE) {
+                GradReduceArgs *r = reinterpret_cast<GradReduceArgs *>(at);
+                r->gpart = reinterpret_cast<double *>(gpart + reinterpret_cast<size_t>(r->gpart));
+            }
+        }
+        if (l.kind == BK_RESIDENT) {
+            // few rows: sixteen wavefronts each, since the launch lasts as
+            // long as its largest circuit (45 structures of up to 13 qubits,
+            // adjoint: 0.41 ms, 0.54 ms with four); many rows: four, so that
+            // more share a CU
+            for (int threads : {1024, kThreads}) {
+                size_t lds = 0;
+                for (size_t i = 0; i < n; i++) {
+                    const ResArgs &a = *reinterpret_cast<const ResArgs *>(b.table.data() + i * size);
+                    lds = std::max(lds, resident_lds_bytes(a.n, a.nacc, mode == BM_ADJ, threads / 64));
+                }
+                l.threads = threads;
+                l.lds = lds;
+                if (threads == kThreads || (blocks <= kBatchWide && lds <= kResidentLds)) break;
+            }
+        }
+        // heaviest blocks first: they start with the launch
+        std::vector<int> order(n);
+        for (size_t i = 0; i < n; i++) order[i] = (int)i;
+        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return b.args[x].second > b.args[y].second; });
+        std::vector<BatchBlock> bl;
+        bl.reserve((size_t)blocks);
+        for (int i : order)
+            for (int k = 0; k < b.args[i].first; k++) bl.push_back(BatchBlock{i, k});
+        l.nblocks = (int)bl.size();
+        align();
+        l.table = host.size();
+        host.insert(host.end(), b.table.begin(), b.table.end());
+        align();
+        l.blocks = host.size();
+        const char *bc = reinterpret_cast<const char *>(bl.data());
+        host.insert(host.end(), bc, bc + bl.size() * sizeof(BatchBlock));
+        bp.launches.push_back(l);
+    }
+    upload(bp.buf, host);
+    bp.covered = std::move(covered);
+    bp.ready = true;
+}
+
+// A program whose rows have several structures and run the table-driven
+// kernels takes merged launches.
+bool batches(tq_program p) { return !p->pd->opt.specialize && p->pd->groups.size() > 1; }
+
+// The merged launches of a mode (recorded on first use, and those of the
+// simpler modes with them, so that a captured call finds them ready).
+const BatchPlan &batch_plan(tq_program p, int mode, int K)
+{
+    ensure_batch(p, p->state_batch, BM_STATE, 0);
+    if (mode == BM_STATE) return p->state_batch;
+    ensure_batch(p, p->obs_batch->exp, BM_EXP, K);
+    if (mode == BM_EXP) return p->obs_batch->exp;
+    ensure_batch(p, p->obs_batch->adj, BM_ADJ, K);
+    return p->obs_batch->adj;
+}
+
+void run_batch(tq_program p, const BatchPlan &bp, ResCall c, hipStream_t s)
+{
+    c.noise_seed = p->noise_seed;
+    const char *at = static_cast<const char *>(bp.buf.p);
+    for (const BatchPlan::Launch &l : bp.launches) {
+        if (l.kind == BK_PAULI_REDUCE && !c.exp_out) continue;
+        hip_check(launch_batch(l.kind, at + l.table, reinterpret_cast<const BatchBlock *>(at + l.blocks), l.nblocks, l.lds,
+                               l.threads, l.p, l.phi, c, s),
+                  "merged launch");
+    }
+}
+
 // Expectations of every group's rows (the body of tq_expectation).
 void expectations_all(tq_program prog, const float *theta, const ObsData &od, float *out, hipStream_t s)
 {
-    const ProgramData &pd = *prog->pd;
     ensure_obs(prog, od);
-    float2 *psi = psi_ws(prog);
-    for (size_t gi = 0; gi < pd.groups.size(); gi++) {
-        const Group &g = *pd.groups[gi];
-        GroupDev &gd = *prog->gdev[gi];
-        const RunRows rr = own_rows(prog, gi);
-        if (resident(prog, gi, false, prog->obs_dev[gi]->tmax)) {
-            ResArgs a = resident_args(prog, gi, theta, false, s, rr);
-            resident_terms(prog, gi, a, od.K, out, rr);
-            run_resident(prog, gi, a, rr.n, s);
-            continue;
-        }
-        build_mats(prog, gi, theta, g.fwd_tasks.begin, g.fwd_tasks.end, s, rr);
-        forward(prog, gi, psi + gd.psi_off, (int64_t)1 << g.n, rr.ident, s, rr);
-        pauli_group(prog, gi, psi + gd.psi_off, nullptr, nullptr, od.K, out, s, rr);
+    const BatchPlan *bp = batches(prog) && od.K > 0 ? &batch_plan(prog, BM_EXP, od.K) : nullptr;
+    if (bp) {
+        ResCall c{};
+        c.theta = theta;
+        c.exp_out = out;
+        run_batch(prog, *bp, c, s);
     }
+    for (size_t gi = 0; gi < prog->pd->groups.size(); gi++)
+        if (!bp || !bp->covered[gi]) expectation_group(prog, gi, theta, od.K, out, s, own_rows(prog, gi));
 }
 
 // ------------------------------------------------ batched shift rules
@@ -1345,7 +1619,7 @@ void shift_grad(tq_program prog, const float *theta, tq_observables obs, const f
                     if (on_chip[gi]) {
                         ResArgs a = resident_args(prog, gi, theta, false, s, rr);
                         resident_terms(prog, gi, a, Ke, vals, rr);
-                        run_resident(prog, gi, a, c, s);
+                        run_resident(prog, gi, a, c, s, rr);
                     } else {
                         build_mats(prog, gi, theta, g.fwd_tasks.begin, g.fwd_tasks.end, s, rr);
                         forward(prog, gi, psi, (int64_t)1 << g.n, ident, s, rr);
@@ -1384,6 +1658,101 @@ void shift_grad(tq_program prog, const float *theta, tq_observables obs, const f
         ga.grad = grad;
         hip_check(launch_shift_grad(ga, nrows, s), "shift-rule gradient launch");
     }
+}
+
+// One group's rows of tq_adjoint_grad.
+void adjoint_group(tq_program prog, size_t gi, const float *theta, int K, const float *upstream, float *grad,
+                   float *expectations, hipStream_t s, const RunRows &rr)
+{
+    const ProgramData &pd = *prog->pd;
+    const Group &g = *pd.groups[gi];
+    GroupDev &gd = *prog->gdev[gi];
+    ObsGroupDev &og = *prog->obs_dev[gi];
+    const int nrows = (int)g.rows.size();
+    const int64_t stride = (int64_t)1 << g.n;
+    if (resident(prog, gi, true, og.tmax)) {
+        ResArgs a = resident_args(prog, gi, theta, pd.S > 0, s, rr);
+        resident_terms(prog, gi, a, K, expectations, rr);
+        if (pd.S > 0) {
+            a.upstream = upstream;
+            a.grad = grad;
+            a.nacc = og.tmax + g.n_gslots;
+        }
+        a.nacc = std::max(a.nacc, 1);
+        run_resident(prog, gi, a, rr.n, s, rr);
+        return;
+    }
+    float2 *psi = psi_ws(prog) + gd.psi_off;
+    build_mats(prog, gi, theta, g.fwd_tasks.begin, g.rev_tasks.end, s, rr);
+    forward(prog, gi, psi, stride, rr.ident, s, rr);
+    if (pd.S == 0) {
+        if (expectations && K > 0) pauli_group(prog, gi, psi, nullptr, nullptr, K, expectations, s, rr);
+        return;
+    }
+    // phi = H_g psi, with the expectations from the same sweep
+    float2 *phi = phi_ws(prog) + gd.psi_off;
+    if (K > 0)
+        pauli_group(prog, gi, psi, phi, upstream, K, expectations, s, rr);
+    else
+        hip_check(launch_zero_tail(phi, stride, (const int32_t *)gd.ident.p, nrows, 0, stride, s), "phi clear");
+    // reverse sweep
+    const int trl = g.rev.empty() ? 0 : g.n - g.rev[0].geom.t;
+    const int wg = wg_for(nrows, trl);
+    const size_t bytes = sizeof(double) * (size_t)nrows * wg * std::max(g.n_gslots, 1);
+    double *gpart = rr.rec ? BatchRec::region(rr.rec->gpart, bytes) : (double *)prog->gpart.ensure(bytes);
+    int gbase = 0;
+    for (size_t pi = 0; pi < g.rev.size(); pi++) {
+        const Pass &ps = g.rev[pi];
+        RevArgs r{};
+        r.psi = psi;
+        r.phi = phi;
+        r.row_stride = stride;
+        r.rows = (const int32_t *)gd.ident.p;
+        r.mats = mat_ws(prog) + gd.mat_off;
+        r.mat_stride = std::max(g.mat_block, 1);
+        r.ops = (const PassOp *)gd.rev_ops.p;
+        r.stages = (const Stage *)gd.rev_stages.p + gd.rev_stage_off[pi];
+        r.nstages = (int)ps.stages.size();
+        r.g = ps.geom;
+        r.tiles_log2 = g.n - ps.geom.t;
+        r.wg_per_row = wg;
+        r.store = pi + 1 < g.rev.size();
+        r.gpart = gpart;
+        r.n_gslots = g.n_gslots;
+        int gc = 0;
+        for (const PassOp &op : ps.ops) gc += op.ngrad;
+        r.gbase = gbase;
+        r.gcount = gc;
+        r.mat_begin = ps.mat_begin;
+        r.mat_end = ps.mat_end;
+        gbase += gc;
+        // (a structure without symbolic parameters has no generated
+        // reverse passes: it takes the precompiled kernel)
+        if (pd.opt.specialize && g.n_gslots > 0) {
+            std::string log;
+            const hipError_t e = launch_rev_pass_spec(g, (int)pi, r, nrows, s, &log, &gd.pass_memo);
+            if (e == hipErrorInvalidSource) fail(TQ_E_DEVICE, log);
+            hip_check(e, "specialised reverse pass launch");
+            continue;
+        }
+        if (rr.rec) rr.rec->add(6, (int)pi, BK_REV, r, nrows * wg, rev_pass_lds_bytes(r), r.nstages);
+        else hip_check(launch_rev_pass(r, nrows, s), "reverse pass launch");
+    }
+    GradReduceArgs gr{};
+    gr.rows = (const int32_t *)gd.rows.p;
+    gr.gpart = gpart;
+    gr.wg_per_row = wg;
+    gr.n_gslots = g.n_gslots;
+    gr.sym_begin = (const int32_t *)gd.sym_begin.p;
+    gr.sym_gslots = (const int32_t *)gd.sym_gslots.p;
+    gr.gslot_slot = (const int32_t *)gd.gslot_slot.p;
+    gr.slot_scale = (const double *)gd.scale.p;
+    gr.uniform = g.uniform_slots;
+    gr.n_slots = g.n_slots;
+    gr.S = pd.S;
+    gr.grad = grad;
+    if (rr.rec) rr.rec->add(7, 0, BK_GRAD_REDUCE, gr, nrows, 0, 0);
+    else hip_check(launch_grad_reduce(gr, nrows, s), "gradient reduce launch");
 }
 
 } // namespace
@@ -1510,26 +1879,15 @@ tq_status tq_simulate_state(tq_program prog, const float *theta, void *states, v
         check_align(theta, 4, "symbol_values");
         ensure_device(prog);
         hipStream_t s = as_stream(stream);
-        const int64_t stride = (int64_t)1 << pd.nmax;
-        for (size_t gi = 0; gi < pd.groups.size(); gi++) {
-            const Group &g = *pd.groups[gi];
-            GroupDev &gd = *prog->gdev[gi];
-            const RunRows rr = own_rows(prog, gi);
-            if (resident(prog, gi, false, 0)) {
-                ResArgs a = resident_args(prog, gi, theta, false, s, rr);
-                a.state_out = (float2 *)states;
-                a.out_stride = stride;
-                a.out_rows = (const int32_t *)gd.rows.p;
-                run_resident(prog, gi, a, rr.n, s);
-            } else {
-                build_mats(prog, gi, theta, g.fwd_tasks.begin, g.fwd_tasks.end, s, rr);
-                forward(prog, gi, (float2 *)states, stride, (const int32_t *)gd.rows.p, s, rr);
-            }
-            if (g.n < pd.nmax)
-                hip_check(launch_zero_tail((float2 *)states, stride, (const int32_t *)gd.rows.p, (int)g.rows.size(),
-                                           (int64_t)1 << g.n, stride, s),
-                          "zero tail launch");
+        const BatchPlan *bp = batches(prog) ? &batch_plan(prog, BM_STATE, 0) : nullptr;
+        if (bp) {
+            ResCall c{};
+            c.theta = theta;
+            c.state_out = (float2 *)states;
+            run_batch(prog, *bp, c, s);
         }
+        for (size_t gi = 0; gi < pd.groups.size(); gi++)
+            if (!bp || !bp->covered[gi]) state_group(prog, gi, theta, (float2 *)states, s, own_rows(prog, gi));
     });
 }
 
@@ -1545,23 +1903,7 @@ tq_status tq_expectation(tq_program prog, const float *theta, tq_observables obs
         check_align(out, 4, "out");
         check_align(theta, 4, "symbol_values");
         ensure_device(prog);
-        ensure_obs(prog, *obs->od);
-        hipStream_t s = as_stream(stream);
-        float2 *psi = psi_ws(prog);
-        for (size_t gi = 0; gi < pd.groups.size(); gi++) {
-            const Group &g = *pd.groups[gi];
-            GroupDev &gd = *prog->gdev[gi];
-            const RunRows rr = own_rows(prog, gi);
-            if (resident(prog, gi, false, prog->obs_dev[gi]->tmax)) {
-                ResArgs a = resident_args(prog, gi, theta, false, s, rr);
-                resident_terms(prog, gi, a, obs->od->K, out, rr);
-                run_resident(prog, gi, a, rr.n, s);
-                continue;
-            }
-            build_mats(prog, gi, theta, g.fwd_tasks.begin, g.fwd_tasks.end, s, rr);
-            forward(prog, gi, psi + gd.psi_off, (int64_t)1 << g.n, rr.ident, s, rr);
-            pauli_group(prog, gi, psi + gd.psi_off, nullptr, nullptr, obs->od->K, out, s, rr);
-        }
+        expectations_all(prog, theta, *obs->od, out, as_stream(stream));
     });
 }
 
@@ -1582,97 +1924,19 @@ tq_status tq_adjoint_grad(tq_program prog, const float *theta, tq_observables ob
         ensure_device(prog);
         ensure_obs(prog, *obs->od);
         hipStream_t s = as_stream(stream);
-        float2 *psi = psi_ws(prog), *phi = phi_ws(prog);
         const int K = obs->od->K;
-        for (size_t gi = 0; gi < pd.groups.size(); gi++) {
-            const Group &g = *pd.groups[gi];
-            GroupDev &gd = *prog->gdev[gi];
-            ObsGroupDev &og = *prog->obs_dev[gi];
-            const int nrows = (int)g.rows.size();
-            const int64_t stride = (int64_t)1 << g.n;
-            const RunRows rr = own_rows(prog, gi);
-            if (resident(prog, gi, true, og.tmax)) {
-                ResArgs a = resident_args(prog, gi, theta, pd.S > 0, s, rr);
-                resident_terms(prog, gi, a, K, expectations, rr);
-                if (pd.S > 0) {
-                    a.upstream = upstream;
-                    a.grad = grad;
-                    a.nacc = og.tmax + g.n_gslots;
-                }
-                a.nacc = std::max(a.nacc, 1);
-                run_resident(prog, gi, a, rr.n, s);
-                continue;
-            }
-            build_mats(prog, gi, theta, g.fwd_tasks.begin, g.rev_tasks.end, s, rr);
-            forward(prog, gi, psi + gd.psi_off, stride, rr.ident, s, rr);
-            if (pd.S == 0) {
-                if (expectations && K > 0)
-                    pauli_group(prog, gi, psi + gd.psi_off, nullptr, nullptr, K, expectations, s, rr);
-                continue;
-            }
-            // phi = H_g psi, with the expectations from the same sweep
-            if (K > 0)
-                pauli_group(prog, gi, psi + gd.psi_off, phi + gd.psi_off, upstream, K, expectations, s, rr);
-            else
-                hip_check(launch_zero_tail(phi + gd.psi_off, stride, (const int32_t *)gd.ident.p, nrows, 0, stride, s),
-                          "phi clear");
-            // reverse sweep
-            const int trl = g.rev.empty() ? 0 : g.n - g.rev[0].geom.t;
-            const int wg = wg_for(nrows, trl);
-            double *gpart =
-                (double *)prog->gpart.ensure(sizeof(double) * (size_t)nrows * wg * std::max(g.n_gslots, 1));
-            int gbase = 0;
-            for (size_t pi = 0; pi < g.rev.size(); pi++) {
-                const Pass &ps = g.rev[pi];
-                RevArgs r{};
-                r.psi = psi + gd.psi_off;
-                r.phi = phi + gd.psi_off;
-                r.row_stride = stride;
-                r.rows = (const int32_t *)gd.ident.p;
-                r.mats = mat_ws(prog) + gd.mat_off;
-                r.mat_stride = std::max(g.mat_block, 1);
-                r.ops = (const PassOp *)gd.rev_ops.p;
-                r.stages = (const Stage *)gd.rev_stages.p + gd.rev_stage_off[pi];
-                r.nstages = (int)ps.stages.size();
-                r.g = ps.geom;
-                r.tiles_log2 = g.n - ps.geom.t;
-                r.wg_per_row = wg;
-                r.store = pi + 1 < g.rev.size();
-                r.gpart = gpart;
-                r.n_gslots = g.n_gslots;
-                int gc = 0;
-                for (const PassOp &op : ps.ops) gc += op.ngrad;
-                r.gbase = gbase;
-                r.gcount = gc;
-                r.mat_begin = ps.mat_begin;
-                r.mat_end = ps.mat_end;
-                gbase += gc;
-                // (a structure without symbolic parameters has no generated
-                // reverse passes: it takes the precompiled kernel)
-                if (pd.opt.specialize && g.n_gslots > 0) {
-                    std::string log;
-                    const hipError_t e = launch_rev_pass_spec(g, (int)pi, r, nrows, s, &log, &gd.pass_memo);
-                    if (e == hipErrorInvalidSource) fail(TQ_E_DEVICE, log);
-                    hip_check(e, "specialised reverse pass launch");
-                    continue;
-                }
-                hip_check(launch_rev_pass(r, nrows, s), "reverse pass launch");
-            }
-            GradReduceArgs gr{};
-            gr.rows = (const int32_t *)gd.rows.p;
-            gr.gpart = gpart;
-            gr.wg_per_row = wg;
-            gr.n_gslots = g.n_gslots;
-            gr.sym_begin = (const int32_t *)gd.sym_begin.p;
-            gr.sym_gslots = (const int32_t *)gd.sym_gslots.p;
-            gr.gslot_slot = (const int32_t *)gd.gslot_slot.p;
-            gr.slot_scale = (const double *)gd.scale.p;
-            gr.uniform = g.uniform_slots;
-            gr.n_slots = g.n_slots;
-            gr.S = pd.S;
-            gr.grad = grad;
-            hip_check(launch_grad_reduce(gr, nrows, s), "gradient reduce launch");
+        const BatchPlan *bp = batches(prog) && K > 0 && pd.S > 0 ? &batch_plan(prog, BM_ADJ, K) : nullptr;
+        if (bp) {
+            ResCall c{};
+            c.theta = theta;
+            c.exp_out = expectations;
+            c.upstream = upstream;
+            c.grad = grad;
+            run_batch(prog, *bp, c, s);
         }
+        for (size_t gi = 0; gi < pd.groups.size(); gi++)
+            if (!bp || !bp->covered[gi])
+                adjoint_group(prog, gi, theta, K, upstream, grad, expectations, s, own_rows(prog, gi));
     });
 }
 
