@@ -1199,6 +1199,16 @@ __device__ __forceinline__ float2 h_elem(uint32_t l, uint64_t fb, const TermDev 
     return make_float2((float)ax, (float)ay);
 }
 
+// -1 when the row's Pauli frame negates the angle of gradient slot gs (the
+// sweep differentiates with respect to the negated one), else 1
+template <class A> __device__ __forceinline__ double frame_sign(const A &a, int row, int gs)
+{
+    if (!a.frames) return 1.0;
+    const int f = a.gslot_flip[gs];
+    if (f < 0) return 1.0;
+    return ((a.frames[(int64_t)row * a.frame_words + (f >> 5)] >> (f & 31)) & 1u) ? -1.0 : 1.0;
+}
+
 // ------------------------------------------- resident circuit parts
 // The resident computation in three parts around the forward and reverse
 // register stages (which the generic kernel loops over and a specialised
@@ -1280,10 +1290,21 @@ __device__ __forceinline__ void resident_end(const A &a, const C &c, double *acc
             double sum = 0;
             for (int k = a.sym_begin[s]; k < a.sym_begin[s + 1]; k++) {
                 const int gs = a.sym_gslots[k];
-                sum += 2.0 * scale[a.gslot_slot[gs]] * total(a.gacc + gs);
+                sum += 2.0 * scale[a.gslot_slot[gs]] * total(a.gacc + gs) * frame_sign(a, row, gs);
             }
             c.grad[(int64_t)b * a.S + s] = (float)sum;
         }
+    }
+}
+
+// Read the matrices [begin, end) of a row block once, all threads together, so
+// that the scalar loads of the stages find them in the L2 (generated kernels
+// keep no copy in LDS).
+__device__ __forceinline__ void touch_mats(const double2 *row_block, int begin, int end)
+{
+    for (int i = begin + (int)threadIdx.x; i < end; i += blockDim.x) {
+        const double v = row_block[i].x;
+        asm volatile("" ::"v"(v));
     }
 }
 
@@ -1305,9 +1326,11 @@ struct PassCtx {
     int row, w, a1;
 };
 
-// state: the states' array; bid: the workgroup's number among the group's
+// state: the states' array; bid: the workgroup's number among the group's;
+// nm: how many of the pass's matrices are staged in LDS (the table-driven
+// kernel: all; generated ones: the product-init ones, which come first)
 template <class A>
-__device__ __forceinline__ PassCtx pass_setup(const A &a, float2 *state, int bid, unsigned char *smem)
+__device__ __forceinline__ PassCtx pass_setup(const A &a, float2 *state, int bid, unsigned char *smem, int nm)
 {
     const auto &g = a.g;
     const int t = g.t;
@@ -1315,14 +1338,16 @@ __device__ __forceinline__ PassCtx pass_setup(const A &a, float2 *state, int bid
     c.lds = reinterpret_cast<float2 *>(smem);
     c.hi_off = reinterpret_cast<uint64_t *>(smem + sizeof(float2) * (1 << t));
     c.lm = reinterpret_cast<double2 *>(c.hi_off + (1 << g.h));
-    c.p1 = c.lm + (a.mat_end - a.mat_begin);
+    c.p1 = c.lm + nm;
     c.a1 = t / 2;
     c.p2 = c.p1 + (1 << c.a1);
     c.row = bid / a.wg_per_row;
     c.w = bid % a.wg_per_row;
     c.st = as_global(state) + (int64_t)cget(a.rows, c.row) * a.row_stride;
     build_hi_off(g, c.hi_off);
-    stage_mats(c.lm, a.mats + (int64_t)c.row * a.mat_stride, a.mat_begin, a.mat_end);
+    const double2 *block = a.mats + (int64_t)c.row * a.mat_stride;
+    stage_mats(c.lm, block, a.mat_begin, a.mat_begin + nm);
+    touch_mats(block, a.mat_begin + nm, a.mat_end);
     __syncthreads();
     if (a.product_init) {
         // per-qubit product-state vectors: column 0 of each init matrix
@@ -1377,12 +1402,12 @@ struct RevCtx {
     float2 *lp, *lf;    // psi and phi tiles
     uint64_t *hi_off;
     double2 *lm;        // the pass's matrices
-    double *acc;        // [4 waves][gcount] gradient partials
+    double *acc;        // [waves][gcount] gradient partials
     float2 *sp, *sf;    // the row's psi and phi
     int row, w;
 };
 
-template <class A> __device__ __forceinline__ RevCtx rev_setup(const A &a, int bid, unsigned char *smem)
+template <class A> __device__ __forceinline__ RevCtx rev_setup(const A &a, int bid, unsigned char *smem, int nm)
 {
     const auto &g = a.g;
     const uint32_t T = 1u << g.t;
@@ -1391,15 +1416,17 @@ template <class A> __device__ __forceinline__ RevCtx rev_setup(const A &a, int b
     c.lf = c.lp + T;
     c.hi_off = reinterpret_cast<uint64_t *>(c.lf + T);
     c.lm = reinterpret_cast<double2 *>(c.hi_off + (1 << g.h));
-    c.acc = reinterpret_cast<double *>(c.lm + (a.mat_end - a.mat_begin));
+    c.acc = reinterpret_cast<double *>(c.lm + nm);
     c.row = bid / a.wg_per_row;
     c.w = bid % a.wg_per_row;
     const int b = cget(a.rows, c.row);
     c.sp = as_global(a.psi) + (int64_t)b * a.row_stride;
     c.sf = as_global(a.phi) + (int64_t)b * a.row_stride;
     build_hi_off(g, c.hi_off);
-    stage_mats(c.lm, a.mats + (int64_t)c.row * a.mat_stride, a.mat_begin, a.mat_end);
-    for (int j = threadIdx.x; j < 4 * a.gcount; j += blockDim.x) c.acc[j] = 0;
+    const double2 *block = a.mats + (int64_t)c.row * a.mat_stride;
+    stage_mats(c.lm, block, a.mat_begin, a.mat_begin + nm);
+    touch_mats(block, a.mat_begin + nm, a.mat_end);
+    for (int j = threadIdx.x; j < (int)(blockDim.x / 64) * a.gcount; j += blockDim.x) c.acc[j] = 0;
     __syncthreads();
     return c;
 }
@@ -1423,8 +1450,11 @@ template <class A> __device__ __forceinline__ void rev_store(const A &a, const R
 template <class A> __device__ __forceinline__ void rev_finish(const A &a, const RevCtx &c)
 {
     double *out = a.gpart + ((int64_t)c.row * a.wg_per_row + c.w) * a.n_gslots + a.gbase;
-    for (int j = threadIdx.x; j < a.gcount; j += blockDim.x)
-        out[j] = ((c.acc[j] + c.acc[a.gcount + j]) + c.acc[2 * a.gcount + j]) + c.acc[3 * a.gcount + j];
+    for (int j = threadIdx.x; j < a.gcount; j += blockDim.x) {
+        double s = c.acc[j];
+        for (int w = 1; w < (int)(blockDim.x / 64); w++) s += c.acc[w * a.gcount + j];
+        out[j] = s;
+    }
 }
 
 } // namespace tq

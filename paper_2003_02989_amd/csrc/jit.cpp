@@ -490,7 +490,7 @@ bool cut_key(const Group &g, const PassOp &op, std::tuple<int, int, double, doub
     if (!bt || bt->mem_count != 1 || bt->diag != 1 || bt->dim != 4) return false;
     const Member &mb = g.members[bt->mem_begin];
     const GateDev &gd = g.gates[mb.gate];
-    if ((gd.op != OP_RZZ && gd.op != OP_ZZPOW) || mb.form != FORM_FULL || gd.np != 1) return false;
+    if ((gd.op != OP_RZZ && gd.op != OP_ZZPOW) || mb.form != FORM_FULL || gd.np != 1 || gd.flip >= 0) return false;
     const int sl = gd.slot0;
     *key = std::make_tuple((int)gd.op, (int)g.slot_sym[sl], g.slot_scale[sl], g.slot_off[sl]);
     return true;
@@ -824,6 +824,7 @@ bool const_m1(const Group &g, const PassOp &op, ConstM1 *out)
     double acc[8] = {1, 0, 0, 0, 0, 0, 1, 0};
     for (int mi = 0; mi < bt->mem_count; mi++) {
         const GateDev &gd = g.gates[g.members[bt->mem_begin + mi].gate];
+        if (gd.flip >= 0) return false;
         double eta[3] = {0, 0, 0};
         for (int j = 0; j < gd.np; j++) {
             if (g.slot_sym[gd.slot0 + j] >= 0) return false;
@@ -1239,78 +1240,72 @@ std::string resident_source(const Group &g)
 
 namespace {
 
+// Workgroups of the generated reverse passes: 256 threads, 512 for tiles whose
+// LDS leaves room for one workgroup on a CU (two states of 2^13 amplitudes), so
+// that eight wavefronts share it as with two workgroups.
+int rev_threads(const TileGeom &gm) { return gm.t > 12 ? 512 : kThreads; }
+// product-init matrices a generated first pass stages (they come first)
+int init_mats(const Pass &ps) { return ps.product_init ? 4 * ps.geom.n : 0; }
+
 // Tile loads and stores of a generated forward pass with the tile's geometry
 // written in (every pass but the first, which generates the product state):
-// thread tid holds the pairs l = 2 tid + 512 k (k < 2^t / 512) of the tile.
-// The global offset of l is a per-thread part -- the tid bits deposited at
-// their global positions -- plus a constant per k, and its LDS position sw(l)
-// is one of two per-thread values (by the parity of k) plus 512 k, an
-// immediate offset: no table lookups and no guards, all loads of a tile
-// issued back to back.
-bool direct_io(const Pass &ps) { return !ps.product_init && ps.geom.t >= 9 && ps.geom.c >= 1; }
-
-// global index bit of tile-local bit b
-int gpos(const TileGeom &gm, int b) { return b < gm.c ? b : gm.hb[b - gm.c]; }
-
-// With kFwdPrefetch the next tile's loads are issued right after the current
-// tile is in LDS, into registers held over its stages, so that every
-// workgroup streams its next tile while it computes; the registers this takes
-// leave three workgroups per CU instead of four.
-constexpr bool kFwdPrefetch = true;
-
-void direct_io_setup(std::ostream &o, const TileGeom &gm)
-{
-    o << "    const uint32_t tb_ = (uint32_t)tid << 1;\n"
-         "    const uint32_t la0_ = tb_ ^ ((tb_ >> 5) & 15u), la1_ = la0_ ^ 16u, lb0_ = la0_ ^ 1u, lb1_ = la1_ ^ 1u;\n"
-         "    uint64_t toff_ = 0;\n";
-    for (int j = 0; j < 8; j++)
-        o << "    toff_ |= (uint64_t)(((uint32_t)tid >> " << j << ") & 1u) << " << gpos(gm, j + 1) << ";\n";
-}
-
-uint64_t chunk_offset(const TileGeom &gm, int k)
-{
-    uint64_t o = 0;
-    for (int m = 0; 9 + m < gm.t; m++)
-        if ((k >> m) & 1) o |= 1ull << gpos(gm, 9 + m);
-    return o;
-}
-
-void direct_load(std::ostream &o, const TileGeom &gm, const std::string &fb, const std::string &dst,
-                 const std::string &row = "c.st")
-{
-    const int K = 1 << (gm.t - 9);
-    o << "    { const float2 *src_ = " << row << " + (" << fb << " | toff_);\n";
-    for (int k = 0; k < K; k++)
-        o << "      " << dst << "[" << k << "] = *reinterpret_cast<const float4 *>(src_ + " << chunk_offset(gm, k)
-          << "ull);\n";
-    o << "    }\n";
-}
-
-void direct_to_lds(std::ostream &o, const TileGeom &gm, const std::string &srcv, const std::string &lds = "lp")
-{
-    const int K = 1 << (gm.t - 9);
-    for (int k = 0; k < K; k++) {
-        const std::string p = (k & 1) ? "1_" : "0_";
-        o << "    " << lds << "[la" << p << " + " << 512 * k << "u] = make_float2(" << srcv << "[" << k << "].x, " << srcv << "[" << k
-          << "].y); " << lds << "[lb" << p << " + " << 512 * k << "u] = make_float2(" << srcv << "[" << k << "].z, " << srcv << "["
-          << k << "].w);\n";
+// thread tid of nt holds the pairs l = 2 tid + 2 nt k (k < 2^t / (2 nt)) of the
+// tile.  The global offset of l is a per-thread part -- the tid bits deposited
+// at their global positions -- plus a constant per k, and its LDS position
+// sw(l) is a per-thread value (for 256 threads one of two, by the parity of k)
+// plus 2 nt k, an immediate offset: no table lookups and no guards, all loads
+// of a tile issued back to back.
+struct DirectIO {
+    int lnt;  // log2 of the threads
+    TileGeom gm;
+    DirectIO(const TileGeom &g, int nt) : lnt(__builtin_ctz(nt)), gm(g) {}
+    bool fits() const { return gm.t >= lnt + 1 && gm.c >= 1; }
+    int chunks() const { return 1 << (gm.t - lnt - 1); }
+    // global index bit of tile-local bit b
+    int gpos(int b) const { return b < gm.c ? b : gm.hb[b - gm.c]; }
+    // the swizzle xors bits 5..9 into 0..4: with 256 threads bit 9 is k's
+    std::string par(int k) const { return lnt == 8 && (k & 1) ? "1_" : "0_"; }
+    uint64_t chunk_offset(int k) const
+    {
+        uint64_t o = 0;
+        for (int m = 0; lnt + 1 + m < gm.t; m++)
+            if ((k >> m) & 1) o |= 1ull << gpos(lnt + 1 + m);
+        return o;
     }
-}
-
-void direct_store(std::ostream &o, const TileGeom &gm, const std::string &fb, const std::string &row = "c.st",
-                  const std::string &lds = "lp")
-{
-    const int K = 1 << (gm.t - 9);
-    o << "    { float2 *dst_ = " << row << " + (" << fb << " | toff_);\n";
-    for (int k = 0; k < K; k++) {
-        const std::string p = (k & 1) ? "1_" : "0_";
-        o << "      { const float2 u0 = " << lds << "[la" << p << " + " << 512 * k << "u], u1 = " << lds << "[lb" << p
-          << " + " << 512 * k
-          << "u]; *reinterpret_cast<float4 *>(dst_ + " << chunk_offset(gm, k)
-          << "ull) = make_float4(u0.x, u0.y, u1.x, u1.y); }\n";
+    void setup(std::ostream &o) const
+    {
+        o << "    const uint32_t tb_ = (uint32_t)tid << 1;\n"
+             "    const uint32_t la0_ = tb_ ^ ((tb_ >> 5) & 31u), lb0_ = la0_ ^ 1u;\n";
+        if (lnt == 8) o << "    const uint32_t la1_ = la0_ ^ 16u, lb1_ = la1_ ^ 1u;\n";
+        o << "    uint64_t toff_ = 0;\n";
+        for (int j = 0; j < lnt; j++)
+            o << "    toff_ |= (uint64_t)(((uint32_t)tid >> " << j << ") & 1u) << " << gpos(j + 1) << ";\n";
     }
-    o << "    }\n";
-}
+    void load(std::ostream &o, const std::string &fb, const std::string &dst, const std::string &row = "c.st") const
+    {
+        o << "    { const float2 *src_ = " << row << " + (" << fb << " | toff_);\n";
+        for (int k = 0; k < chunks(); k++)
+            o << "      " << dst << "[" << k << "] = *reinterpret_cast<const float4 *>(src_ + " << chunk_offset(k)
+              << "ull);\n";
+        o << "    }\n";
+    }
+    void to_lds(std::ostream &o, const std::string &srcv, const std::string &lds = "lp") const
+    {
+        for (int k = 0; k < chunks(); k++)
+            o << "    " << lds << "[la" << par(k) << " + " << (2 << lnt) * k << "u] = make_float2(" << srcv << "[" << k
+              << "].x, " << srcv << "[" << k << "].y); " << lds << "[lb" << par(k) << " + " << (2 << lnt) * k
+              << "u] = make_float2(" << srcv << "[" << k << "].z, " << srcv << "[" << k << "].w);\n";
+    }
+    void store(std::ostream &o, const std::string &fb, const std::string &row = "c.st", const std::string &lds = "lp") const
+    {
+        o << "    { float2 *dst_ = " << row << " + (" << fb << " | toff_);\n";
+        for (int k = 0; k < chunks(); k++)
+            o << "      { const float2 u0 = " << lds << "[la" << par(k) << " + " << (2 << lnt) * k << "u], u1 = " << lds
+              << "[lb" << par(k) << " + " << (2 << lnt) * k << "u]; *reinterpret_cast<float4 *>(dst_ + " << chunk_offset(k)
+              << "ull) = make_float4(u0.x, u0.y, u1.x, u1.y); }\n";
+        o << "    }\n";
+    }
+};
 
 } // namespace
 
@@ -1319,19 +1314,23 @@ std::string pass_kernel_source(const Group &g, int pass)
     std::ostringstream o;
     const Pass &ps = g.fwd[pass];
     const TileGeom &gm = ps.geom;
-    const bool dio = direct_io(ps), pre = dio && kFwdPrefetch;
+    const int nt = kThreads;
+    const DirectIO io(gm, nt);
     const int64_t NT = 1ll << (gm.n - gm.t);
+    const bool dio = !ps.product_init && io.fits();
     // at most 128 registers (four workgroups of the tile's LDS share a CU), or
     // 168 with the prefetch registers (three); a pass with four-bit stages
     // (16 amplitudes and up to 16 diagonal entries per thread) may take 256,
     // so that it never spills -- the waves per SIMD follow what it uses
     int maxr = 0;
     for (const Stage &st : ps.stages) maxr = std::max(maxr, (int)st.r);
-    const int minwg = maxr >= 4 ? 2 : pre ? 3 : 4;
-    o << "extern \"C\" __global__ __launch_bounds__(256, " << minwg << ") void tq_fwd_" << pass
+    const int minwg = maxr >= 4 ? 2 : dio ? 3 : 4;
+    o << "extern \"C\" __global__ __launch_bounds__(" << nt << ", " << minwg << ") void tq_fwd_" << pass
       << "(PassArgs a)\n{\n"
          "    extern __shared__ __align__(16) unsigned char smem[];\n"
-         "    const PassCtx c = pass_setup(a, a.state, blockIdx.x, smem);\n"
+         "    const PassCtx c = pass_setup(a, a.state, blockIdx.x, smem, "
+      << init_mats(ps)
+      << ");\n"
          // op matrices through the scalar cache (SGPR operands of the FMAs),
          // not from the LDS copy: the stages' LDS traffic is the tile alone
          "    const SMat M = smat(a.mats + (int64_t)c.row * a.mat_stride + a.mat_begin);\n"
@@ -1340,6 +1339,7 @@ std::string pass_kernel_source(const Group &g, int pass)
          "    const int tid = threadIdx.x;\n";
     Env e{gm.t, ps.mat_begin, "G", gm.fixed_mask != 0, "", ""};
     e.fgrp = &g;
+    e.nt = nt;
     int ntab = 0;
     const std::vector<CutClass> cuts = cut_classes(g, ps, &ntab);
     if (!cuts.empty()) {
@@ -1367,7 +1367,7 @@ std::string pass_kernel_source(const Group &g, int pass)
         }
         o << "    }\n    __syncthreads();\n";
         for (const CutClass &c : cuts)
-            o << "    for (int j_ = tid; j_ <= " << c.ops.size() << "; j_ += 256) cutw_[" << c.tab << " + j_] = zpow(cutm_["
+            o << "    for (int j_ = tid; j_ <= " << c.ops.size() << "; j_ += " << nt << ") cutw_[" << c.tab << " + j_] = zpow(cutm_["
               << c.id << "], (uint32_t)j_);\n";
         o << "    __syncthreads();\n";
     }
@@ -1388,28 +1388,23 @@ std::string pass_kernel_source(const Group &g, int pass)
              "}\n";
         return o.str();
     }
-    direct_io_setup(o, gm);
-    const int K = 1 << (gm.t - 9);
-    o << "    float4 nx_[" << K << "];\n";
-    if (pre) {
-        o << "    if (c.w < " << NT << "ll) {\n";
-        direct_load(o, gm, "pdep64((uint64_t)c.w, " + std::to_string(gm.fixed_mask) + "ull)", "nx_");
-        o << "    }\n";
-    }
-    o << "    for (int64_t tile = c.w; tile < " << NT << "ll; tile += a.wg_per_row) {\n"
+    io.setup(o);
+    o << "    float4 nx_[" << io.chunks() << "];\n    if (c.w < " << NT << "ll) {\n";
+    io.load(o, "pdep64((uint64_t)c.w, " + std::to_string(gm.fixed_mask) + "ull)", "nx_");
+    o << "    }\n"
+      << "    for (int64_t tile = c.w; tile < " << NT << "ll; tile += a.wg_per_row) {\n"
       << "    const uint64_t fb = pdep64((uint64_t)tile, " << gm.fixed_mask << "ull);\n";
-    if (!pre) direct_load(o, gm, "fb", "nx_");
-    direct_to_lds(o, gm, "nx_");
-    o << "    __syncthreads();\n";
-    if (pre) {
-        // the next tile's loads, in flight during this tile's stages
-        o << "    if (tile + a.wg_per_row < " << NT << "ll) {\n"
-          << "    const uint64_t fbn_ = pdep64((uint64_t)(tile + a.wg_per_row), " << gm.fixed_mask << "ull);\n";
-        direct_load(o, gm, "fbn_", "nx_");
-        o << "    }\n";
-    }
+    io.to_lds(o, "nx_");
+    o << "    __syncthreads();\n"
+         // the next tile's loads, issued right after the current tile is in
+         // LDS, into registers held over its stages
+         "    if (tile + a.wg_per_row < "
+      << NT << "ll) {\n"
+      << "    const uint64_t fbn_ = pdep64((uint64_t)(tile + a.wg_per_row), " << gm.fixed_mask << "ull);\n";
+    io.load(o, "fbn_", "nx_");
+    o << "    }\n";
     stages();
-    direct_store(o, gm, "fb");
+    io.store(o, "fb");
     o << "    __syncthreads();\n"
          "    }\n"
          "}\n";
@@ -1426,48 +1421,50 @@ std::string rev_pass_kernel_source(const Group &g, int pass)
     const TileGeom &gm = ps.geom;
     int gcount = 0;
     for (const PassOp &op : ps.ops) gcount += op.ngrad;
-    const bool dio = gm.t >= 9 && gm.c >= 1;
-    o << "extern \"C\" __global__ __launch_bounds__(256, 2) void tq_rev_" << pass
+    const int nt = rev_threads(gm);
+    const DirectIO io(gm, nt);
+    const bool dio = io.fits();
+    o << "extern \"C\" __global__ __launch_bounds__(" << nt << ", 2) void tq_rev_" << pass
       << "(RevArgs a)\n{\n"
          "    extern __shared__ __align__(16) unsigned char smem[];\n"
-         "    const RevCtx c = rev_setup(a, blockIdx.x, smem);\n"
+         "    const RevCtx c = rev_setup(a, blockIdx.x, smem, 0);\n"
          // matrices through the scalar cache, as in the forward passes
          "    const SMat M = smat(a.mats + (int64_t)c.row * a.mat_stride + a.mat_begin);\n"
          "    float2 *lp = c.lp, *lf = c.lf;\n"
          "    double *acc = c.acc;\n"
          "    const int tid = threadIdx.x;\n";
-    if (dio) direct_io_setup(o, gm);
+    if (dio) io.setup(o);
     const bool greg = gcount > 0 && gcount <= kRevRegGrads;
     if (greg) o << "    double gacc_[" << gcount << "] = {};\n";
     const long long NT = 1ll << (gm.n - gm.t);
-    const int K = dio ? 1 << (gm.t - 9) : 0;
+    const int K = dio ? io.chunks() : 0;
     const bool pre = dio && kRevPrefetch;
     if (pre) {
         o << "    float4 xp_[" << K << "], xf_[" << K << "];\n"
           << "    if (c.w < " << NT << "ll) {\n";
         const std::string f0 = "pdep64((uint64_t)c.w, " + std::to_string(gm.fixed_mask) + "ull)";
-        direct_load(o, gm, f0, "xp_", "c.sp");
-        direct_load(o, gm, f0, "xf_", "c.sf");
+        io.load(o, f0, "xp_", "c.sp");
+        io.load(o, f0, "xf_", "c.sf");
         o << "    }\n";
     }
     o << "    for (int64_t tile = c.w; tile < " << NT << "ll; tile += a.wg_per_row) {\n"
       << "    const uint64_t fb = pdep64((uint64_t)tile, " << gm.fixed_mask << "ull);\n";
     if (pre) {
-        direct_to_lds(o, gm, "xp_", "lp");
-        direct_to_lds(o, gm, "xf_", "lf");
+        io.to_lds(o, "xp_", "lp");
+        io.to_lds(o, "xf_", "lf");
         o << "    __syncthreads();\n";
         // the next tile's loads, in flight during this tile's stages
         o << "    if (tile + a.wg_per_row < " << NT << "ll) {\n"
           << "    const uint64_t fbn_ = pdep64((uint64_t)(tile + a.wg_per_row), " << gm.fixed_mask << "ull);\n";
-        direct_load(o, gm, "fbn_", "xp_", "c.sp");
-        direct_load(o, gm, "fbn_", "xf_", "c.sf");
+        io.load(o, "fbn_", "xp_", "c.sp");
+        io.load(o, "fbn_", "xf_", "c.sf");
         o << "    }\n";
     } else if (dio) {
         o << "    { float4 xp_[" << K << "], xf_[" << K << "];\n";
-        direct_load(o, gm, "fb", "xp_", "c.sp");
-        direct_load(o, gm, "fb", "xf_", "c.sf");
-        direct_to_lds(o, gm, "xp_", "lp");
-        direct_to_lds(o, gm, "xf_", "lf");
+        io.load(o, "fb", "xp_", "c.sp");
+        io.load(o, "fb", "xf_", "c.sf");
+        io.to_lds(o, "xp_", "lp");
+        io.to_lds(o, "xf_", "lf");
         o << "    }\n    __syncthreads();\n";
     } else {
         o << "    rev_load(a, c, fb);\n    __syncthreads();\n";
@@ -1475,13 +1472,14 @@ std::string rev_pass_kernel_source(const Group &g, int pass)
     // accumulator rows of gcount slots, the pass's first slot at column 0
     Env e{gm.t, ps.mat_begin, "G", gm.fixed_mask != 0, N(gcount), N(-gbase)};
     e.grp = &g;
+    e.nt = nt;
     e.gacc_reg = greg;
     e.gshift = -gbase;
     for (const Stage &st : ps.stages) reverse_stage(o, e, ps, st);
     if (dio) {
         o << "    if (a.store) {\n";
-        direct_store(o, gm, "fb", "c.sp", "lp");
-        direct_store(o, gm, "fb", "c.sf", "lf");
+        io.store(o, "fb", "c.sp", "lp");
+        io.store(o, "fb", "c.sf", "lf");
         o << "    }\n";
     } else {
         o << "    rev_store(a, c, fb);\n";
@@ -2278,7 +2276,7 @@ hipError_t launch_pass_spec(const Group &g, int pass, const PassArgs &a, int nro
     hipFunction_t fn;
     hipError_t e = pass_kernel(g, false, pass, &fn, log, memo);
     if (e != hipSuccess) return e;
-    const size_t lds = pass_lds_bytes(a.g, a.product_init != 0, a.mat_end - a.mat_begin);
+    const size_t lds = pass_lds_bytes(a.g, a.product_init != 0, init_mats(g.fwd[pass]));
     return launch(fn, a, nrows * a.wg_per_row, lds, s, "pass");
 }
 
@@ -2340,7 +2338,8 @@ hipError_t launch_rev_pass_spec(const Group &g, int pass, const RevArgs &a, int 
     hipFunction_t fn;
     hipError_t e = pass_kernel(g, true, pass, &fn, log, memo);
     if (e != hipSuccess) return e;
-    return launch(fn, a, nrows * a.wg_per_row, rev_pass_lds_bytes(a), s, "rev_pass");
+    const int nt = rev_threads(a.g);
+    return launch(fn, a, nrows * a.wg_per_row, rev_pass_lds_bytes(a.g, 0, nt / 64, a.gcount), s, "rev_pass", nt);
 }
 
 hipError_t prepare_spec(const Group &g, bool resident, const char *target, std::string *log)

@@ -26,7 +26,8 @@ struct ShiftDev {
 struct BuildArgs {
     const BuildTask *tasks;
     int task_begin, task_end;
-    const Member *members;
+    const MemberDev *members;
+    int32_t full;                 // some task is a 4x4 neither diagonal nor a pair
     const GateDev *gates;
     const int32_t *slot_sym;
     const double *slot_scale, *slot_off;
@@ -46,6 +47,14 @@ struct BuildArgs {
     const PhaseTerm *phase_terms;
     // seed of the channels' per-row Kraus draws
     uint64_t noise_seed;
+    // Pauli frames (see plan_frames): per group row frame_words words (angles
+    // negated, X mask, Z mask, power of i); drawn by the builder from the
+    // channels and the table of what each Pauli changes; NULL: none
+    uint32_t *frames;
+    int32_t frame_words;
+    int32_t nchan;
+    const int32_t *chan_gates;    // gate of each channel
+    const uint32_t *frame_table;  // [nchan][2][frame_words]
     // derived rows of the batched shift rules (x_period = 0: the rows
     // themselves): launch row r is row L = x_begin + r of the group's
     // expansion, a copy of group row L / x_period with the parameter moves of
@@ -57,17 +66,11 @@ struct BuildArgs {
     // derived rows built from their source row's block: the block's first
     // x_copy entries are copied from x_src (the source rows' blocks), then
     // only the tasks task_list[list_begin[m] .. list_begin[m + 1]) of the
-    // row's move m are built again.  When the row carries a global phase,
-    // either the list starts with the task of phase_out (its members have a
-    // moved parameter), which takes the derived row's whole phase, or the
-    // copied phase_out matrix, holding the source row's phase, is multiplied
-    // by the change of the phase terms phase_list[phase_begin[m] ..
-    // phase_begin[m + 1]) (the terms of a moved parameter); phase_full[m]
-    // says which
+    // row's move m are built again (derived rows give expectations alone and
+    // keep no global phase of their own)
     const double2 *x_src;
     int32_t x_copy;
     const int32_t *list_begin, *task_list;
-    const int32_t *phase_full, *phase_begin, *phase_list;
 };
 
 struct StageBuildArgs {
@@ -211,6 +214,9 @@ struct ResArgs {
     int nrstages;
     const float *upstream;
     const int32_t *sym_begin, *sym_gslots, *gslot_slot;
+    const uint32_t *frames;      // Pauli frames (NULL: none) and the frame bit of each gradient slot
+    int frame_words;
+    const int32_t *gslot_flip;
     float *grad;
 };
 
@@ -247,6 +253,9 @@ struct GradReduceArgs {
     const double *slot_scale;
     int uniform, n_slots;
     int S;
+    const uint32_t *frames;      // as in ResArgs
+    int frame_words;
+    const int32_t *gslot_flip;
     float *grad;
 };
 

@@ -29,6 +29,7 @@ int gate_table_host(int op, const double *eta, const double *ex, int form, int d
 size_t pass_lds_bytes(const TileGeom &g, bool product_init, int nmat);
 size_t resident_lds_bytes(int n, int nacc, bool adjoint, int waves = kThreads / 64);
 hipError_t launch_resident(const ResArgs &a, int nrows, hipStream_t s);
+inline size_t build_lds_bytes(const BuildArgs &a) { return a.frames ? sizeof(uint32_t) * (size_t)a.frame_words : 0; }
 hipError_t launch_build(const BuildArgs &a, int nrows, hipStream_t s);
 // derived rows: the source rows' blocks copied, then the listed tasks of each
 // row's move rebuilt (max_list: the longest list)
@@ -44,6 +45,7 @@ int pauli_diag_slots(int amax, int k_count);
 // amax: the largest class count of a chunk (<= kDiagClassMax)
 hipError_t launch_pauli_diag(const DiagArgs &a, int nrows, int amax, hipStream_t s);
 hipError_t launch_pauli_reduce(const PauliReduceArgs &a, int nrows, hipStream_t s);
+size_t rev_pass_lds_bytes(const TileGeom &g, int nmat, int waves, int gcount);
 size_t rev_pass_lds_bytes(const RevArgs &a);
 hipError_t launch_rev_pass(const RevArgs &a, int nrows, hipStream_t s);
 hipError_t launch_grad_reduce(const GradReduceArgs &a, int nrows, hipStream_t s);

@@ -45,180 +45,253 @@ namespace tq {
 struct cd {
     double x, y;
 };
-__host__ __device__ __forceinline__ cd C(double x, double y) { return cd{x, y}; }
+__host__ __device__ __forceinline__ constexpr cd C(double x, double y) { return cd{x, y}; }
 __host__ __device__ __forceinline__ cd cdmul(cd a, cd b) { return cd{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
 __host__ __device__ __forceinline__ cd cdadd(cd a, cd b) { return cd{a.x + b.x, a.y + b.y}; }
 
-// sin and cos of x, and of pi x
-__host__ __device__ __forceinline__ void sc(double x, double *s, double *c)
+// sin and cos of x, or of pi x (half_turns).  Every lane of a builder
+// wavefront needs one and a lone wavefront runs at the speed of its
+// instruction stream, so both kinds share one short straight-line path: the
+// argument is reduced to y + yl, |y| <= pi/4, by k quarter turns (exactly for
+// pi x; for x by pi/2 in two parts, with k P1 exact under FMA while |x| <
+// 2^20; larger arguments take the library's reduction), then the Taylor series
+// (remainders y^19/19! < 1e-19 and y^18/18! < 3e-18).
+__host__ __device__ __forceinline__ void sincos_of(double x, bool half_turns, double *s, double *c)
 {
+    const double k = half_turns ? std::rint(2.0 * x) : std::rint(x * 0.63661977236758134308);
+    double y, yl;
+    if (half_turns) {
+        const double r = std::fma(-0.5, k, x);
+        y = r * 3.14159265358979311600;
+        yl = std::fma(r, 3.14159265358979311600, -y) + r * 1.22464679914735320717e-16;
+    } else {
+        const double r = std::fma(-k, 1.57079632679489655800, x);
+        y = std::fma(-k, 6.12323399573676603587e-17, r);
+        yl = std::fma(-k, 6.12323399573676603587e-17, r - y);
+    }
+    const double z = y * y;
+    double ps = 1.0 / 355687428096000.0, pc = 1.0 / 20922789888000.0;  // 1/17!, 1/16!
+    ps = std::fma(ps, z, -1.0 / 1307674368000.0);
+    pc = std::fma(pc, z, -1.0 / 87178291200.0);
+    ps = std::fma(ps, z, 1.0 / 6227020800.0);
+    pc = std::fma(pc, z, 1.0 / 479001600.0);
+    ps = std::fma(ps, z, -1.0 / 39916800.0);
+    pc = std::fma(pc, z, -1.0 / 3628800.0);
+    ps = std::fma(ps, z, 1.0 / 362880.0);
+    pc = std::fma(pc, z, 1.0 / 40320.0);
+    ps = std::fma(ps, z, -1.0 / 5040.0);
+    pc = std::fma(pc, z, -1.0 / 720.0);
+    ps = std::fma(ps, z, 1.0 / 120.0);
+    pc = std::fma(pc, z, 1.0 / 24.0);
+    ps = std::fma(ps, z, -1.0 / 6.0);
+    const double w = 0.5 * z, c0 = 1.0 - w;
+    const double sy = y + std::fma(y * z, ps, std::fma(-w, yl, yl));
+    const double cy = c0 + (((1.0 - c0) - w) + std::fma(z * z, pc, -y * yl));
+    // k mod 4 without an integer conversion that could overflow
+    const double q4 = k - 4.0 * std::floor(0.25 * k);
+    const bool odd = q4 == 1.0 || q4 == 3.0;
+    const double ss = odd ? cy : sy, cc = odd ? sy : cy;
+    *s = q4 >= 2.0 ? -ss : ss;
+    *c = q4 == 1.0 || q4 == 2.0 ? -cc : cc;
+    // (infinities and NaN take this path as well)
+    if (!half_turns && !(std::fabs(x) < 1048576.0)) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    sincos(x, s, c);
+        sincos(x, s, c);
 #else
-    *s = std::sin(x);
-    *c = std::cos(x);
+        *s = std::sin(x);
+        *c = std::cos(x);
 #endif
-}
-__host__ __device__ __forceinline__ void scpi(double x, double *s, double *c)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    sincospi(x, s, c);
-#else
-    *s = std::sin(M_PI * x);
-    *c = std::cos(M_PI * x);
-#endif
+    }
 }
 
-// m: row-major d x d, zero-initialised by the caller
-__host__ __device__ __forceinline__ int gate_matrix_dev(int op, const double *eta, const double *ex, int form, cd *m)
+// The angle a gate's matrix is written in: eta / 2 (RX, RY), eta (RZ, RZZ,
+// fSim's theta), pi t / 2 (X^t, Y^t, XX^t, YY^t) or pi t (Z^t, CZ^t, CNOT^t,
+// ZZ^t); pi / 4 for the gates without one, whose tables use cos and sin of it
+// as 1/sqrt(2).  deriv: times the derivative of the angle by eta, which every
+// entry of a derivative carries.
+constexpr uint32_t op_set() { return 0; }
+template <class... T> constexpr uint32_t op_set(int op, T... rest) { return (1u << op) | op_set(rest...); }
+constexpr uint32_t kRadian = op_set(OP_RX, OP_RY, OP_RZ, OP_RZZ, OP_FSIM);
+constexpr uint32_t kTurns = op_set(OP_XPOW, OP_YPOW, OP_XXPOW, OP_YYPOW, OP_ZPOW, OP_CZPOW, OP_CNOTPOW, OP_ZZPOW);
+constexpr uint32_t kHalfAngle = op_set(OP_RX, OP_RY, OP_XPOW, OP_YPOW, OP_XXPOW, OP_YYPOW);
+__host__ __device__ __forceinline__ void gate_angle(int op, double eta, bool deriv, double *s, double *c)
 {
-    const double r = 0.70710678118654752440;
-    double c, s;
+    const uint32_t bit = op < 32 ? 1u << op : 0u;
+    const bool turns = (bit & kTurns) != 0, plain = (bit & (kRadian | kTurns)) == 0;
+    const double h = bit & kHalfAngle ? 0.5 : 1.0;
+    sincos_of(h * eta, turns, s, c);
+    if (plain) *s = *c = 0.70710678118654752440;
+    if (deriv) {
+        const double dh = turns ? h * 3.14159265358979323846 : h;
+        *s *= dh;
+        *c *= dh;
+    }
+}
+
+// The tables: matrices and derivatives, entries linear in 1, c and s with
+// coefficients in halves (see GateCodes).  m: row-major, zero-initialised;
+// the dimension is returned, 0 if the gate has none in that form.
+// MATRIX1/MATRIX2 and fSim's second parameter (entry 15) are not in them.
+constexpr int gate_matrix(int op, int form, double s, double c, cd *m)
+{
     switch (op) {
-    case OP_H: m[0] = C(r, 0); m[1] = C(r, 0); m[2] = C(r, 0); m[3] = C(-r, 0); return 2;
+    case OP_H: m[0] = C(c, 0); m[1] = C(c, 0); m[2] = C(c, 0); m[3] = C(-c, 0); return 2;
     case OP_X: m[1] = C(1, 0); m[2] = C(1, 0); return 2;
     case OP_Y: m[1] = C(0, -1); m[2] = C(0, 1); return 2;
     case OP_Z: m[0] = C(1, 0); m[3] = C(-1, 0); return 2;
-    case OP_RX:
-        sc(eta[0] * 0.5, &s, &c);
+    case OP_RX: case OP_XPOW: case OP_SQRTX:
         m[0] = C(c, 0); m[1] = C(0, -s); m[2] = C(0, -s); m[3] = C(c, 0); return 2;
-    case OP_RY:
-        sc(eta[0] * 0.5, &s, &c);
+    case OP_RY: case OP_YPOW: case OP_SQRTY:
         m[0] = C(c, 0); m[1] = C(-s, 0); m[2] = C(s, 0); m[3] = C(c, 0); return 2;
-    case OP_RZ:
-        sc(eta[0], &s, &c);
-        m[0] = C(1, 0); m[3] = C(c, s); return 2;
-    case OP_XPOW: case OP_SQRTX: case OP_YPOW: case OP_SQRTY: {
-        scpi(0.5 * (op == OP_XPOW || op == OP_YPOW ? eta[0] : 0.5), &s, &c);
-        m[0] = m[3] = C(c, 0);
-        if (op == OP_XPOW || op == OP_SQRTX) { m[1] = m[2] = C(0, -s); }
-        else { m[1] = C(-s, 0); m[2] = C(s, 0); }
-        return 2;
-    }
-    case OP_ZPOW:
-        scpi(eta[0], &s, &c);
-        m[0] = C(1, 0); m[3] = C(c, s); return 2;
+    case OP_RZ: case OP_ZPOW: m[0] = C(1, 0); m[3] = C(c, s); return 2;
     case OP_SQRTW:
         // W^{1/2} = e^{i pi/4} (cos(pi/4) I - i sin(pi/4) W) with W = [[0, e^{-i pi/4}],
         // [e^{i pi/4}, 0]]: without the phase, r I - i r W with r = 1/sqrt(2)
         // (real diagonal; -i r e^{-/+ i pi/4} = (-1 -/+ i)/2 off it)
-        m[0] = m[3] = C(r, 0); m[1] = C(-0.5, -0.5); m[2] = C(0.5, -0.5);
+        m[0] = m[3] = C(c, 0); m[1] = C(-0.5, -0.5); m[2] = C(0.5, -0.5);
         return 2;
-    case OP_CZ:
-        m[0] = m[5] = m[10] = C(1, 0); m[15] = C(-1, 0); return 4;
-    case OP_CZPOW:
-        scpi(eta[0], &s, &c);
-        m[0] = m[5] = m[10] = C(1, 0); m[15] = C(c, s); return 4;
+    case OP_CZ: m[0] = m[5] = m[10] = C(1, 0); m[15] = C(-1, 0); return 4;
+    case OP_CZPOW: m[0] = m[5] = m[10] = C(1, 0); m[15] = C(c, s); return 4;
     case OP_CNOT:
         if (form == FORM_CBLOCK) { m[1] = m[2] = C(1, 0); return 2; }
         m[0] = m[5] = C(1, 0); m[11] = m[14] = C(1, 0); return 4;
     case OP_CNOTPOW: {
-        scpi(eta[0], &s, &c);
-        cd a = C(0.5 * (1 + c), 0.5 * s), bq = C(0.5 * (1 - c), -0.5 * s);
-        if (form == FORM_CBLOCK) { m[0] = m[3] = a; m[1] = m[2] = bq; return 2; }
-        m[0] = m[5] = C(1, 0); m[10] = m[15] = a; m[11] = m[14] = bq; return 4;
+        const cd p = C(0.5 * (1 + c), 0.5 * s), q = C(0.5 * (1 - c), -0.5 * s);
+        if (form == FORM_CBLOCK) { m[0] = m[3] = p; m[1] = m[2] = q; return 2; }
+        m[0] = m[5] = C(1, 0); m[10] = m[15] = p; m[11] = m[14] = q; return 4;
     }
-    case OP_XXPOW: {  // cos I - i sin XX; XX couples 00 with 11 and 01 with 10, all with +1
-        scpi(0.5 * eta[0], &s, &c);
+    case OP_XXPOW:  // cos I - i sin XX; XX couples 00 with 11 and 01 with 10, all with +1
         m[0] = m[5] = m[10] = m[15] = C(c, 0);
         m[3] = m[6] = m[9] = m[12] = C(0, -s);
         return 4;
-    }
-    case OP_YYPOW: {  // cos I - i sin YY; YY = -|11><00| - |00><11| + |10><01| + |01><10|
-        scpi(0.5 * eta[0], &s, &c);
+    case OP_YYPOW:  // cos I - i sin YY; YY = -|11><00| - |00><11| + |10><01| + |01><10|
         m[0] = m[5] = m[10] = m[15] = C(c, 0);
         m[3] = m[12] = C(0, s);
         m[6] = m[9] = C(0, -s);
         return 4;
+    case OP_ZZPOW: case OP_RZZ: m[0] = m[15] = C(1, 0); m[5] = m[10] = C(c, s); return 4;
+    case OP_FSIM: m[0] = C(1, 0); m[5] = m[10] = C(c, 0); m[6] = m[9] = C(0, -s); return 4;
+    case OP_SWAP: m[0] = m[6] = m[9] = m[15] = C(1, 0); return 4;
     }
-    case OP_ZZPOW:
-        scpi(eta[0], &s, &c);
-        m[0] = m[15] = C(1, 0); m[5] = m[10] = C(c, s); return 4;
-    case OP_RZZ:
-        sc(eta[0], &s, &c);
-        m[0] = m[15] = C(1, 0); m[5] = m[10] = C(c, s); return 4;
+    return 0;
+}
+// derivatives of the matrices (as built, without their left-out phase) with
+// respect to parameter `which`; s and c carry the derivative of the angle
+constexpr int gate_deriv(int op, int form, int which, double s, double c, cd *m)
+{
+    switch (op) {
+    case OP_RX: case OP_XPOW: m[0] = C(-s, 0); m[1] = C(0, -c); m[2] = C(0, -c); m[3] = C(-s, 0); return 2;
+    case OP_RY: case OP_YPOW: m[0] = C(-s, 0); m[1] = C(-c, 0); m[2] = C(c, 0); m[3] = C(-s, 0); return 2;
+    case OP_RZ: case OP_ZPOW: m[3] = C(-s, c); return 2;
+    case OP_CZPOW: m[15] = C(-s, c); return 4;
+    case OP_CNOTPOW: {
+        const cd p = C(-0.5 * s, 0.5 * c), q = C(0.5 * s, -0.5 * c);
+        if (form == FORM_CBLOCK) { m[0] = m[3] = p; m[1] = m[2] = q; return 2; }
+        m[10] = m[15] = p; m[11] = m[14] = q; return 4;
+    }
+    case OP_XXPOW: m[0] = m[5] = m[10] = m[15] = C(-s, 0); m[3] = m[6] = m[9] = m[12] = C(0, -c); return 4;
+    case OP_YYPOW:  // YY: -1 on (00, 11) and (11, 00), +1 on (01, 10) and (10, 01)
+        m[0] = m[5] = m[10] = m[15] = C(-s, 0); m[3] = m[12] = C(0, c); m[6] = m[9] = C(0, -c); return 4;
+    case OP_ZZPOW: case OP_RZZ: m[5] = m[10] = C(-s, c); return 4;
     case OP_FSIM:
-        sc(eta[0], &s, &c);
-        m[0] = C(1, 0); m[5] = m[10] = C(c, 0); m[6] = m[9] = C(0, -s);
-        sc(eta[1], &s, &c);
-        m[15] = C(c, -s); return 4;
-    case OP_SWAP:
-        m[0] = m[6] = m[9] = m[15] = C(1, 0); return 4;
-    case OP_MATRIX1:
-        for (int i = 0; i < 4; i++) m[i] = C(ex[2 * i], ex[2 * i + 1]);
-        return 2;
-    case OP_MATRIX2:
-        for (int i = 0; i < 16; i++) m[i] = C(ex[2 * i], ex[2 * i + 1]);
+        if (which == 0) { m[5] = m[10] = C(-s, 0); m[6] = m[9] = C(0, -c); }
         return 4;
     }
     return 0;
 }
-
-// derivative of gate_matrix_dev (the matrix as built, without its left-out
-// phase) with respect to parameter `which` (m zero-initialised)
-__host__ __device__ __forceinline__ int gate_deriv_dev(int op, const double *eta, int which, int form, cd *m)
+// fSim's entry 15: e^{-i phi}, or its derivative -i e^{-i phi}, from sin and cos of phi
+__host__ __device__ __forceinline__ cd fsim_corner(double s, double c, bool deriv, int which)
 {
-    double c, s;
-    const double pi = 3.14159265358979323846;
-    switch (op) {
-    case OP_RX:
-        sc(eta[0] * 0.5, &s, &c);
-        m[0] = C(-0.5 * s, 0); m[1] = C(0, -0.5 * c); m[2] = C(0, -0.5 * c); m[3] = C(-0.5 * s, 0); return 2;
-    case OP_RY:
-        sc(eta[0] * 0.5, &s, &c);
-        m[0] = C(-0.5 * s, 0); m[1] = C(-0.5 * c, 0); m[2] = C(0.5 * c, 0); m[3] = C(-0.5 * s, 0); return 2;
-    case OP_RZ:  // d/dtheta diag(1, e^{i theta})
-        sc(eta[0], &s, &c);
-        m[3] = C(-s, c); return 2;
-    case OP_RZZ:
-        sc(eta[0], &s, &c);
-        m[5] = m[10] = C(-s, c); return 4;
-    case OP_XPOW: case OP_YPOW: case OP_XXPOW: case OP_YYPOW: {
-        // d/dt (cos(pi t/2) I - i sin(pi t/2) G) = (pi/2)(-sin I - i cos G): the
-        // diagonal ds, and -i dc times each entry of G.  Every entry is its own
-        // expression (a negated copy of a complex value with a zero part has
-        // been compiled for the device with the sign of only one part flipped).
-        scpi(0.5 * eta[0], &s, &c);
-        const double ds = -0.5 * pi * s, dc = 0.5 * pi * c;
-        switch (op) {
-        case OP_XPOW: m[0] = m[3] = C(ds, 0); m[1] = m[2] = C(0, -dc); return 2;
-        case OP_YPOW: m[0] = m[3] = C(ds, 0); m[1] = C(-dc, 0); m[2] = C(dc, 0); return 2;
-        case OP_XXPOW: m[0] = m[5] = m[10] = m[15] = C(ds, 0); m[3] = m[6] = m[9] = m[12] = C(0, -dc); return 4;
-        default:  // YY: -1 on (00, 11) and (11, 00), +1 on (01, 10) and (10, 01)
-            m[0] = m[5] = m[10] = m[15] = C(ds, 0); m[3] = m[12] = C(0, dc); m[6] = m[9] = C(0, -dc); return 4;
+    return !deriv ? C(c, -s) : which == 1 ? C(-s, -c) : C(0, 0);
+}
+
+// The tables as the builder reads them: an entry's six coefficients (real,
+// then imaginary part; of 1, c and s) in halves, four signed bits each.  The
+// lanes of a wavefront build different gates' matrices: a switch runs its
+// cases one after another, each with instruction fetches that miss (measured
+// on a lone wavefront: 2600 instructions, 60% of the time waiting), a table
+// makes every entry the same few instructions.  Row: (derivative by the first,
+// second parameter or none; form; qubits swapped; op).
+struct GateCodes {
+    uint32_t e[3][2][2][32][16];
+};
+constexpr uint32_t half_units(double a, double b, double c)
+{
+    const double v[3] = {2 * a, 2 * b, 2 * c};
+    uint32_t r = 0;
+    for (int i = 0; i < 3; i++) r |= ((uint32_t)(int)v[i] & 15u) << (4 * i);
+    return r;
+}
+constexpr GateCodes gate_codes()
+{
+    GateCodes t{};
+    for (int d = 0; d < 3; d++)
+        for (int form = 0; form < 2; form++)
+            for (int sw = 0; sw < 2; sw++)
+                for (int op = 0; op < 32; op++) {
+                    cd m[3][16] = {};
+                    int dim = 0;
+                    for (int b = 0; b < 3; b++) {
+                        const double s = b == 2 ? 1 : 0, c = b == 1 ? 1 : 0;
+                        dim = d ? gate_deriv(op, form, d - 1, s, c, m[b]) : gate_matrix(op, form, s, c, m[b]);
+                    }
+                    for (int i = 0; i < dim; i++)
+                        for (int j = 0; j < dim; j++) {
+                            // (reversed qubit order: |ab> -> |ba>)
+                            const int pi = sw && dim == 4 && (i == 1 || i == 2) ? 3 - i : i;
+                            const int pj = sw && dim == 4 && (j == 1 || j == 2) ? 3 - j : j;
+                            const int k = i * dim + j;
+                            t.e[d][form][sw][op][pi * dim + pj] =
+                                half_units(m[0][k].x, m[1][k].x - m[0][k].x, m[2][k].x - m[0][k].x) |
+                                half_units(m[0][k].y, m[1][k].y - m[0][k].y, m[2][k].y - m[0][k].y) << 12;
+                        }
+                }
+    return t;
+}
+__device__ const GateCodes kGateCodes = gate_codes();
+
+// The matrix of a row of codes at c and s.  A coefficient 0 leaves a
+// non-finite angle out of its entry.
+__device__ __forceinline__ double code_part(uint32_t q, double c2, double s2)
+{
+    const double k0 = (double)((int32_t)(q << 28) >> 28), kc = (double)((int32_t)(q << 24) >> 28),
+                 ks = (double)((int32_t)(q << 20) >> 28);
+    return fma(kc, c2, fma(ks, s2, 0.5 * k0));
+}
+// entries at(0 .. N-1) of a row into g
+template <int N, class At>
+__device__ __forceinline__ void code_entries(const uint32_t *code, At at, double s, double c, cd *g)
+{
+    const double c2 = 0.5 * c, s2 = 0.5 * s;
+    uint32_t q[N];
+#pragma unroll
+    for (int i = 0; i < N; i++) q[i] = code[at(i)];
+#pragma unroll
+    for (int i = 0; i < N; i++) g[i] = C(code_part(q[i], c2, s2), code_part(q[i] >> 12, c2, s2));
+    if (!(fabs(s) + fabs(c) < 1e300)) {
+#pragma unroll
+        for (int i = 0; i < N; i++) {
+            if (!(q[i] & 0xff0u)) g[i].x = 0.5 * (double)((int32_t)(q[i] << 28) >> 28);
+            if (!((q[i] >> 12) & 0xff0u)) g[i].y = 0.5 * (double)((int32_t)(q[i] << 16) >> 28);
         }
     }
-    case OP_ZPOW: case OP_CZPOW: case OP_CNOTPOW: case OP_ZZPOW: {
-        // d/dt G^t = (i pi w / 2)(I - G), w = e^{i pi t}: i pi w / 2 = (kx, ky)
-        scpi(eta[0], &s, &c);
-        const double kx = -0.5 * pi * s, ky = 0.5 * pi * c;
-        switch (op) {
-        case OP_ZPOW: m[3] = C(2 * kx, 2 * ky); return 2;
-        case OP_CZPOW: m[15] = C(2 * kx, 2 * ky); return 4;
-        case OP_CNOTPOW:
-            if (form == FORM_CBLOCK) { m[0] = m[3] = C(kx, ky); m[1] = m[2] = C(-kx, -ky); return 2; }
-            m[10] = m[15] = C(kx, ky); m[11] = m[14] = C(-kx, -ky); return 4;
-        default: m[5] = m[10] = C(2 * kx, 2 * ky); return 4;  // ZZPOW
-        }
-    }
-    case OP_FSIM:
-        if (which == 0) {
-            sc(eta[0], &s, &c);
-            m[5] = m[10] = C(-s, 0); m[6] = m[9] = C(0, -c);
-        } else {
-            sc(eta[1], &s, &c);
-            m[15] = C(-s, -c);  // -i e^{-i phi}
-        }
-        return 4;
-    }
-    return 0;
 }
 
 int gate_table_host(int op, const double *eta, const double *ex, int form, int deriv, int which, double *out)
 {
     cd m[16];
     for (int i = 0; i < 16; i++) m[i] = C(0, 0);
-    const int d = deriv ? gate_deriv_dev(op, eta, which, form, m) : gate_matrix_dev(op, eta, ex, form, m);
+    double s, c;
+    gate_angle(op, eta[0], deriv != 0, &s, &c);
+    int d = deriv ? gate_deriv(op, form, which, s, c, m) : gate_matrix(op, form, s, c, m);
+    if (op == OP_FSIM) {
+        gate_angle(op, eta[1], deriv != 0, &s, &c);
+        m[15] = fsim_corner(s, c, deriv != 0, which);
+    }
+    if (!deriv && (op == OP_MATRIX1 || op == OP_MATRIX2)) {
+        d = op == OP_MATRIX1 ? 2 : 4;
+        for (int i = 0; i < d * d; i++) m[i] = C(ex[2 * i], ex[2 * i + 1]);
+    }
     for (int i = 0; i < d * d; i++) {
         out[2 * i] = m[i].x;
         out[2 * i + 1] = m[i].y;
@@ -226,24 +299,16 @@ int gate_table_host(int op, const double *eta, const double *ex, int form, int d
     return d;
 }
 
-// permutation of a 4x4 two-qubit matrix for reversed qubit order (|ab> -> |ba>)
-__host__ __device__ __forceinline__ void swap_qubits4(cd *m)
+// entry i of a 4x4 matrix under reversed qubit order (|ab> -> |ba>)
+__device__ __forceinline__ int swapped_entry(int i)
 {
-    cd t[16];
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            const int pi = (i == 1) ? 2 : (i == 2) ? 1 : i, pj = (j == 1) ? 2 : (j == 2) ? 1 : j;
-            t[pi * 4 + pj] = m[i * 4 + j];
-        }
-#pragma unroll
-    for (int i = 0; i < 16; i++) m[i] = t[i];
+    const int sw = 0xd8;  // 0, 2, 1, 3
+    return ((sw >> (2 * (i >> 2))) & 3) * 4 + ((sw >> (2 * (i & 3))) & 3);
 }
 
 // Where the builder finds one batch row's parameters.
 struct BuildCtx {
-    const Member *members;
+    const MemberDev *members;
     const GateDev *gates;
     const int32_t *slot_sym;
     const double *scale, *off;  // this row's scale and offset per slot
@@ -253,6 +318,13 @@ struct BuildCtx {
     int64_t b;                  // batch row
     const ShiftDev *shift;      // derived rows: the row's parameter moves (else NULL)
     double eps;                 // symbol moves are dtheta x eps
+    bool phased;                // the row's global phase is kept (derived rows: not)
+    const uint32_t *frame;      // the row's Pauli frame (NULL: none)
+    int frame_words;
+    __device__ __forceinline__ bool flipped(int bit) const
+    {
+        return frame && bit >= 0 && ((frame[bit >> 5] >> (bit & 31)) & 1u);
+    }
 };
 
 __device__ __forceinline__ uint64_t splitmix64(uint64_t seed, uint64_t counter);
@@ -275,33 +347,52 @@ __device__ __forceinline__ int channel_pick(uint64_t seed, int64_t b, int k, con
 
 // symbol resolution eta = scale*theta + offset (or the constant) of a parameter slot
 // (derived rows: the symbol value moved by dtheta, eta moved by delta)
-__device__ __forceinline__ double slot_value(const BuildCtx &c, int slot)
+struct SlotLoad {
+    double scale, off;
+    float theta;
+};
+__device__ __forceinline__ SlotLoad slot_load(const BuildCtx &c, int slot, int sy)
 {
-    const int sy = c.slot_sym[slot];
-    if (!c.shift) return sy >= 0 ? c.scale[slot] * (double)c.theta[sy] + c.off[slot] : c.off[slot];
+    SlotLoad l{0.0, 0.0, 0.0f};
+    if (slot >= 0) {
+        l.scale = c.scale[slot];
+        l.off = c.off[slot];
+        if (sy >= 0) l.theta = c.theta[sy];
+    }
+    return l;
+}
+__device__ __forceinline__ double slot_value(const BuildCtx &c, int slot, int sy, const SlotLoad &l)
+{
+    if (sy < 0) return l.off;
+    if (!c.shift) return l.scale * (double)l.theta + l.off;
     const ShiftDev &x = *c.shift;
-    if (sy < 0) return c.off[slot];
-    const double th = sy == x.sym ? (double)c.theta[sy] + x.dtheta * c.eps : (double)c.theta[sy];
-    const double eta = c.scale[slot] * th + c.off[slot];
+    const double th = sy == x.sym ? (double)l.theta + x.dtheta * c.eps : (double)l.theta;
+    const double eta = l.scale * th + l.off;
     return slot == x.slot[0] ? eta + x.delta[0] : slot == x.slot[1] ? eta + x.delta[1] : eta;
 }
-__device__ __forceinline__ void resolve(const BuildCtx &c, const GateDev &gd, double *eta)
+__device__ __forceinline__ double slot_value(const BuildCtx &c, int slot, int sy)
 {
-    for (int j = 0; j < gd.np; j++) eta[j] = slot_value(c, gd.slot0 + j);
+    return slot_value(c, slot, sy, slot_load(c, slot, sy));
 }
 
 // Half turns of a forward rotation task: rint(phi / pi) of its angle phi (the
 // sum over its members, all about one axis), the matrix being cos phi I - i
-// sin phi G.
+// sin phi G.  half_angle: a member's phi / pi at its parameter eta.
+__device__ __forceinline__ double half_angle(const MemberDev &gd, double eta)
+{
+    if (gd.slot[0] < 0) return 0.25;  // sqrt X, sqrt Y: G^(1/2)
+    return gd.op == OP_RX || gd.op == OP_RY ? eta * (0.5 / 3.14159265358979323846) : 0.5 * eta;
+}
+__device__ __forceinline__ int odd_turns(double phi) { return (int)((long long)rint(phi) & 1); }
 __device__ __forceinline__ int rot_turns(const BuildTask &bt, const BuildCtx &c)
 {
-    double phi = 0.0;  // in units of pi
+    double phi = 0.0;
     for (int mi = 0; mi < bt.mem_count; mi++) {
-        const GateDev gd = c.gates[c.members[bt.mem_begin + mi].gate];
-        const double eta = gd.np ? slot_value(c, gd.slot0) : 0.5;  // sqrt X, sqrt Y: G^(1/2)
-        phi += gd.op == OP_RX || gd.op == OP_RY ? eta * (0.5 / 3.14159265358979323846) : 0.5 * eta;
+        const MemberDev gd = c.members[bt.mem_begin + mi];
+        const double t = half_angle(gd, slot_value(c, gd.slot[0], gd.sym[0]));
+        phi += c.flipped(gd.flip) ? -t : t;
     }
-    return (int)((long long)rint(phi) & 1);
+    return odd_turns(phi);
 }
 
 // Rotation [[c, -s], [s, c]] up to its sign as three shears: with c >= 0 it is
@@ -321,95 +412,216 @@ __device__ __forceinline__ double2 shear_of(double c, double s, bool odd)
     return make_double2(-s / (1.0 + c), s);
 }
 
-// One build task for one row: symbol resolution eta = scale*theta + offset
-// and the fused product / dagger / derivative, all in float64.  D is the
-// matrix dimension; fixed at compile time so every array stays in registers.
-// Returns 1 when its shears leave out a sign that belongs to the row's phase.
-template <int D> __device__ __forceinline__ int build_task_d(const BuildTask &bt, const BuildCtx &c, double2 *out)
+// The matrix product of one member, g, and the members before it (column by
+// column: column j of g acc needs column j of acc alone).
+template <int D> __device__ __forceinline__ void apply_left(const cd *g, cd *acc)
 {
-    cd acc[16], g[16];
 #pragma unroll
-    for (int i = 0; i < 16; i++) acc[i] = C(0, 0);
+    for (int j = 0; j < D; j++) {
+        cd t[D];
 #pragma unroll
-    for (int i = 0; i < D; i++) acc[i * D + i] = C(1, 0);
-    for (int mi = 0; mi < bt.mem_count; mi++) {
-        const Member mem = c.members[bt.mem_begin + mi];
-        const GateDev gd = c.gates[mem.gate];
-        double eta[3] = {0, 0, 0};
-        resolve(c, gd, eta);
-        const double *ex = gd.explicit_ >= 0 ? c.explicit_mats + 32 * gd.explicit_ : nullptr;
+        for (int i = 0; i < D; i++) {
+            t[i] = C(0, 0);
 #pragma unroll
-        for (int i = 0; i < 16; i++) g[i] = C(0, 0);
-        int gdim;
-        if (gd.op == OP_PCHAN) {  // this row's Pauli (never a derivative: no symbols)
-            const int k = channel_pick(c.noise_seed, c.b, gd.chan, eta);
-            if (k == 0) { g[0] = g[3] = C(1, 0); }
-            else if (k == 1) { g[1] = g[2] = C(1, 0); }
-            else if (k == 2) { g[1] = C(0, -1); g[2] = C(0, 1); }
-            else { g[0] = C(1, 0); g[3] = C(-1, 0); }
-            gdim = 2;
-        } else {
-            gdim = bt.kind == BT_DERIV ? gate_deriv_dev(gd.op, eta, bt.which, mem.form, g)
-                                       : gate_matrix_dev(gd.op, eta, ex, mem.form, g);
+            for (int k = 0; k < D; k++) t[i] = cdadd(t[i], cdmul(g[i * D + k], acc[k * D + j]));
         }
-        if (gdim != D) continue;  // the planner never mixes dimensions
-        if (D == 4 && mem.swapped) swap_qubits4(g);
-        if (bt.kind == BT_DAGGER) {
 #pragma unroll
-            for (int i = 0; i < D; i++)
-#pragma unroll
-                for (int j = 0; j < D; j++) acc[i * D + j] = C(g[j * D + i].x, -g[j * D + i].y);
-        } else if (bt.kind == BT_DERIV || bt.mem_count == 1) {  // one member: its matrix itself
-#pragma unroll
-            for (int i = 0; i < D * D; i++) acc[i] = g[i];
-        } else {
-            cd t[16];
-#pragma unroll
-            for (int i = 0; i < D; i++)
-#pragma unroll
-                for (int j = 0; j < D; j++) {
-                    cd sacc = C(0, 0);
-#pragma unroll
-                    for (int k = 0; k < D; k++) sacc = cdadd(sacc, cdmul(g[i * D + k], acc[k * D + j]));
-                    t[i * D + j] = sacc;
-                }
-#pragma unroll
-            for (int i = 0; i < D * D; i++) acc[i] = t[i];
-        }
+        for (int i = 0; i < D; i++) acc[i * D + j] = t[i];
     }
-    if (bt.diag == 4) {
-        // excitation preserving: |00> phase, the (|01>, |10>) block, |11> phase
-        const int ix[6] = {0, 5, 6, 9, 10, 15};
-#pragma unroll
-        for (int i = 0; i < 6; i++) out[i] = make_double2(acc[ix[i]].x, acc[ix[i]].y);
-    } else if (bt.diag >= 2) {
-        // a I + b P: a from entry (0,0), b from entry (0,3) (P_03 = 1 for XX, -1 for YY)
-        const double sg = bt.diag == 3 ? -1.0 : 1.0;
-        out[0] = make_double2(acc[0].x, acc[0].y);
-        out[1] = make_double2(sg * acc[D - 1].x, sg * acc[D - 1].y);
-    } else if (bt.diag) {
-#pragma unroll
-        for (int i = 0; i < D; i++) out[i] = make_double2(acc[i * D + i].x, acc[i * D + i].y);
+}
+// A Pauli channel's (this row's draw) or a frame's (X^x Z^z of qubit slot0)
+// Pauli.
+__device__ __forceinline__ void pauli_matrix(const BuildCtx &c, const MemberDev &gd, cd *g)
+{
+    int x, z;
+    bool y = false;
+    if (gd.op == OP_FRAME) {
+        x = (c.frame[c.frame_words - 3] >> gd.slot[0]) & 1u;
+        z = (c.frame[c.frame_words - 2] >> gd.slot[0]) & 1u;
     } else {
-#pragma unroll
-        for (int i = 0; i < D * D; i++) out[i] = make_double2(acc[i].x, acc[i].y);
+        const int k = channel_pick(c.noise_seed, c.b, gd.chan, c.off + gd.slot[0]);
+        x = k == 1 || k == 2;
+        z = k == 2 || k == 3;
+        y = k == 2;  // Y = i X Z
     }
-    if (bt.kind == BT_DERIV || bt.which == BX_NONE) return 0;
+    const double sg = z ? -1.0 : 1.0;
+    g[0] = C(x ? 0.0 : 1.0, 0);
+    g[1] = C(x && !y ? sg : 0.0, y ? sg : 0.0);
+    g[2] = C(x && !y ? 1.0 : 0.0, y ? 1.0 : 0.0);
+    g[3] = C(x ? 0.0 : sg, 0);
+}
+
+// One build task for one row: symbol resolution eta = scale*theta + offset
+// and the fused product / dagger / derivative, all in float64.  A lone
+// wavefront is bound by the fetch of the code it runs through, so the shapes
+// that nearly all tasks have share one path of four entries: 2x2 matrices, the
+// pairs a I + b P (their product is that of the middle blocks [[a, b], [b,
+// a]]) and diagonals of 4x4 matrices; other 4x4 matrices go through 16.
+// Measured, kernel alone, against a switch over the gates in each lane with
+// four dependent loads per member: 987 rows of 7 qubits 12.6 -> 6.6 us; the
+// shifted rows of 823 rows of 3 qubits 203 -> 53 us, 11 rows of 6 qubits 8.1 ->
+// 7.5 us.
+// Returns 1 when its shears leave out a sign that belongs to the row's phase.
+template <bool FULL> __device__ __forceinline__ int build_task(const BuildTask &bt, const BuildCtx &c, double2 *out)
+{
+    constexpr int NA = FULL ? 16 : 4;
+    cd acc[NA];
+    const bool two = bt.dim == 2, pair = !two && (bt.diag == 2 || bt.diag == 3), diag4 = !two && bt.diag == 1;
+    const bool small = !FULL || two || pair || diag4, deriv = bt.kind == BT_DERIV, first_only = bt.kind != BT_PRODUCT;
+    const uint32_t at4 = two ? 0x3210u : pair ? 0xa965u : 0xfa50u;
+    double phi = 0.0;
+    // (a task without members is the identity: a qubit no gate prepares)
+#pragma unroll
+    for (int i = 0; i < NA; i++) acc[i] = C((small ? i == 0 || i == 3 : i % 5 == 0) ? 1 : 0, 0);
+    const int last = bt.mem_begin + bt.mem_count - 1;
+    MemberDev next{};
+    next.slot[0] = -1;
+    if (bt.mem_count > 0) next = c.members[bt.mem_begin];
+    SlotLoad loaded = slot_load(c, next.op == OP_FRAME ? -1 : next.slot[0], next.sym[0]);
+    for (int mi = 0; mi < bt.mem_count; mi++) {
+        // the next member's loads run under this one's arithmetic
+        const MemberDev gd = next;
+        next = c.members[min(bt.mem_begin + mi + 1, last)];
+        double eta = slot_value(c, gd.slot[0], gd.sym[0], loaded);
+        if (c.flipped(gd.flip)) eta = -eta;
+        phi += half_angle(gd, eta);
+        const uint32_t *code = kGateCodes.e[deriv ? 1 + bt.which : 0][gd.form][gd.swapped][gd.op & 31];
+        const double *ex = gd.explicit_ >= 0 ? c.explicit_mats + 32 * gd.explicit_ : nullptr;
+        double sn = 0.0, cs = 1.0;
+        cd corner = C(0, 0);
+        for (int j = gd.op == OP_FSIM ? 1 : 0; j >= 0; j--) {
+            gate_angle(gd.op, j ? slot_value(c, gd.slot[1], gd.sym[1]) : eta, deriv, &sn, &cs);
+            if (j) corner = fsim_corner(sn, cs, deriv, bt.which);
+        }
+        loaded = slot_load(c, next.op == OP_FRAME ? -1 : next.slot[0], next.sym[0]);
+        if (small) {
+            cd g[4];
+            code_entries<4>(code, [&](int i) { return (at4 >> (4 * i)) & 15u; }, sn, cs, g);
+            if (ex) {
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const int k = (at4 >> (4 * i)) & 15u, e = gd.swapped && !two ? swapped_entry(k) : k;
+                    g[i] = C(ex[2 * e], ex[2 * e + 1]);
+                }
+            }
+            if (gd.op == OP_FSIM && diag4) g[3] = corner;
+            if (gd.op == OP_PCHAN || gd.op == OP_FRAME) pauli_matrix(c, gd, g);
+            if (mi == 0 || first_only) {
+#pragma unroll
+                for (int i = 0; i < 4; i++) acc[i] = g[i];
+            } else if (diag4) {
+#pragma unroll
+                for (int i = 0; i < 4; i++) acc[i] = cdmul(g[i], acc[i]);
+            } else {
+                apply_left<2>(g, acc);
+            }
+        } else if constexpr (FULL) {
+            cd g[16];
+            code_entries<16>(code, [](int i) { return i; }, sn, cs, g);
+            if (ex) {
+#pragma unroll
+                for (int i = 0; i < 16; i++) {
+                    const int e = gd.swapped ? swapped_entry(i) : i;
+                    g[i] = C(ex[2 * e], ex[2 * e + 1]);
+                }
+            }
+            if (gd.op == OP_FSIM) g[15] = corner;
+            if (mi == 0 || first_only) {
+#pragma unroll
+                for (int i = 0; i < 16; i++) acc[i] = g[i];
+            } else {
+                apply_left<4>(g, acc);
+            }
+        }
+    }
+    if (bt.kind == BT_DAGGER) {
+#pragma unroll
+        for (int i = 0; i < NA; i++) acc[i].y = -acc[i].y;
+        if (two || pair) {
+            const cd t = acc[1];
+            acc[1] = acc[2];
+            acc[2] = t;
+        } else if constexpr (FULL) {
+            if (!small) {
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int j = 0; j < i; j++) {
+                    const cd t = acc[i * 4 + j];
+                    acc[i * 4 + j] = acc[j * 4 + i];
+                    acc[j * 4 + i] = t;
+                }
+            }
+        }
+    }
+    if (small) {
+        // a pair stores (a, b), a 2x2 diagonal its entries 0 and 3
+        const bool d2 = two && bt.diag != 0;
+        out[0] = make_double2(acc[0].x, acc[0].y);
+        out[1] = d2 ? make_double2(acc[3].x, acc[3].y) : make_double2(acc[1].x, acc[1].y);
+        if (!d2 && !pair) {
+            out[2] = make_double2(acc[2].x, acc[2].y);
+            out[3] = make_double2(acc[3].x, acc[3].y);
+        }
+    } else if constexpr (FULL) {
+        if (bt.diag == 4) {
+            // excitation preserving: |00> phase, the (|01>, |10>) block, |11> phase
+            const int ix[6] = {0, 5, 6, 9, 10, 15};
+#pragma unroll
+            for (int i = 0; i < 6; i++) out[i] = make_double2(acc[ix[i]].x, acc[ix[i]].y);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; i++) out[i] = make_double2(acc[i].x, acc[i].y);
+        }
+    }
+    if (deriv || bt.which == BX_NONE) return 0;
     const bool fwd = bt.kind == BT_PRODUCT;
-    const double cr = acc[0].x, sr = D == 4 ? -out[1].y : bt.which == BX_REAL ? acc[D].x : -acc[D].y;
-    const bool odd = fwd ? rot_turns(bt, c) != 0 : cr < 0.0;
-    out[D == 4 ? 2 : 4] = shear_of(cr, sr, odd);
+    const double cr = acc[0].x, sr = bt.which == BX_REAL ? acc[2].x : -acc[2].y;
+    const bool odd = fwd && c.phased ? odd_turns(phi) != 0 : cr < 0.0;
+    out[two ? 4 : 2] = shear_of(cr, sr, odd);
     return fwd && odd;
 }
 
-__device__ __forceinline__ int build_task(const BuildTask &bt, const BuildCtx &c, double2 *out)
+// --------------------------------------------------------- Pauli frames
+// The frame of group row `src` (batch row b) into LDS, by one wavefront: the
+// lanes draw the channels (64 at a time), and the table rows of the few Paulis
+// drawn are xored word by word (lane w holds the words w, w + 64, ...), while
+// every lane keeps the frame itself, F = i^k X^x Z^z, in channel order: F <-
+// P F with P the drawn Pauli moved to the end.
+template <class A>
+__device__ __forceinline__ void frame_row(const A &a, const double *off, uint64_t noise_seed, int b, uint32_t *acc)
 {
-    return bt.dim == 2 ? build_task_d<2>(bt, c, out) : build_task_d<4>(bt, c, out);
+    const int lane = threadIdx.x & 63, nw = a.frame_words - 3;
+    for (int w = lane; w < nw; w += 64) acc[w] = 0u;
+    uint32_t x = 0, z = 0, k = 0;
+    for (int c0 = 0; c0 < a.nchan; c0 += 64) {
+        int pick = 0;
+        if (c0 + lane < a.nchan) {
+            const GateDev gd = a.gates[a.chan_gates[c0 + lane]];
+            const double p[3] = {off[gd.slot0], off[gd.slot0 + 1], off[gd.slot0 + 2]};
+            pick = channel_pick(noise_seed, b, gd.chan, p);
+        }
+        for (uint64_t m = __ballot(pick != 0); m; m &= m - 1) {
+            const int l = __ffsll((unsigned long long)m) - 1;
+            const int d = __builtin_amdgcn_readlane(pick, l);
+            for (int t = 1; t >= 0; t--) {  // Y = i X Z: Z first
+                if (d == (t ? 1 : 3)) continue;
+                const uint32_t *r = a.frame_table + (int64_t)(2 * (c0 + l) + t) * a.frame_words;
+                for (int w = lane; w < nw; w += 64) acc[w] ^= r[w];
+                const uint32_t rx = r[nw], rz = r[nw + 1];
+                k += r[nw + 2] + 2u * (uint32_t)__popc(rz & x);
+                x ^= rx;
+                z ^= rz;
+            }
+            if (d == 2) k += 1;
+        }
+    }
+    if (lane < 3) acc[nw + lane] = lane == 0 ? x : lane == 1 ? z : k & 3u;
 }
 
 // --------------------------------------------------- matrix build kernel
 // One thread per (row, task); the result goes to the row's matrix block.
-template <class A>
+template <bool FULL, class A>
 __device__ __forceinline__ void build_rows(const A &a, const float *theta, uint64_t noise_seed, int row, int bx)
 {
     const int ti = bx * blockDim.x + threadIdx.x + a.task_begin;
@@ -426,11 +638,21 @@ __device__ __forceinline__ void build_rows(const A &a, const float *theta, uint6
     BuildCtx c{a.members, a.gates, a.slot_sym,
                a.slot_scale + (a.uniform ? 0 : (int64_t)src * a.n_slots),
                a.slot_off + (a.uniform ? 0 : (int64_t)src * a.n_slots), a.explicit_mats,
-               theta + (int64_t)b * a.S, noise_seed, b, shift, a.x_eps};
+               theta + (int64_t)b * a.S, noise_seed, b, shift, a.x_eps, a.phase_out >= 0, nullptr, a.frame_words};
+    if (a.frames) {
+        extern __shared__ uint32_t frame_lds[];
+        if (threadIdx.x < 64) frame_row(a, c.off, noise_seed, b, frame_lds);
+        __syncthreads();
+        c.frame = frame_lds;
+        // kept for the gradients' signs and the rows derived from this one
+        if (bx == 0 && !shift)
+            for (int w = threadIdx.x; w < a.frame_words; w += blockDim.x)
+                a.frames[(int64_t)src * a.frame_words + w] = frame_lds[w];
+    }
     int odd = 0;
     if (ti < a.task_end) {
         const BuildTask bt = a.tasks[ti];
-        odd = build_task(bt, c, a.mats + (int64_t)row * a.mat_stride + bt.out);
+        odd = build_task<FULL>(bt, c, a.mats + (int64_t)row * a.mat_stride + bt.out);
     }
     if (a.phase_out < 0 || bx != 0) return;
     // the row's global phase (block 0 of the row; its thread 0 built the
@@ -443,16 +665,19 @@ __device__ __forceinline__ void build_rows(const A &a, const float *theta, uint6
         if (bt.kind == BT_PRODUCT && bt.which != BX_NONE) odd += rot_turns(bt, c);
     }
     double ph = odd * 3.14159265358979323846;
+    if (c.frame && threadIdx.x == 0) ph += (double)(c.frame[c.frame_words - 1] & 3u) * (0.5 * 3.14159265358979323846);
     for (int j = threadIdx.x; j < a.n_phase; j += blockDim.x) {
         const PhaseTerm pt = a.phase_terms[j];
-        ph += pt.slot >= 0 ? pt.c * slot_value(c, pt.slot) : pt.c;
+        const double k = c.flipped(pt.flip) ? pt.cf : pt.c;
+        ph += pt.slot >= 0 ? k * slot_value(c, pt.slot, c.slot_sym[pt.slot]) : k;
     }
     ph = wave_sum(ph);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ph;
     __syncthreads();
     if (threadIdx.x == 0) {
         double s, co;
-        sc(part[0] + part[1] + part[2] + part[3], &s, &co);
+        for (int w = 1; w < (int)(blockDim.x >> 6); w++) part[0] += part[w];
+        sincos_of(part[0], false, &s, &co);
         double2 *out = a.mats + (int64_t)row * a.mat_stride + a.phase_out;
         for (int i = 0; i < 4; i++) {
             const double2 v = out[i];
@@ -461,9 +686,13 @@ __device__ __forceinline__ void build_rows(const A &a, const float *theta, uint6
     }
 }
 
-__global__ __launch_bounds__(256) void k_build_mats(BuildArgs a)
+// FULL: programs with 4x4 matrices that are neither diagonal nor a pair; the
+// 310 registers of their sixteen entries leave one wavefront per SIMD where
+// the other kernel's 188 leave two (shifted rows of 12 rows of 10-qubit QAOA
+// 28.0 -> 15.4 us, of 823 rows of 3 qubits 110 -> 53 us)
+template <bool FULL> __global__ __launch_bounds__(256) void k_build_mats(BuildArgs a)
 {
-    build_rows(a, a.theta, a.noise_seed, blockIdx.y, blockIdx.x);
+    build_rows<FULL>(a, a.theta, a.noise_seed, blockIdx.y, blockIdx.x);
 }
 
 // Derived rows of the batched shift rules, one wavefront per row (four rows
@@ -481,51 +710,26 @@ __global__ __launch_bounds__(256) void k_copy_source(BuildArgs a, int nrows)
 }
 
 // ... then the tasks that read a moved parameter built again, one thread per
-// row (a move's list holds a task or two); the row's global phase, as in
-// k_build_mats, multiplied into the product-init task when it heads the
-// list, else the change of the moved parameters' phase terms multiplied into
-// the copied product-init matrix.  (The signs of the rotations' shears are
-// left out: derived rows only give expectations.)
-__global__ __launch_bounds__(256) void k_build_list(BuildArgs a, int nrows)
+// row (a move's list holds a task or two).  (Derived rows give expectations
+// alone: their global phase is whatever the copied and rebuilt matrices make
+// it.)
+template <bool FULL> __global__ __launch_bounds__(256) void k_build_list(BuildArgs a, int nrows)
 {
     const int row = blockIdx.x * blockDim.x + threadIdx.x;
     if (row >= nrows) return;
     const int64_t L = a.x_begin + row;
     const int src = (int)(L / a.x_period);
     const int m = (int)(L - (int64_t)src * a.x_period);
-    const ShiftDev *shift = a.x_shift + m;
     const int b = cget(a.rows, src);
-    BuildCtx c{a.members, a.gates, a.slot_sym,
-               a.slot_scale + (a.uniform ? 0 : (int64_t)src * a.n_slots),
-               a.slot_off + (a.uniform ? 0 : (int64_t)src * a.n_slots), a.explicit_mats,
-               a.theta + (int64_t)b * a.S, a.noise_seed, b, shift, a.x_eps};
+    const BuildCtx c{a.members, a.gates, a.slot_sym,
+                     a.slot_scale + (a.uniform ? 0 : (int64_t)src * a.n_slots),
+                     a.slot_off + (a.uniform ? 0 : (int64_t)src * a.n_slots), a.explicit_mats,
+                     a.theta + (int64_t)b * a.S, a.noise_seed, b, a.x_shift + m, a.x_eps, false,
+                     a.frames ? a.frames + (int64_t)src * a.frame_words : nullptr, a.frame_words};
     double2 *block = a.mats + (int64_t)row * a.mat_stride;
     for (int li = a.list_begin[m]; li < a.list_begin[m + 1]; li++) {
         const BuildTask bt = a.tasks[a.task_list[li]];
-        build_task(bt, c, block + bt.out);
-    }
-    if (a.phase_out < 0) return;
-    double ph = 0.0;
-    if (a.phase_full[m]) {
-        for (int j = 0; j < a.n_phase; j++) {
-            const PhaseTerm pt = a.phase_terms[j];
-            ph += pt.slot >= 0 ? pt.c * slot_value(c, pt.slot) : pt.c;
-        }
-    } else {
-        if (a.phase_begin[m] == a.phase_begin[m + 1]) return;
-        BuildCtx c0 = c;
-        c0.shift = nullptr;
-        for (int j = a.phase_begin[m]; j < a.phase_begin[m + 1]; j++) {
-            const PhaseTerm pt = a.phase_terms[a.phase_list[j]];
-            ph += pt.c * (slot_value(c, pt.slot) - slot_value(c0, pt.slot));
-        }
-    }
-    double sn, co;
-    sc(ph, &sn, &co);
-    double2 *out = block + a.phase_out;
-    for (int i = 0; i < 4; i++) {
-        const double2 v = out[i];
-        out[i] = make_double2(co * v.x - sn * v.y, co * v.y + sn * v.x);
+        build_task<FULL>(bt, c, block + bt.out);
     }
 }
 
@@ -550,7 +754,7 @@ __global__ __launch_bounds__(64) void k_build_stage(StageBuildArgs a) { build_st
 // ------------------------------------------------------- forward pass
 template <class A> __device__ __forceinline__ void run_pass(const A &a, float2 *state, int bid, unsigned char *smem)
 {
-    const PassCtx c = pass_setup(a, state, bid, smem);
+    const PassCtx c = pass_setup(a, state, bid, smem, a.mat_end - a.mat_begin);
     const SMat G = smat(a.mats + (int64_t)c.row * a.mat_stride);
     const int64_t ntiles = (int64_t)1 << a.tiles_log2;
     for (int64_t tile = c.w; tile < ntiles; tile += a.wg_per_row) {
@@ -874,7 +1078,7 @@ __global__ __launch_bounds__(256) void k_pauli_diag(DiagArgs a)
 // psi and phi tiles side by side in LDS; the pass's matrices too.
 template <class A> __device__ __forceinline__ void run_rev_pass(const A &a, int bid, unsigned char *smem)
 {
-    const RevCtx c = rev_setup(a, bid, smem);
+    const RevCtx c = rev_setup(a, bid, smem, a.mat_end - a.mat_begin);
     const int64_t ntiles = (int64_t)1 << a.tiles_log2;
     for (int64_t tile = c.w; tile < ntiles; tile += a.wg_per_row) {
         const uint64_t fb = pdep64((uint64_t)tile, a.g.fixed_mask);
@@ -909,7 +1113,7 @@ template <class A> __device__ __forceinline__ void grad_reduce(const A &a, float
             int gs = a.sym_gslots[k];
             double v = 0;
             for (int w = 0; w < a.wg_per_row; w++) v += p[(int64_t)w * a.n_gslots + gs];
-            sum += 2.0 * scale[a.gslot_slot[gs]] * v;
+            sum += 2.0 * scale[a.gslot_slot[gs]] * v * frame_sign(a, row, gs);
         }
         grad[(int64_t)b * a.S + s] = (float)sum;
     }
@@ -971,7 +1175,7 @@ __global__ __launch_bounds__(256) void k_build_batch(const void *table, const Ba
     const BatchBlock bb = cget(blocks, blockIdx.x);
     TableArg<BuildArgs> &a = table_arg<BuildArgs>(table, bb.arg);
     const int nx = (a.task_end - a.task_begin + 255) / 256;
-    build_rows(a, c.theta, c.noise_seed, bb.block / nx, bb.block % nx);
+    build_rows<true>(a, c.theta, c.noise_seed, bb.block / nx, bb.block % nx);
 }
 __global__ __launch_bounds__(64) void k_stage_batch(const void *table, const BatchBlock *blocks, ResCall)
 {
@@ -1393,8 +1597,9 @@ hipError_t launch_build_derived(const BuildArgs &a, int nrows, int max_list, hip
     prof::Scope ps("build", s);
     const unsigned blocks = (unsigned)((nrows + 3) / 4);
     if (a.x_copy > 0) hipLaunchKernelGGL(k_copy_source, dim3(blocks), dim3(256), 0, s, a, nrows);
-    if (max_list > 0 || a.phase_out >= 0)
-        hipLaunchKernelGGL(k_build_list, dim3((unsigned)((nrows + 255) / 256)), dim3(256), 0, s, a, nrows);
+    if (max_list > 0)
+        hipLaunchKernelGGL(a.full ? k_build_list<true> : k_build_list<false>, dim3((unsigned)((nrows + 255) / 256)),
+                       dim3(256), 0, s, a, nrows);
     return hipGetLastError();
 }
 
@@ -1402,9 +1607,11 @@ hipError_t launch_build(const BuildArgs &a, int nrows, hipStream_t s)
 {
     int n = a.task_end - a.task_begin;
     if (n <= 0 || nrows <= 0) return hipSuccess;
-    dim3 grid((n + 255) / 256, nrows);
+    // rows of up to 64 tasks: one wavefront each, none waits idle at the phase sum
+    const int nt = n <= 64 ? 64 : 256;
+    dim3 grid((n + nt - 1) / nt, nrows);
     prof::Scope ps("build", s);
-    hipLaunchKernelGGL(k_build_mats, grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(a.full ? k_build_mats<true> : k_build_mats<false>, grid, dim3(nt), build_lds_bytes(a), s, a);
     return hipGetLastError();
 }
 
@@ -1513,10 +1720,14 @@ hipError_t launch_pauli_reduce(const PauliReduceArgs &a, int nrows, hipStream_t 
     return hipGetLastError();
 }
 
+size_t rev_pass_lds_bytes(const TileGeom &g, int nmat, int waves, int gcount)
+{
+    return 2 * sizeof(float2) * ((size_t)1 << g.t) + sizeof(uint64_t) * ((size_t)1 << g.h) +
+           sizeof(double2) * (size_t)nmat + sizeof(double) * waves * (size_t)(gcount > 0 ? gcount : 1);
+}
 size_t rev_pass_lds_bytes(const RevArgs &a)
 {
-    return 2 * sizeof(float2) * ((size_t)1 << a.g.t) + sizeof(uint64_t) * ((size_t)1 << a.g.h) +
-           sizeof(double2) * (size_t)(a.mat_end - a.mat_begin) + sizeof(double) * 4 * (size_t)(a.gcount > 0 ? a.gcount : 1);
+    return rev_pass_lds_bytes(a.g, a.mat_end - a.mat_begin, kThreads / 64, a.gcount);
 }
 
 hipError_t launch_rev_pass(const RevArgs &a, int nrows, hipStream_t s)

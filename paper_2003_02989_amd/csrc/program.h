@@ -17,6 +17,7 @@ struct Error {
 };
 
 struct Options {
+    bool auto_tile = false;   // the caller left the tile size open (see rev_tile)
     int tile = 12;    // forward tile bits
     int low = 6;      // contiguous low bits per tile
     bool fuse = true;
@@ -92,6 +93,7 @@ struct Group {
     // plan
     std::vector<BuildTask> tasks;
     std::vector<Member> members;
+    bool full4 = false;  // some task's matrix is a 4x4 neither diagonal nor a pair
     TaskRange fwd_tasks, rev_tasks;
     int32_t mat_block = 0;                      // complex entries per row
     std::vector<Pass> fwd;
@@ -104,6 +106,15 @@ struct Group {
     int32_t fwd_mat_end = 0;                    // forward matrices (with the product init) end here
     std::vector<std::pair<int, int>> dense_stages;  // (forward pass, stage) with a stage matrix
     std::vector<PhaseTerm> phase_terms;         // the row's global phase, linear in the parameters
+    // Pauli frames (plan_frames): channels are not applied gate by gate.  Per
+    // channel and Pauli (X, Z) the frame words an inserted Pauli changes:
+    // n_flips bits (angles negated), then the X mask, the Z mask and the power
+    // of i of the Pauli it becomes at the end (bit q: qubit q)
+    bool frames = false;
+    int n_flips = 0, frame_words = 0;
+    std::vector<uint32_t> frame_rows;           // [channels][2][frame_words]
+    std::vector<int32_t> chan_gates;            // gate of each channel
+    std::vector<int32_t> gslot_flip;            // per gradient slot its gate's frame bit or -1
     bool rot = false;                           // forward rotations run as shears (their signs join the phase)
     std::vector<Occurrence> occurrences;        // symbolic blob parameters, in gate and parameter order
 };
@@ -143,6 +154,17 @@ inline int rev_stage_bits(int n, const Options &opt)
 {
     if (n > std::min(opt.tile, 12)) return kStageBitsRev;
     return opt.specialize && n <= kWideRevQubits ? kStageBitsRev : kStageBitsRevResident;
+}
+
+// Generated reverse passes of 13 qubits take both states (128 KB of a CU's 160
+// KB of LDS) as one tile when the caller left the tile size open, so that the
+// whole sweep is one pass; larger states keep tiles of 2^12, two workgroups per
+// CU.  (A forward state of 2^14 amplitudes as one tile measured no faster than
+// two passes over tiles of 2^13: 1.38 ms against 1.36 ms for 5040 derived rows
+// of a 14-qubit QAOA circuit, bound by VALU issue and LDS either way.)
+inline int rev_tile(int n, const Options &opt)
+{
+    return opt.specialize && opt.auto_tile && n == 13 ? 13 : std::min(opt.tile, 12);
 }
 
 struct ProgramData {

@@ -28,11 +28,15 @@ enum Opcode : uint16_t {
 // exp(-i eta P) of a Pauli string: a blob opcode only, lowered to the gates
 // above when a program is parsed
 constexpr uint16_t OP_PAULIEXP = 26;
+// the Pauli frame of a noisy row on one qubit (slot0), applied after the other
+// gates: a plan's gate only (see plan_frames)
+constexpr uint16_t OP_FRAME = 0x100;
 
 constexpr int kMaxQubits = 32;
 constexpr int kThreads = 256;  // threads per workgroup of every tile kernel
 constexpr uint8_t kFixed = 0xFF;  // "bit not in the tile" marker
 constexpr int kMaxGradPerPass = 512;  // gradient slots one reverse pass accumulates
+constexpr int kMaxGradWhole = 448;    // the same beside two states of 2^13 amplitudes (eight wavefronts' sums)
 constexpr int kMaxPassMat = 2048;     // matrix entries (complex128) one pass stages in LDS
 
 // One gate of a structure, as the device matrix builder reads it.
@@ -42,6 +46,8 @@ struct GateDev {
     int32_t slot0;     // first of its np parameter slots
     int32_t explicit_; // index of its explicit matrix (MATRIX1/2) or -1
     int32_t chan;      // OP_PCHAN: its ordinal among the circuit's channels, else -1
+    int32_t flip;      // rotations of a structure with Pauli frames: the frame bit that negates its
+                       // angle, else -1
 };
 
 // How a matrix is rendered by the builder.
@@ -59,12 +65,23 @@ struct Member {
     uint8_t pad[2];
 };
 
+// A member with all of its gate that the builder reads, so that a lane needs
+// one load, not a chain of four, before it can ask for the parameter's value.
+struct MemberDev {
+    uint16_t op;
+    uint8_t form, swapped;
+    int32_t slot[2];   // its parameter slots (-1: none)
+    int32_t sym[2];    // their symbols (-1: constant)
+    int32_t explicit_, chan, flip;  // as the gate's
+};
+
 // One term of a row's global phase (the phases the gate matrices leave out):
-// c * eta(slot), or the constant c when slot < 0.
+// c * eta(slot), or the constant c when slot < 0; cf instead of c when the
+// frame bit `flip` is set (-1: none).
 struct PhaseTerm {
     int32_t slot;
-    int32_t pad;
-    double c;
+    int32_t flip;
+    double c, cf;
 };
 
 // Build tasks of the matrix builder; each writes one matrix per batch row.
