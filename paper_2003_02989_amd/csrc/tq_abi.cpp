@@ -1351,16 +1351,23 @@ void ensure_batch(tq_program p, BatchPlan &bp, int mode, int K)
 // kernels takes merged launches.
 bool batches(tq_program p) { return !p->pd->opt.specialize && p->pd->groups.size() > 1; }
 
-// The merged launches of a mode (recorded on first use, and those of the
-// simpler modes with them, so that a captured call finds them ready).
-const BatchPlan &batch_plan(tq_program p, int mode, int K)
+// The merged launches of a mode, recorded on first use together with those of
+// the simpler modes.  nullptr: run group by group; so also while the stream is
+// captured and the mode is not yet recorded, since recording allocates and
+// uploads, which a capture does not take, and the groups of resident circuits
+// need neither.
+const BatchPlan *batch_plan(tq_program p, int mode, int K, hipStream_t s)
 {
+    if (!batches(p)) return nullptr;
+    BatchPlan &want = mode == BM_STATE ? p->state_batch : mode == BM_EXP ? p->obs_batch->exp : p->obs_batch->adj;
+    if (want.ready) return &want;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    hip_check(hipStreamIsCapturing(s, &st), "hipStreamIsCapturing");
+    if (st != hipStreamCaptureStatusNone) return nullptr;
     ensure_batch(p, p->state_batch, BM_STATE, 0);
-    if (mode == BM_STATE) return p->state_batch;
-    ensure_batch(p, p->obs_batch->exp, BM_EXP, K);
-    if (mode == BM_EXP) return p->obs_batch->exp;
-    ensure_batch(p, p->obs_batch->adj, BM_ADJ, K);
-    return p->obs_batch->adj;
+    if (mode != BM_STATE) ensure_batch(p, p->obs_batch->exp, BM_EXP, K);
+    if (mode == BM_ADJ) ensure_batch(p, p->obs_batch->adj, BM_ADJ, K);
+    return &want;
 }
 
 void run_batch(tq_program p, const BatchPlan &bp, ResCall c, hipStream_t s)
@@ -1379,7 +1386,8 @@ void run_batch(tq_program p, const BatchPlan &bp, ResCall c, hipStream_t s)
 void expectations_all(tq_program prog, const float *theta, const ObsData &od, float *out, hipStream_t s)
 {
     ensure_obs(prog, od);
-    const BatchPlan *bp = batches(prog) && od.K > 0 ? &batch_plan(prog, BM_EXP, od.K) : nullptr;
+    psi_ws(prog);  // (also when no group needs it: a later call may be captured, and takes no allocation then)
+    const BatchPlan *bp = od.K > 0 ? batch_plan(prog, BM_EXP, od.K, s) : nullptr;
     if (bp) {
         ResCall c{};
         c.theta = theta;
@@ -1905,7 +1913,7 @@ tq_status tq_simulate_state(tq_program prog, const float *theta, void *states, v
         check_align(theta, 4, "symbol_values");
         ensure_device(prog);
         hipStream_t s = as_stream(stream);
-        const BatchPlan *bp = batches(prog) ? &batch_plan(prog, BM_STATE, 0) : nullptr;
+        const BatchPlan *bp = batch_plan(prog, BM_STATE, 0, s);
         if (bp) {
             ResCall c{};
             c.theta = theta;
@@ -1949,9 +1957,10 @@ tq_status tq_adjoint_grad(tq_program prog, const float *theta, tq_observables ob
         check_align(expectations, 4, "expectations");
         ensure_device(prog);
         ensure_obs(prog, *obs->od);
+        psi_ws(prog);  // (as in expectations_all)
         hipStream_t s = as_stream(stream);
         const int K = obs->od->K;
-        const BatchPlan *bp = batches(prog) && K > 0 && pd.S > 0 ? &batch_plan(prog, BM_ADJ, K) : nullptr;
+        const BatchPlan *bp = K > 0 && pd.S > 0 ? batch_plan(prog, BM_ADJ, K, s) : nullptr;
         if (bp) {
             ResCall c{};
             c.theta = theta;

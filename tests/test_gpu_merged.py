@@ -94,3 +94,23 @@ def test_observable_sets_in_turn_and_capture():
         got = (g.clone(), e.clone())
         eager = tq.adjoint_grad(p, th, o, up), tq.expectation(p, th, o)
         assert torch.equal(got[0], eager[0]) and torch.equal(got[1], eager[1])
+
+
+def test_first_gradient_inside_a_capture():
+    # the observables' tables are there from an expectation call, the
+    # gradient's merged launches are not: the groups run one by one
+    w = ragged(81, [2, 5, 7, 3])
+    p = tq.Program(w.program_blob(), specialize=False)
+    o, th, up = tq.Observables(w.observable_blob()), dev(w.theta), dev(w.upstream)
+    g = torch.empty((w.B, w.n_symbols), dtype=torch.float32, device="cuda")
+    tq.expectation(p, th, o)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        tq.adjoint_grad(p, th, o, up, grad=g)
+    ref = tq.adjoint_grad(p, th, o, up)
+    for _ in range(3):
+        g.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.abs((g - ref).cpu().numpy()).max() <= 1e-4
