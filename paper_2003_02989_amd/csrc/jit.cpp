@@ -1202,12 +1202,49 @@ int resident_threads(const Group &g)
     return std::min(kThreads, std::max(64, 1 << std::max(g.n - kStageBitsRev, 0)));
 }
 
-std::string resident_source(const Group &g)
+namespace {
+
+// The product state of a resident kernel: thread tid's amplitudes share the
+// factors of the index bits that tid holds, so those are multiplied once per
+// thread and the other bits' factors (the same for all lanes) by doubling:
+// 7 + 14 products per thread for 10 qubits and 128 threads, where a product per
+// amplitude and qubit takes 80, each behind a load whose address varies by lane.
+// (10 qubits, 1024 rows, adjoint: 89.8 -> 84.5 us per call; 4 qubits, 16 rows:
+// 22.6 -> 21.7 us.)
+void resident_init(std::ostream &o, const Group &g, int nt)
+{
+    const int n = g.n, lb = std::min(n, (int)__builtin_ctz((unsigned)nt)), hb = n - lb;
+    o << "    for (int j = tid; j < " << nt / 64 << " * a.nacc; j += " << nt << ") acc[j] = 0;\n"
+         "    " << (1 << n < nt ? "if (tid < " + N(1 << n) + ") " : std::string()) << "{\n"
+         "        double2 w[" << (1 << hb) << "];\n        w[0] = make_double2(1.0, 0.0);\n";
+    for (int j = 0; j < lb; j++) {  // index bit j: qubit n - 1 - j
+        const int m = g.init_mat[n - 1 - j];
+        const std::string f = "zsel((tid >> " + N(j) + ") & 1, M[" + N(m) + "], M[" + N(m + 2) + "])";
+        o << "        w[0] = " << (j ? "zmul(w[0], " + f + ")" : f) << ";\n";
+    }
+    for (int j = 0; j < hb; j++) {
+        const int m = g.init_mat[n - 1 - lb - j];
+        for (int k = (1 << j) - 1; k >= 0; k--)
+            o << "        w[" << k + (1 << j) << "] = zmul(w[" << k << "], M[" << m + 2 << "]); w[" << k << "] = zmul(w["
+              << k << "], M[" << m << "]);\n";
+    }
+    for (int k = 0; k < (1 << hb); k++) o << "        lp[sw(tid + " << k * nt << "u)] = down2(w[" << k << "]);\n";
+    o << "    }\n    __syncthreads();\n";
+}
+
+// A resident kernel: the whole computation (tq_resident_spec), or without the
+// gradient part (tq_resident_fwd).  Two kernels, because the reverse stages
+// hold two states in registers: the whole one takes 122 (four wavefronts per
+// SIMD) on the 10-qubit classifier, forward stages alone 67 (seven), and calls
+// of many rows are bound by latency.  Shift rule of 256 rows: 740 -> 487 us per
+// call, the product state (resident_init) included.
+std::string resident_kernel(const Group &g, bool grad)
 {
     std::ostringstream o;
     const int n = g.n, nt = resident_threads(g);
-    o << kHead
-      << "extern \"C\" __global__ __launch_bounds__(" << nt << ") void tq_resident_spec(ResArgs a)\n{\n"
+    o << kHead << "extern \"C\" __global__ __launch_bounds__(" << nt << ") void "
+      << (grad ? "tq_resident_spec" : "tq_resident_fwd")
+      << "(ResArgs a)\n{\n"
          "    extern __shared__ __align__(16) unsigned char smem[];\n"
          "    double *acc = reinterpret_cast<double *>(smem);\n"
          "    float2 *lp = reinterpret_cast<float2 *>(acc + 4 * a.nacc);\n"
@@ -1216,9 +1253,13 @@ std::string resident_source(const Group &g)
       << "u;\n"
          "    const SMat M = smat(a.mats + (int64_t)blockIdx.x * a.mat_stride);\n"
          "    const int tid = threadIdx.x;\n"
-         "    resident_begin(a, M, acc, lp, tid, " << nt << ");\n";
+         "    ResCall c{};\n"
+         "    c.state_out = a.state_out;\n"
+         "    c.exp_out = a.exp_out;\n"
+      << (grad ? "    c.upstream = a.upstream;\n    c.grad = a.grad;\n" : "");
+    resident_init(o, g, nt);
     Env e{n, 0, "M", false, "a.nacc", "a.gacc"};
-    e.pin = false;  // two waves per SIMD: registers to spare, latency to hide
+    e.pin = false;  // few waves per SIMD with the reverse stages: registers to spare, latency to hide
     e.nt = nt;
     e.grp = &g;
     e.fgrp = &g;
@@ -1227,18 +1268,18 @@ std::string resident_source(const Group &g)
         for (size_t si = 0; si < ps.stages.size(); si++)
             forward_stage(o, e, ps, ps.stages[si], si + 1 == ps.stages.size() ? scale : "");
     }
-    o << "    resident_middle(a, a, acc, lp, lf, blockIdx.x, tid, " << nt << ");\n"
-         "    if (a.grad) {\n";
-    for (const Pass &ps : g.rev)
-        for (const Stage &st : ps.stages) reverse_stage(o, e, ps, st);
-    o << "    }\n"
-         "    resident_end(a, a, acc, blockIdx.x, tid, " << nt << ");\n"
+    o << "    resident_middle(a, c, acc, lp, lf, blockIdx.x, tid, " << nt << ");\n";
+    if (grad) {
+        o << "    if (a.grad) {\n";
+        for (const Pass &ps : g.rev)
+            for (const Stage &st : ps.stages) reverse_stage(o, e, ps, st);
+        o << "    }\n";
+    }
+    o << "    resident_end(a, c, acc, blockIdx.x, tid, " << nt << ");\n"
          "}\n"
          "} // namespace tq\n";
     return o.str();
 }
-
-namespace {
 
 // Workgroups of the generated reverse passes: 256 threads, 512 for tiles whose
 // LDS leaves room for one workgroup on a CU (two states of 2^13 amplitudes), so
@@ -2303,7 +2344,18 @@ hipError_t launch_resident_spec(const Group &g, const ResArgs &a, int nrows, siz
 {
     if (nrows <= 0) return hipSuccess;
     hipFunction_t fn;
-    hipError_t e = memo_kernel(memo, 0, 1, [&] { return resident_source(g); }, "tq_resident_spec", &fn, log);
+    bool grad = a.grad != nullptr;
+    auto loaded = [&](size_t slot) { return memo && slot < memo->fn.size() && memo->fn[slot]; };
+    if (!grad && !loaded(0) && loaded(1)) {
+        // nothing is compiled or loaded while the stream is captured: the
+        // whole kernel does forward calls too
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        hipError_t e = hipStreamIsCapturing(s, &st);
+        if (e != hipSuccess) return e;
+        grad = st != hipStreamCaptureStatusNone;
+    }
+    hipError_t e = memo_kernel(memo, grad, 2, [&] { return resident_kernel(g, grad); },
+                               grad ? "tq_resident_spec" : "tq_resident_fwd", &fn, log);
     if (e != hipSuccess) return e;
     return launch(fn, a, nrows, lds, s, "resident", resident_threads(g));
 }
@@ -2383,7 +2435,7 @@ hipError_t launch_rev_pass_spec(const Group &g, int pass, const RevArgs &a, int 
 
 hipError_t prepare_spec(const Group &g, bool resident, const char *target, std::string *log)
 {
-    const std::vector<std::string> bodies = resident ? std::vector<std::string>{resident_source(g)} : pass_chunks(g);
+    const std::vector<std::string> bodies = resident ? std::vector<std::string>{resident_kernel(g, false), resident_kernel(g, true)} : pass_chunks(g);
     if (target) {
         std::vector<const std::string *> ptrs;
         for (const std::string &b : bodies) ptrs.push_back(&b);

@@ -21,8 +21,6 @@
 
 namespace tq {
 
-// The specialised resident kernel's source (without the shared device code).
-std::string resident_source(const Group &g);
 // The specialised forward (tq_fwd_<pass>) and reverse (tq_rev_<pass>) tile
 // pass kernels of group g, to be placed in namespace tq after the shared
 // device code (all passes of a group are compiled as one program).

@@ -8,8 +8,10 @@ changes sign or its entries are extreme.  Sizes: resident circuits, states
 of one tile and of several."""
 import numpy as np
 import pytest
+import torch
 
-from gpu_util import compare, gpu_outputs, oracle_outputs, say
+from gpu_util import compare, dev, gpu_outputs, oracle_outputs, say
+from paper_2003_02989_amd import tq
 from paper_2003_02989_amd import workloads as wl
 from paper_2003_02989_amd.circuits import Circuit, sym
 
@@ -83,3 +85,37 @@ def test_rotation_shears_at_special_angles(n):
     obs = wl.random_observables(rng, n, 1, max_terms=6, max_weight=3)
     w = wl.Workload(f"angles_n{n}", [c] * 6, 5, theta, [obs] * 6, np.ones((6, 1), "float32"))
     compare(gpu_outputs(w, specialize=True), oracle_outputs(w))
+
+
+@pytest.mark.parametrize("n", [1, 2, 6, 7, 9, 10, 11, 12])
+def test_resident_sizes(n):
+    # the product state by thread and register bits: fewer amplitudes than
+    # threads, one each, and every count of shared bits; first gates dense
+    rng = wl.rng_for(9500 + n)
+    c = Circuit(n)
+    for q in range(n):
+        c.add("RX", q, [sym(q % 3, 0.5, 0.1 * q)]).add("RZ", q, [sym((q + 1) % 3, 1.0, 0.2)]).add("RY", q, [sym(q % 3)])
+    for q in range(n - 1):
+        c.add("CZ", (q, q + 1)).add("RY", q, [sym(q % 3, -0.7)])
+    obs = wl.random_observables(rng, n, 2, max_terms=5, max_weight=min(n, 3))
+    theta = rng.uniform(-3, 3, size=(3, 3)).astype("float32")
+    w = wl.Workload(f"resident_n{n}", [c] * 3, 3, theta, [obs] * 3, rng.standard_normal((3, 2)).astype("float32"))
+    compare(gpu_outputs(w, specialize=True), oracle_outputs(w))
+
+
+def test_first_forward_call_inside_a_capture():
+    # after a gradient alone nothing forward is loaded: the whole kernel runs
+    w = batch("mixed", 7, 60, 9600)
+    p, o, th = tq.Program(w.program_blob(), specialize=True), tq.Observables(w.observable_blob()), dev(w.theta)
+    tq.adjoint_grad(p, th, o, dev(w.upstream))
+    out = torch.empty((w.B, w.K), dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        tq.expectation(p, th, o, out=out)
+    ref = tq.expectation(p, th, o)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (out - ref).abs().max().item() <= 1e-5
