@@ -1281,10 +1281,6 @@ std::string resident_kernel(const Group &g, bool grad)
     return o.str();
 }
 
-// Workgroups of the generated reverse passes: 256 threads, 512 for tiles whose
-// LDS leaves room for one workgroup on a CU (two states of 2^13 amplitudes), so
-// that eight wavefronts share it as with two workgroups.
-int rev_threads(const TileGeom &gm) { return gm.t > 12 ? 512 : kThreads; }
 // product-init matrices a generated first pass stages (they come first)
 int init_mats(const Pass &ps) { return ps.product_init ? 4 * ps.geom.n : 0; }
 

@@ -1232,7 +1232,7 @@ void plan_group(Group &g, const Options &opt, int S)
     g.fwd_mat_end = g.mat_block;
 
     // reverse passes: every gate, last first, W^dagger and dW/deta per op;
-    // two states share the LDS, so the tile is one bit smaller at most 12
+    // two states share the LDS (see rev_tile)
     g.rev_tasks.begin = (int)g.tasks.size();
     std::vector<int> ritems;
     for (int gi = G - 1; gi >= 0; gi--)
@@ -1252,11 +1252,12 @@ void plan_group(Group &g, const Options &opt, int S)
     for (auto &s0 : rs0) {
         Sched cur;
         cur.bits = s0.bits;
+        const int most = rev_max_grads(geom_from_bits(n, pass_low(s0.bits, crev), s0.bits));
         int ng = 0;
         for (int gi : s0.items) {
             int k = 0;
             for (int j = 0; j < g.gates[gi].np; j++) k += g.slot_sym[g.gates[gi].slot0 + j] >= 0;
-            if (ng + k > (trev > 12 ? kMaxGradWhole : kMaxGradPerPass) && !cur.items.empty()) {
+            if (ng + k > most && !cur.items.empty()) {
                 rs.push_back(cur);
                 cur.items.clear();
                 ng = 0;

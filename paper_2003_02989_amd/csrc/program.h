@@ -166,6 +166,19 @@ inline int rev_tile(int n, const Options &opt)
 {
     return opt.specialize && opt.auto_tile && n == 13 ? 13 : std::min(opt.tile, 12);
 }
+// Workgroups of the generated reverse passes: 256 threads, 512 for tiles whose
+// LDS leaves room for one workgroup on a CU (two states of 2^13 amplitudes), so
+// that eight wavefronts share it as with two workgroups.
+inline int rev_threads(const TileGeom &gm) { return gm.t > 12 ? 512 : kThreads; }
+// Gradient slots one reverse pass over tile gm accumulates: each takes a sum
+// per wavefront in the LDS that a whole-state tile and its offset table leave
+// (384 slots with runs of 2^3 amplitudes, 496 with 2^6).
+inline int rev_max_grads(const TileGeom &gm)
+{
+    if (gm.t <= 12) return kMaxGradPerPass;
+    const int left = kCuLds - 2 * (int)sizeof(float) * 2 * (1 << gm.t) - (int)sizeof(uint64_t) * (1 << gm.h);
+    return std::min(kMaxGradPerPass, left / ((int)sizeof(double) * (rev_threads(gm) / 64)));
+}
 
 struct ProgramData {
     int B = 0, S = 0, nmax = 0;

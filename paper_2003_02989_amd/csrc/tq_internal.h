@@ -36,7 +36,7 @@ constexpr int kMaxQubits = 32;
 constexpr int kThreads = 256;  // threads per workgroup of every tile kernel
 constexpr uint8_t kFixed = 0xFF;  // "bit not in the tile" marker
 constexpr int kMaxGradPerPass = 512;  // gradient slots one reverse pass accumulates
-constexpr int kMaxGradWhole = 448;    // the same beside two states of 2^13 amplitudes (eight wavefronts' sums)
+constexpr int kCuLds = 160 * 1024;    // LDS bytes of a CU, and the most one workgroup can have
 constexpr int kMaxPassMat = 2048;     // matrix entries (complex128) one pass stages in LDS
 
 // One gate of a structure, as the device matrix builder reads it.
