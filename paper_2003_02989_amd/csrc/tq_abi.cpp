@@ -196,7 +196,11 @@ struct BatchRec {
         size_t lds = 0;
     };
     std::map<Key, Bucket> buckets;
-    size_t partial = 0, gpart = 0;  // bytes
+    // a workspace whose regions the launches of all groups use side by side;
+    // largest: what the launches of one group at a time need of it
+    struct Space {
+        size_t total = 0, largest = 0;  // bytes
+    } partial, gpart;
 
     template <class Args> void add(int phase, int index, int kind, const Args &a, int nblocks, size_t lds, int64_t weight,
                                    int p = 0, bool phi = false)
@@ -210,10 +214,11 @@ struct BatchRec {
     }
     // a region of a workspace, as its byte offset (the base is added once
     // the workspace's size is known)
-    static double *region(size_t &total, size_t bytes)
+    static double *region(Space &w, size_t bytes)
     {
-        double *at = reinterpret_cast<double *>(total);
-        total += (bytes + 255) & ~(size_t)255;
+        double *at = reinterpret_cast<double *>(w.total);
+        w.total += (bytes + 255) & ~(size_t)255;
+        w.largest = std::max(w.largest, bytes);
         return at;
     }
 };
@@ -1278,8 +1283,13 @@ void ensure_batch(tq_program p, BatchPlan &bp, int mode, int K)
     }
     bp.release();
     bp.launches.clear();
-    char *partial = rec.partial ? (char *)bp.partial.ensure(rec.partial) : nullptr;
-    char *gpart = rec.gpart ? (char *)bp.gpart.ensure(rec.gpart) : nullptr;
+    char *partial = rec.partial.total ? (char *)bp.partial.ensure(rec.partial.total) : nullptr;
+    char *gpart = rec.gpart.total ? (char *)bp.gpart.ensure(rec.gpart.total) : nullptr;
+    // the groups' own launches take the same sums from the program's
+    // workspaces: a call that runs them later (another observable set, a Z-only
+    // set, no plan yet) may be captured, and takes no allocation then
+    if (rec.partial.largest) p->partial.ensure(rec.partial.largest);
+    if (rec.gpart.largest) p->gpart.ensure(rec.gpart.largest);
     std::vector<char> host;
     auto align = [&] { host.resize((host.size() + 63) & ~(size_t)63); };
     for (auto &kv : rec.buckets) {
