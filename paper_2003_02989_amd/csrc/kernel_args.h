@@ -230,13 +230,14 @@ struct ResCall {
     const float *upstream;
     float *grad;
 };
-// The tail [from, to) of the simulated states of a structure's rows.
+// The tail [from, to) of the simulated states of a structure's rows, cleared
+// by wg_per_row workgroups each.
 struct ZeroArgs {
     int64_t row_stride;
     const int32_t *rows;
     int64_t from, to;
+    int wg_per_row;
 };
-constexpr int kZeroBlock = 4096;  // amplitudes one workgroup clears
 // The steps that merged launches run.
 enum BatchKind { BK_BUILD, BK_STAGE, BK_RESIDENT, BK_PASS, BK_PAULI, BK_PAULI_REDUCE, BK_REV, BK_GRAD_REDUCE, BK_ZERO };
 // One workgroup of a merged launch: its argument block in the table and its

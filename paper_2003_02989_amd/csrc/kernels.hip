@@ -1502,11 +1502,9 @@ __global__ __launch_bounds__(256) void k_zero_batch(const void *table, const Bat
 {
     const BatchBlock bb = cget(blocks, blockIdx.x);
     TableArg<ZeroArgs> &a = table_arg<ZeroArgs>(table, bb.arg);
-    const int nx = (int)((a.to - a.from + kZeroBlock - 1) / kZeroBlock);
-    float2 *st = c.state_out + (int64_t)cget(a.rows, bb.block / nx) * a.row_stride;
-    const int64_t from = a.from + (int64_t)(bb.block % nx) * kZeroBlock;
-    const int64_t to = from + kZeroBlock < a.to ? from + kZeroBlock : a.to;
-    for (int64_t i = from + threadIdx.x; i < to; i += 256) st[i] = make_float2(0.f, 0.f);
+    float2 *st = c.state_out + (int64_t)cget(a.rows, bb.block / a.wg_per_row) * a.row_stride;
+    for (int64_t i = a.from + (bb.block % a.wg_per_row) * 256 + threadIdx.x; i < a.to; i += 256 * a.wg_per_row)
+        st[i] = make_float2(0.f, 0.f);
 }
 
 __global__ void k_zero_tail(float2 *state, int64_t row_stride, const int32_t *rows, int64_t from, int64_t to)

@@ -192,7 +192,8 @@ struct BatchRec {
     };
     struct Bucket {
         std::vector<char> table;
-        std::vector<std::pair<int, int64_t>> args;  // workgroups and weight (heaviest first) of each block
+        std::vector<std::pair<int64_t, int64_t>> args;  // workgroups and weight (heaviest first) of each block
+        int64_t blocks = 0;                             // workgroups in all
         size_t lds = 0;
     };
     std::map<Key, Bucket> buckets;
@@ -202,15 +203,22 @@ struct BatchRec {
         size_t total = 0, largest = 0;  // bytes
     } partial, gpart;
 
-    template <class Args> void add(int phase, int index, int kind, const Args &a, int nblocks, size_t lds, int64_t weight,
-                                   int p = 0, bool phi = false)
+    template <class Args> void add(int phase, int index, int kind, const Args &a, int64_t nblocks, size_t lds,
+                                   int64_t weight, int p = 0, bool phi = false)
     {
         if (nblocks <= 0) return;
         Bucket &b = buckets[Key{phase, index, kind, p, phi}];
         const char *c = reinterpret_cast<const char *>(&a);
         b.table.insert(b.table.end(), c, c + sizeof a);
         b.args.emplace_back(nblocks, weight);
+        b.blocks += nblocks;
         b.lds = std::max(b.lds, lds);
+    }
+    int64_t largest() const  // workgroups of the largest launch
+    {
+        int64_t n = 0;
+        for (auto &kv : buckets) n = std::max(n, kv.second.blocks);
+        return n;
     }
     // a region of a workspace, as its byte offset (the base is added once
     // the workspace's size is known)
@@ -517,7 +525,7 @@ void build_mats(tq_program p, size_t gi, const float *theta, int begin, int end,
         hip_check(launch_build_derived(a, rr.n, rr.max_list, s), "derived matrix build launch");
     } else if (rr.rec) {
         const int nx = (end - begin + kThreads - 1) / kThreads;
-        rr.rec->add(0, 0, BK_BUILD, a, rr.n * nx, build_lds_bytes(a), 0);
+        rr.rec->add(0, 0, BK_BUILD, a, (int64_t)rr.n * nx, build_lds_bytes(a), 0);
     } else {
         hip_check(launch_build(a, rr.n, s), "matrix build launch");
     }
@@ -530,7 +538,7 @@ void build_mats(tq_program p, size_t gi, const float *theta, int begin, int end,
         sb.ops = (const PassOp *)gd.fwd_ops.p;
         sb.mats = a.mats;
         sb.mat_stride = a.mat_stride;
-        if (rr.rec) rr.rec->add(1, 0, BK_STAGE, sb, rr.n * sb.nlist, 0, 0);
+        if (rr.rec) rr.rec->add(1, 0, BK_STAGE, sb, (int64_t)rr.n * sb.nlist, 0, 0);
         else hip_check(launch_build_stage(sb, rr.n, s), "stage matrix build launch");
     }
 }
@@ -569,7 +577,7 @@ void forward(tq_program p, size_t gi, float2 *state, int64_t row_stride, const i
             continue;
         }
         if (rr.rec)
-            rr.rec->add(3, (int)pi, BK_PASS, a, nrows * a.wg_per_row,
+            rr.rec->add(3, (int)pi, BK_PASS, a, (int64_t)nrows * a.wg_per_row,
                         pass_lds_bytes(a.g, a.product_init != 0, a.mat_end - a.mat_begin), a.nstages);
         else hip_check(launch_pass(a, nrows, s), "pass launch");
     }
@@ -954,7 +962,7 @@ void pauli_group(tq_program p, size_t gi, const float2 *psi, float2 *phi, const 
         const size_t bytes = sizeof(double) * (size_t)slots * a.k_count;
         a.partial = rr.rec ? BatchRec::region(rr.rec->partial, bytes) : (double *)p->partial.ensure(bytes);
         if (rr.rec)
-            rr.rec->add(4, k0, BK_PAULI, a, (int)slots, pauli_lds_bytes(a.g, a.k_count, og.partner), 0,
+            rr.rec->add(4, k0, BK_PAULI, a, slots, pauli_lds_bytes(a.g, a.k_count, og.partner), 0,
                         a.g.t <= 8 ? 1 : 1 << (a.g.t - 8), a.phi != nullptr);
         else hip_check(launch_pauli(a, nrows, og.partner, s), "Pauli kernel launch");
         if (out) {
@@ -966,7 +974,7 @@ void pauli_group(tq_program p, size_t gi, const float2 *psi, float2 *phi, const 
             r.k_begin = k0;
             r.k_count = a.k_count;
             r.out = out;
-            if (rr.rec) rr.rec->add(4, k0, BK_PAULI_REDUCE, r, nrows * r.k_count, 0, 0);
+            if (rr.rec) rr.rec->add(4, k0, BK_PAULI_REDUCE, r, (int64_t)nrows * r.k_count, 0, 0);
             else hip_check(launch_pauli_reduce(r, nrows, s), "Pauli reduce launch");
         }
     }
@@ -983,6 +991,17 @@ constexpr size_t kResidentSpecLds = 64 * 1024;
 // merged resident launches of at most this many rows (two per CU) take
 // sixteen wavefronts per row instead of four
 constexpr int64_t kBatchWide = 512;
+// rows of a structure past which its own launches are long enough: two
+// structures of 8 qubits, expectation / gradient merged against one by one, 512
+// rows each 83 / 158 against 133 / 253 us, 2048 rows 260 / 598 against 264 / 618,
+// 4096 rows 469 / 1143 against 462 / 1145, 16384 rows 1635 / 4375 against 1570 /
+// 4230; larger states gain at all their row counts (two states of 24 qubits
+// 1025 / 8845 against 1087 / 12900 us)
+constexpr int64_t kBatchRows = 4096;
+// workgroups of a merged launch, past which the remaining structures launch
+// their own: 32 MB of workgroup list, and blocks x threads below the 2^32 that
+// a launch takes
+constexpr int64_t kBatchBlocks = (int64_t)1 << 22;
 
 bool resident(tq_program p, size_t gi, bool adjoint, int tmax)
 {
@@ -1241,8 +1260,12 @@ void state_group(tq_program prog, size_t gi, const float *theta, float2 *states,
     if (g.n >= pd.nmax) return;
     const int64_t from = (int64_t)1 << g.n;
     if (rr.rec) {
-        const ZeroArgs z{stride, (const int32_t *)gd.rows.p, from, stride};
-        rr.rec->add(8, 0, BK_ZERO, z, rr.n * (int)((stride - from + kZeroBlock - 1) / kZeroBlock), 0, 0);
+        // enough workgroups for the chip over all rows of the program: the
+        // launch's list does not grow with the amplitudes it clears
+        const int64_t most = std::max<int64_t>(1, 8192 / pd.B);
+        const ZeroArgs z{stride, (const int32_t *)gd.rows.p, from, stride,
+                         (int)std::min<int64_t>(most, (stride - from + 4095) / 4096)};
+        rr.rec->add(8, 0, BK_ZERO, z, (int64_t)rr.n * z.wg_per_row, 0, 0);
     } else {
         hip_check(launch_zero_tail(states, stride, (const int32_t *)gd.rows.p, rr.n, from, stride, s), "zero tail launch");
     }
@@ -1255,9 +1278,11 @@ void adjoint_group(tq_program prog, size_t gi, const float *theta, int K, const 
 enum BatchMode { BM_STATE, BM_EXP, BM_ADJ };
 
 // Whether group gi joins the merged launches of a mode: everything but the
-// Z-only expectation kernel of larger states (diag_group).
+// Z-only expectation kernel of larger states (diag_group) and structures of
+// more than kBatchRows rows.
 bool batch_covers(tq_program p, size_t gi, int mode)
 {
+    if ((int64_t)p->pd->groups[gi]->rows.size() > kBatchRows) return false;
     if (mode == BM_STATE) return true;
     const ObsGroupDev &og = *p->obs_dev[gi];
     return resident(p, gi, mode == BM_ADJ, og.tmax) || mode == BM_ADJ || !og.diag;
@@ -1274,6 +1299,7 @@ void ensure_batch(tq_program p, BatchPlan &bp, int mode, int K)
     float *some = reinterpret_cast<float *>(sizeof(float4));
     for (size_t gi = 0; gi < G; gi++) {
         if (!batch_covers(p, gi, mode)) continue;
+        if (rec.largest() >= kBatchBlocks) break;
         covered[gi] = 1;
         RunRows rr = own_rows(p, gi);
         rr.rec = &rec;
@@ -1301,9 +1327,7 @@ void ensure_batch(tq_program p, BatchPlan &bp, int mode, int K)
         l.phi = kv.first.phi;
         l.threads = kThreads;
         l.lds = b.lds;
-        int64_t blocks = 0;
-        for (auto &ar : b.args) blocks += ar.first;
-        if (blocks > ((int64_t)1 << 30)) fail(TQ_E_UNSUPPORTED, "too many workgroups in one launch");
+        const int64_t blocks = b.blocks;
         auto base = [](double *&at, char *b0) { at = reinterpret_cast<double *>(b0 + reinterpret_cast<size_t>(at)); };
         for (size_t i = 0; i < n; i++) {
             char *at = b.table.data() + i * size;
@@ -1341,7 +1365,7 @@ void ensure_batch(tq_program p, BatchPlan &bp, int mode, int K)
         std::vector<BatchBlock> bl;
         bl.reserve((size_t)blocks);
         for (int i : order)
-            for (int k = 0; k < b.args[i].first; k++) bl.push_back(BatchBlock{i, k});
+            for (int64_t k = 0; k < b.args[i].first; k++) bl.push_back(BatchBlock{i, (int)k});
         l.nblocks = (int)bl.size();
         align();
         l.table = host.size();
@@ -1361,11 +1385,11 @@ void ensure_batch(tq_program p, BatchPlan &bp, int mode, int K)
 // kernels takes merged launches.
 bool batches(tq_program p) { return !p->pd->opt.specialize && p->pd->groups.size() > 1; }
 
-// The merged launches of a mode, recorded on first use together with those of
-// the simpler modes.  nullptr: run group by group; so also while the stream is
-// captured and the mode is not yet recorded, since recording allocates and
-// uploads, which a capture does not take, and the groups of resident circuits
-// need neither.
+// The merged launches of a mode, recorded on first use (those of expectations
+// together with a gradient's, for the observable set it trains on).  nullptr:
+// run group by group; so also while the stream is captured and the mode is not
+// yet recorded, since recording allocates and uploads, which a capture does not
+// take.
 const BatchPlan *batch_plan(tq_program p, int mode, int K, hipStream_t s)
 {
     if (!batches(p)) return nullptr;
@@ -1374,9 +1398,8 @@ const BatchPlan *batch_plan(tq_program p, int mode, int K, hipStream_t s)
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     hip_check(hipStreamIsCapturing(s, &st), "hipStreamIsCapturing");
     if (st != hipStreamCaptureStatusNone) return nullptr;
-    ensure_batch(p, p->state_batch, BM_STATE, 0);
-    if (mode != BM_STATE) ensure_batch(p, p->obs_batch->exp, BM_EXP, K);
-    if (mode == BM_ADJ) ensure_batch(p, p->obs_batch->adj, BM_ADJ, K);
+    if (mode == BM_ADJ) ensure_batch(p, p->obs_batch->exp, BM_EXP, K);
+    ensure_batch(p, want, mode, K);
     return &want;
 }
 
@@ -1773,7 +1796,7 @@ void adjoint_group(tq_program prog, size_t gi, const float *theta, int K, const 
             hip_check(e, "specialised reverse pass launch");
             continue;
         }
-        if (rr.rec) rr.rec->add(6, (int)pi, BK_REV, r, nrows * wg, rev_pass_lds_bytes(r), r.nstages);
+        if (rr.rec) rr.rec->add(6, (int)pi, BK_REV, r, (int64_t)nrows * wg, rev_pass_lds_bytes(r), r.nstages);
         else hip_check(launch_rev_pass(r, nrows, s), "reverse pass launch");
     }
     GradReduceArgs gr{};
