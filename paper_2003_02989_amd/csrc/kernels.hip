@@ -364,10 +364,10 @@ __device__ __forceinline__ SlotLoad slot_load(const BuildCtx &c, int slot, int s
 __device__ __forceinline__ double slot_value(const BuildCtx &c, int slot, int sy, const SlotLoad &l)
 {
     if (sy < 0) return l.off;
-    if (!c.shift) return l.scale * (double)l.theta + l.off;
+    if (!c.shift) return fma(l.scale, (double)l.theta, l.off);
     const ShiftDev &x = *c.shift;
-    const double th = sy == x.sym ? (double)l.theta + x.dtheta * c.eps : (double)l.theta;
-    const double eta = l.scale * th + l.off;
+    const double th = sy == x.sym ? fma(x.dtheta, c.eps, (double)l.theta) : (double)l.theta;
+    const double eta = fma(l.scale, th, l.off);
     return slot == x.slot[0] ? eta + x.delta[0] : slot == x.slot[1] ? eta + x.delta[1] : eta;
 }
 __device__ __forceinline__ double slot_value(const BuildCtx &c, int slot, int sy)
@@ -375,22 +375,44 @@ __device__ __forceinline__ double slot_value(const BuildCtx &c, int slot, int sy
     return slot_value(c, slot, sy, slot_load(c, slot, sy));
 }
 
-// Half turns of a forward rotation task: rint(phi / pi) of its angle phi (the
-// sum over its members, all about one axis), the matrix being cos phi I - i
-// sin phi G.  half_angle: a member's phi / pi at its parameter eta.
-__device__ __forceinline__ double half_angle(const MemberDev &gd, double eta)
+// Half turns of a forward rotation task: its angle phi (the sum over its
+// members, all about one axis), the matrix being cos phi I - i sin phi G, in
+// units of pi and modulo 2, so that the sum keeps its parity however large the
+// parameters are.  half_turns: a member's phi / pi at its parameter eta, in
+// [-1, 1].  Where eta / (2 pi) may have lost its fraction it comes from the
+// angle's sine s and cosine c, asin to m^5 within 1e-3 (the shears hold for any
+// cosine well above -1, so the parity may be off near an odd quarter turn).  One
+// lane counts the tasks of other blocks again, so every operation is rounded on
+// its own (no product is left to be contracted into a sum): the two counts are
+// the same bit for bit.
+constexpr double kTurnsExact = 1099511627776.0;  // 2^40
+__device__ __forceinline__ bool far_turned(const MemberDev &gd, double eta)
+{
+    return (gd.op == OP_RX || gd.op == OP_RY) && !(fabs(eta) < kTurnsExact);
+}
+__device__ __forceinline__ double mod2(double t) { return fma(-2.0, rint(0.5 * t), t); }
+__device__ __forceinline__ double half_turns(const MemberDev &gd, double eta, double s, double c)
 {
     if (gd.slot[0] < 0) return 0.25;  // sqrt X, sqrt Y: G^(1/2)
-    return gd.op == OP_RX || gd.op == OP_RY ? eta * (0.5 / 3.14159265358979323846) : 0.5 * eta;
+    if (far_turned(gd, eta)) {
+        const double as = fabs(s), ac = fabs(c), m = fmin(as, ac), z = m * m;
+        const double k = fma(z, fma(z, 0.0239, 0.0531), 0.3183);  // (1 + z / 6 + 3 z^2 / 40) / pi
+        const double q = as > ac ? fma(-m, k, 0.5) : m * k;
+        return copysign(c < 0.0 ? 1.0 - q : q, s);
+    }
+    return mod2(gd.op == OP_RX || gd.op == OP_RY ? eta * (0.5 / 3.14159265358979323846) : 0.5 * eta);
 }
-__device__ __forceinline__ int odd_turns(double phi) { return (int)((long long)rint(phi) & 1); }
+__device__ __forceinline__ int odd_turns(double phi) { return fabs(mod2(phi)) > 0.5; }
 __device__ __forceinline__ int rot_turns(const BuildTask &bt, const BuildCtx &c)
 {
     double phi = 0.0;
     for (int mi = 0; mi < bt.mem_count; mi++) {
         const MemberDev gd = c.members[bt.mem_begin + mi];
-        const double t = half_angle(gd, slot_value(c, gd.slot[0], gd.sym[0]));
-        phi += c.flipped(gd.flip) ? -t : t;
+        double eta = slot_value(c, gd.slot[0], gd.sym[0]);
+        if (c.flipped(gd.flip)) eta = -eta;
+        double sn = 0.0, cs = 1.0;
+        if (far_turned(gd, eta)) gate_angle(gd.op, eta, false, &sn, &cs);
+        phi += half_turns(gd, eta, sn, cs);
     }
     return odd_turns(phi);
 }
@@ -469,6 +491,8 @@ template <bool FULL> __device__ __forceinline__ int build_task(const BuildTask &
     const bool two = bt.dim == 2, pair = !two && (bt.diag == 2 || bt.diag == 3), diag4 = !two && bt.diag == 1;
     const bool small = !FULL || two || pair || diag4, deriv = bt.kind == BT_DERIV, first_only = bt.kind != BT_PRODUCT;
     const uint32_t at4 = two ? 0x3210u : pair ? 0xa965u : 0xfa50u;
+    // (the sign of a phase-keeping row's forward rotation comes from its angle)
+    const bool turns = bt.kind == BT_PRODUCT && bt.which != BX_NONE && c.phased;
     double phi = 0.0;
     // (a task without members is the identity: a qubit no gate prepares)
 #pragma unroll
@@ -484,7 +508,6 @@ template <bool FULL> __device__ __forceinline__ int build_task(const BuildTask &
         next = c.members[min(bt.mem_begin + mi + 1, last)];
         double eta = slot_value(c, gd.slot[0], gd.sym[0], loaded);
         if (c.flipped(gd.flip)) eta = -eta;
-        phi += half_angle(gd, eta);
         const uint32_t *code = kGateCodes.e[deriv ? 1 + bt.which : 0][gd.form][gd.swapped][gd.op & 31];
         const double *ex = gd.explicit_ >= 0 ? c.explicit_mats + 32 * gd.explicit_ : nullptr;
         double sn = 0.0, cs = 1.0;
@@ -493,6 +516,7 @@ template <bool FULL> __device__ __forceinline__ int build_task(const BuildTask &
             gate_angle(gd.op, j ? slot_value(c, gd.slot[1], gd.sym[1]) : eta, deriv, &sn, &cs);
             if (j) corner = fsim_corner(sn, cs, deriv, bt.which);
         }
+        if (turns) phi += half_turns(gd, eta, sn, cs);
         loaded = slot_load(c, next.op == OP_FRAME ? -1 : next.slot[0], next.sym[0]);
         if (small) {
             cd g[4];
@@ -575,11 +599,10 @@ template <bool FULL> __device__ __forceinline__ int build_task(const BuildTask &
         }
     }
     if (deriv || bt.which == BX_NONE) return 0;
-    const bool fwd = bt.kind == BT_PRODUCT;
     const double cr = acc[0].x, sr = bt.which == BX_REAL ? acc[2].x : -acc[2].y;
-    const bool odd = fwd && c.phased ? odd_turns(phi) != 0 : cr < 0.0;
+    const bool odd = turns ? odd_turns(phi) != 0 : cr < 0.0;
     out[two ? 4 : 2] = shear_of(cr, sr, odd);
-    return fwd && odd;
+    return turns && odd;
 }
 
 // --------------------------------------------------------- Pauli frames
