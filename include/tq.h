@@ -341,13 +341,18 @@ tq_status tq_gate_matrix(int32_t op, const double *params, const double *explici
 
 /* The matrix builder's output, for checks: resolves the symbols and builds
  * every matrix of every structure group (forward products, W^dagger and
- * dW/deta of the reverse sweep, dense stage matrices) exactly as a call of
- * tq_adjoint_grad would, then copies each group's row blocks, groups in the
+ * dW/deta of the reverse sweep, dense stage matrices) as a call of
+ * tq_adjoint_grad would, and the row's global phase (in the first qubit's
+ * product-init matrix) as one of tq_simulate_state would, then copies each
+ * group's row blocks, groups in the
  * order of tq_program_describe, rows in its "row_ids" order, into out:
  * complex128 (re, im) device array of cap entries.  *entries (may be NULL)
  * receives the number of entries needed (sum over groups of rows x
  * mat_block); with out = NULL only that is returned.  The layout of a block
- * is the "tasks" list of tq_program_describe. */
+ * is the "tasks" list of tq_program_describe; with specialize = 1 one entry
+ * follows a rotation's matrix (its shears), in noisy circuits of Clifford
+ * gates and rotations the channels give way to one Pauli per qubit, a task
+ * with a gate index past the circuit's. */
 tq_status tq_build_matrices(tq_program prog, const float *symbol_values, void *out, int64_t cap, int64_t *entries,
                             void *stream);
 

@@ -43,7 +43,7 @@ struct BuildArgs {
     // global phase, the sum of the phases the gate matrices leave out; -1: none
     int32_t phase_out;
     int32_t n_phase;
-    int32_t rot_end;         // forward tasks end (0: no rotation leaves a sign to the row's phase)
+    int32_t rot_end;         // forward tasks end (0: the rotations leave no signs to the row's phase)
     const PhaseTerm *phase_terms;
     // seed of the channels' per-row Kraus draws
     uint64_t noise_seed;

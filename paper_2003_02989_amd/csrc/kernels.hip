@@ -683,6 +683,7 @@ __device__ __forceinline__ void build_rows(const A &a, const float *theta, uint6
     __shared__ double part[4];
     // (signs the shears of forward rotations leave out: this block's tasks,
     // then the tasks of the row's other blocks)
+    if (!a.rot_end) odd = 0;
     for (int j = ti + blockDim.x; j < a.rot_end; j += blockDim.x) {
         const BuildTask bt = a.tasks[j];
         if (bt.kind == BT_PRODUCT && bt.which != BX_NONE) odd += rot_turns(bt, c);

@@ -471,9 +471,11 @@ template <class T> const T *or_own(const int32_t *derived, const DevBuf &own)
 // Symbol resolution + fused matrices for the task range [begin, end).  phase:
 // the rows' global phases are kept, which only states and amplitudes show
 // (expectations and gradients without them: one wavefront's sum and its sine
-// and cosine less, 8.5 -> 7.5 us for 11 rows of 6 qubits).
+// and cosine less, 8.5 -> 7.5 us for 11 rows of 6 qubits).  signs: with them
+// the signs that the shears of generated kernels leave out; the matrices
+// themselves hold theirs.
 void build_mats(tq_program p, size_t gi, const float *theta, int begin, int end, hipStream_t s, const RunRows &rr,
-                bool phase)
+                bool phase, bool signs = true)
 {
     const Group &g = *p->pd->groups[gi];
     GroupDev &gd = *p->gdev[gi];
@@ -515,7 +517,7 @@ void build_mats(tq_program p, size_t gi, const float *theta, int begin, int end,
     // expectations, keep none)
     const bool init = phase && rr.period == 0 && g.n > 0 && begin == g.fwd_tasks.begin && end > begin && (!g.phase_terms.empty() || g.rot || g.frames);
     a.phase_out = init ? g.init_mat[0] : -1;
-    a.rot_end = g.rot ? g.fwd_tasks.end : 0;
+    a.rot_end = g.rot && signs ? g.fwd_tasks.end : 0;
     a.n_phase = (int32_t)g.phase_terms.size();
     a.phase_terms = (const PhaseTerm *)gd.phase_terms.p;
     a.noise_seed = p->noise_seed;
@@ -2296,7 +2298,7 @@ tq_status tq_build_matrices(tq_program prog, const float *theta, void *out, int6
         for (size_t gi = 0; gi < pd.groups.size(); gi++) {
             const Group &g = *pd.groups[gi];
             GroupDev &gd = *prog->gdev[gi];
-            build_mats(prog, gi, theta, g.fwd_tasks.begin, g.rev_tasks.end, s, own_rows(prog, gi), true);
+            build_mats(prog, gi, theta, g.fwd_tasks.begin, g.rev_tasks.end, s, own_rows(prog, gi), true, false);
             const size_t n = g.rows.size() * (size_t)std::max(g.mat_block, 1);
             hip_check(hipMemcpyAsync((double2 *)out + off, mat_ws(prog) + gd.mat_off, n * sizeof(double2),
                                      hipMemcpyDeviceToDevice, s),

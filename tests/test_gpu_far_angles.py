@@ -1,6 +1,7 @@
 """The signs that the shears of rotations leave to a row's global phase: states
-of generated kernels against the oracle with angles of any size, and with
-rotations at odd quarter turns in more build tasks than one workgroup builds."""
+of generated kernels against the oracle with angles of any size, with rotations
+at odd quarter turns in more build tasks than one workgroup builds, and the
+builder's matrices against the host's."""
 import numpy as np
 import pytest
 
@@ -8,6 +9,7 @@ from gpu_util import TOL_AMP, TOL_EXP, gpu_outputs, oracle_outputs
 from paper_2003_02989_amd import tq
 from paper_2003_02989_amd import workloads as wl
 from paper_2003_02989_amd.circuits import Circuit, sym
+from test_gpu_builder import check
 
 pytestmark = pytest.mark.gpu
 FAR = [1e5, 2.0**39, 2.0**41, 1e15, -1e16, 3e17, -1e20, 1e25, 1e30, 3e38]
@@ -109,3 +111,10 @@ def test_ties_beyond_one_workgroup(n):
     assert sum(t[0] == 0 for t in d["tasks"]) > 256
     got, ref = gpu_outputs(w, want=("state",), specialize=True), oracle_outputs(w, want=("state",))
     assert np.linalg.norm(got["state"] - ref["state"], axis=1).max() <= TOL_AMP
+
+
+@pytest.mark.parametrize("specialize", [True, False])
+def test_matrices_of_odd_turns(specialize):
+    # the matrices hold their own signs: the phase beside them takes none up
+    w = workload(rotations(4, ["RX", "YPOW"], ["XXPOW"]), [[v, 0.3] for v in (1.0, 3.0, 5.0, 7.0, 9.0)])
+    assert check(w, specialize=specialize) < 1e-12
