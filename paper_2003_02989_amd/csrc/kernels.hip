@@ -395,10 +395,10 @@ __device__ __forceinline__ double half_turns(const MemberDev &gd, double eta, do
 {
     if (gd.slot[0] < 0) return 0.25;  // sqrt X, sqrt Y: G^(1/2)
     if (far_turned(gd, eta)) {
-        const double as = fabs(s), ac = fabs(c), m = fmin(as, ac), z = m * m;
+        const bool steep = fabs(s) > fabs(c);
+        const double m = fmin(fabs(s), fabs(c)), z = m * m;
         const double k = fma(z, fma(z, 0.0239, 0.0531), 0.3183);  // (1 + z / 6 + 3 z^2 / 40) / pi
-        const double q = as > ac ? fma(-m, k, 0.5) : m * k;
-        return copysign(c < 0.0 ? 1.0 - q : q, s);
+        return copysign(fma(steep == (c < 0.0) ? m : -m, k, steep ? 0.5 : c < 0.0 ? 1.0 : 0.0), s);
     }
     return mod2(gd.op == OP_RX || gd.op == OP_RY ? eta * (0.5 / 3.14159265358979323846) : 0.5 * eta);
 }
