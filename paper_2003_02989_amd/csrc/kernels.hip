@@ -258,14 +258,9 @@ __device__ __forceinline__ double code_part(uint32_t q, double c2, double s2)
                  ks = (double)((int32_t)(q << 20) >> 28);
     return fma(kc, c2, fma(ks, s2, 0.5 * k0));
 }
-// entries at(0 .. N-1) of a row into g
-template <int N, class At>
-__device__ __forceinline__ void code_entries(const uint32_t *code, At at, double s, double c, cd *g)
+template <int N> __device__ __forceinline__ void code_values(const uint32_t *q, double s, double c, cd *g)
 {
     const double c2 = 0.5 * c, s2 = 0.5 * s;
-    uint32_t q[N];
-#pragma unroll
-    for (int i = 0; i < N; i++) q[i] = code[at(i)];
 #pragma unroll
     for (int i = 0; i < N; i++) g[i] = C(code_part(q[i], c2, s2), code_part(q[i] >> 12, c2, s2));
     if (!(fabs(s) + fabs(c) < 1e300)) {
@@ -275,6 +270,29 @@ __device__ __forceinline__ void code_entries(const uint32_t *code, At at, double
             if (!((q[i] >> 12) & 0xff0u)) g[i].y = 0.5 * (double)((int32_t)(q[i] << 16) >> 28);
         }
     }
+}
+// entries at(0 .. 3) of a row into g
+template <class At>
+__device__ __forceinline__ void code_entries4(const uint32_t *code, At at, double s, double c, cd *g)
+{
+    uint32_t q[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) q[i] = code[at(i)];
+    code_values<4>(q, s, c, g);
+}
+// All sixteen, N at a time: fewer as more of them are held, so that the
+// unpacked coefficients stay within the 256 registers of two wavefronts per
+// SIMD.  All at once the builder took 310, one wavefront; gradients with dense
+// 4x4 products, the builder alone: 16384 rows of 3 qubits 1005 -> 577 us, 16384
+// of 8 qubits 694 -> 240, 1024 of 8 qubits 58 -> 42, a row of 13 qubits 17.7 ->
+// 18.3.
+template <int N, int... Rest>
+__device__ __forceinline__ void code_steps(const uint32_t *q, double s, double c, cd *g)
+{
+    __builtin_amdgcn_sched_barrier(0);
+    code_values<N>(q, s, c, g);
+    if constexpr (sizeof...(Rest) > 0) code_steps<Rest...>(q + N, s, c, g + N);
+    else __builtin_amdgcn_sched_barrier(0);
 }
 
 int gate_table_host(int op, const double *eta, const double *ex, int form, int deriv, int which, double *out)
@@ -520,7 +538,7 @@ template <bool FULL> __device__ __forceinline__ int build_task(const BuildTask &
         loaded = slot_load(c, next.op == OP_FRAME ? -1 : next.slot[0], next.sym[0]);
         if (small) {
             cd g[4];
-            code_entries<4>(code, [&](int i) { return (at4 >> (4 * i)) & 15u; }, sn, cs, g);
+            code_entries4(code, [&](int i) { return (at4 >> (4 * i)) & 15u; }, sn, cs, g);
             if (ex) {
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
@@ -541,7 +559,10 @@ template <bool FULL> __device__ __forceinline__ int build_task(const BuildTask &
             }
         } else if constexpr (FULL) {
             cd g[16];
-            code_entries<16>(code, [](int i) { return i; }, sn, cs, g);
+            uint32_t q[16];
+#pragma unroll
+            for (int i = 0; i < 16; i++) q[i] = code[i];
+            code_steps<4, 4, 2, 2, 1, 1, 1, 1>(q, sn, cs, g);
             if (ex) {
 #pragma unroll
                 for (int i = 0; i < 16; i++) {
@@ -710,11 +731,12 @@ __device__ __forceinline__ void build_rows(const A &a, const float *theta, uint6
     }
 }
 
-// FULL: programs with 4x4 matrices that are neither diagonal nor a pair; the
-// 310 registers of their sixteen entries leave one wavefront per SIMD where
-// the other kernel's 188 leave two (shifted rows of 12 rows of 10-qubit QAOA
-// 28.0 -> 15.4 us, of 823 rows of 3 qubits 110 -> 53 us)
-template <bool FULL> __global__ __launch_bounds__(256) void k_build_mats(BuildArgs a)
+// FULL: programs with 4x4 matrices that are neither diagonal nor a pair.  Its
+// sixteen entries take all 256 registers that two wavefronts per SIMD leave (see
+// code_steps); the other kernel, at 173, fetches less code: with the entries
+// unpacked all at once, shifted rows of 12 rows of 10-qubit QAOA took 28.0 us in
+// the one and 15.4 in the other.
+template <bool FULL> __global__ __launch_bounds__(256, 2) void k_build_mats(BuildArgs a)
 {
     build_rows<FULL>(a, a.theta, a.noise_seed, blockIdx.y, blockIdx.x);
 }
@@ -1194,7 +1216,7 @@ template <class T> __device__ __forceinline__ TableArg<T> &table_arg(const void 
     return reinterpret_cast<TableArg<T> *>(reinterpret_cast<uintptr_t>(table))[i];
 }
 
-__global__ __launch_bounds__(256) void k_build_batch(const void *table, const BatchBlock *blocks, ResCall c)
+__global__ __launch_bounds__(256, 2) void k_build_batch(const void *table, const BatchBlock *blocks, ResCall c)
 {
     const BatchBlock bb = cget(blocks, blockIdx.x);
     TableArg<BuildArgs> &a = table_arg<BuildArgs>(table, bb.arg);
