@@ -72,7 +72,7 @@ typedef enum {
  *                    (default 0 = no limit; 1 makes every gate its own pass,
  *                    which measures the bandwidth of single-gate passes);
  *   specialize:      1 = every circuit structure runs kernels generated
- *                    for it (the resident kernel, or its forward and reverse
+ *                    for it (resident kernels, or its forward and reverse
  *                    tile passes) and compiled with hipRTC on first use (or
  *                    by tq_program_specialize), with every stage and op
  *                    written in as constants; likewise an observable set that

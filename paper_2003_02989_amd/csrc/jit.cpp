@@ -2429,9 +2429,12 @@ hipError_t launch_rev_pass_spec(const Group &g, int pass, const RevArgs &a, int 
     return launch(fn, a, nrows * a.wg_per_row, rev_pass_lds_bytes(a.g, 0, nt / 64, a.gcount), s, "rev_pass", nt);
 }
 
-hipError_t prepare_spec(const Group &g, bool resident, const char *target, std::string *log)
+hipError_t prepare_spec(const Group &g, bool resident, bool grads, const char *target, std::string *log)
 {
-    const std::vector<std::string> bodies = resident ? std::vector<std::string>{resident_kernel(g, false), resident_kernel(g, true)} : pass_chunks(g);
+    std::vector<std::string> bodies;
+    if (!resident) bodies = pass_chunks(g);
+    else bodies.push_back(resident_kernel(g, false));
+    if (resident && grads) bodies.push_back(resident_kernel(g, true));
     if (target) {
         std::vector<const std::string *> ptrs;
         for (const std::string &b : bodies) ptrs.push_back(&b);

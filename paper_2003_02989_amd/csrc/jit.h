@@ -69,11 +69,12 @@ hipError_t launch_hphi_spec(const std::string &src, int pass, const HPhiArgs &a,
 // Workgroups of a specialised Pauli pass that fit on the device at once (0 if unknown).
 int pauli_spec_slots(const std::string &src, const TileGeom &g, int K, std::string *log, SpecMemo *memo);
 
-// Compile the specialised kernels of group g (the resident kernel, or the
-// forward and reverse pass kernels) ahead of their first launch: for the current device when
+// Compile the specialised kernels of group g (the resident kernels, the whole
+// one where the program has gradients, or the forward and reverse pass kernels)
+// ahead of their first launch: for the current device when
 // target is NULL (the module is then cached), else only check that they
 // compile for the offload target (e.g. "gfx950"), which needs no device.
-hipError_t prepare_spec(const Group &g, bool resident, const char *target, std::string *log);
+hipError_t prepare_spec(const Group &g, bool resident, bool grads, const char *target, std::string *log);
 
 // Specialised kernel programs loaded so far in this process (all devices),
 // and how many of their code objects came from the on-disk code cache.

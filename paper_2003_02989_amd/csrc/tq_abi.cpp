@@ -1906,7 +1906,8 @@ tq_status tq_program_specialize(tq_program prog, const char *target)
         if (!prog->pd->opt.specialize) return;
         for (size_t gi = 0; gi < prog->pd->groups.size(); gi++) {
             std::string log;
-            const hipError_t e = prepare_spec(*prog->pd->groups[gi], resident(prog, gi, false, 0), target, &log);
+            const hipError_t e =
+                prepare_spec(*prog->pd->groups[gi], resident(prog, gi, false, 0), prog->pd->S > 0, target, &log);
             if (e == hipErrorInvalidSource) fail(TQ_E_DEVICE, log);
             hip_check(e, "specialised kernel compilation");
         }
