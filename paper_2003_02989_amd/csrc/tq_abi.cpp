@@ -1004,6 +1004,11 @@ constexpr int64_t kBatchRows = 4096;
 // their own: 32 MB of workgroup list, and blocks x threads below the 2^32 that
 // a launch takes
 constexpr int64_t kBatchBlocks = (int64_t)1 << 22;
+// the same for the bytes of the structures' partial sums, which merged launches
+// keep side by side, per observable set (a structure alone needs them one at a
+// time): structures of long rows with thousands of parameters, whose own
+// launches fill the chip
+constexpr size_t kBatchSums = (size_t)256 << 20;
 
 bool resident(tq_program p, size_t gi, bool adjoint, int tmax)
 {
@@ -1301,7 +1306,7 @@ void ensure_batch(tq_program p, BatchPlan &bp, int mode, int K)
     float *some = reinterpret_cast<float *>(sizeof(float4));
     for (size_t gi = 0; gi < G; gi++) {
         if (!batch_covers(p, gi, mode)) continue;
-        if (rec.largest() >= kBatchBlocks) break;
+        if (rec.largest() >= kBatchBlocks || rec.partial.total + rec.gpart.total >= kBatchSums) break;
         covered[gi] = 1;
         RunRows rr = own_rows(p, gi);
         rr.rec = &rec;

@@ -114,3 +114,33 @@ def test_memory_of_many_small_rows_beside_a_large_one():
     took = free - torch.cuda.mem_get_info()[0]
     state = 8 * 2**n
     assert took <= state + (48 << 20), took  # matrices, tables and partial sums beside it: some MB
+
+
+def test_memory_of_many_parameters_on_large_states():
+    # the gradient sums of all structures side by side would take 590 MB
+    n, G, S = 22, 12, 6000
+    sums = 8 * S * 2 ** (n - 12)  # of one structure
+    circuits = []
+    for k in range(G):
+        c = Circuit(n)
+        for q in range(n):
+            c.add("RY", q, [0.1 + 0.2 * q])
+        for i in range(S):
+            c.add("RZ", (i + k) % n, [sym(0, 0.001 * (1 + i % 7))])
+        circuits.append(c.add("CNOT", (k, k + 1)))
+    theta = np.linspace(-1, 1, G, dtype=np.float32)[:, None]
+    obs = [[[(0.7, [(0, "X"), (5, "X")]), (0.4, [(k, "Y")])]] for k in range(G)]
+    w = wl.Workload("params", circuits, 1, theta, obs, np.ones((G, 1), np.float32))
+    p, o, th, up = tq.Program(w.program_blob()), tq.Observables(w.observable_blob()), dev(w.theta), dev(w.upstream)
+    g = torch.empty((G, 1), dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    tq.adjoint_grad(p, th, o, up, grad=g)
+    torch.cuda.synchronize()
+    took = free - torch.cuda.mem_get_info()[0] - 2 * 8 * G * 2**n
+    # 256 MB, passed by one structure's at most, and the program's own for one structure
+    assert took <= (256 << 20) + 2 * sums + (64 << 20), took
+    for k in (0, 6, G - 1):
+        one = wl.Workload("one", [circuits[k]], 1, theta[k : k + 1], [obs[k]], w.upstream[:1])
+        ref = gpu_outputs(one, want=("grad",))["grad"]
+        assert np.abs(g[k].cpu().numpy() - ref[0]).max() <= TOL_GRAD
