@@ -62,7 +62,8 @@ typedef enum {
  *   max_tile_qubits: log2 of the amplitudes one workgroup stages in LDS per
  *                    forward pass (default 12, or 13 with specialize = 1;
  *                    allowed 8..13; by default 13 also for the reverse
- *                    passes of 13-qubit circuits with specialize = 1);
+ *                    passes of 13-qubit circuits with specialize = 1 where
+ *                    that is faster);
  *   low_qubits:      contiguous low index bits every tile keeps, so that each
  *                    wavefront reads runs of 2^low_qubits amplitudes
  *                    (default 6, allowed 3..8);

@@ -571,6 +571,17 @@ Packing pack(const Pass &ps, int rmax, int rdense, bool commute, bool soft_first
     return P;
 }
 
+// The cheapest of the four packings.
+Packing best(const Pass &ps, int rmax, int rdense, bool forward, int dispatch)
+{
+    Packing b;
+    for (int v = 0; v < 4; v++) {
+        Packing P = pack(ps, rmax, rdense, v & 1, v & 2, forward, dispatch);
+        if (v == 0 || P.cost < b.cost) b = std::move(P);
+    }
+    return b;
+}
+
 } // namespace stages
 
 void make_stages(Pass &ps, int rmax, int rdense, Group &g, const std::map<int32_t, int> &task_at, bool forward,
@@ -578,13 +589,7 @@ void make_stages(Pass &ps, int rmax, int rdense, Group &g, const std::map<int32_
 {
     const int nops = (int)ps.ops.size();
     ps.stages.clear();
-    stages::Packing best;
-    bool first = true;
-    for (int v = 0; v < 4; v++) {
-        stages::Packing P = stages::pack(ps, rmax, rdense, v & 1, v & 2, forward, dispatch);
-        if (first || P.cost < best.cost) best = std::move(P);
-        first = false;
-    }
+    const stages::Packing best = stages::best(ps, rmax, rdense, forward, dispatch);
     std::vector<PassOp> ops(nops);
     for (int k = 0; k < nops; k++) ops[k] = ps.ops[best.order[k]];
     ps.ops = std::move(ops);
@@ -1231,57 +1236,95 @@ void plan_group(Group &g, const Options &opt, int S)
     g.fwd_tasks.end = (int)g.tasks.size();
     g.fwd_mat_end = g.mat_block;
 
-    // reverse passes: every gate, last first, W^dagger and dW/deta per op;
-    // two states share the LDS (see rev_tile)
+    // reverse passes: every gate, last first, W^dagger and dW/deta per op; two
+    // states share the LDS, so tiles have at most 12 bits (or see whole_rev_pays)
     g.rev_tasks.begin = (int)g.tasks.size();
     std::vector<int> ritems;
     for (int gi = G - 1; gi >= 0; gi--)
         if (applied(gi)) ritems.push_back(gi);
-    const int trev = rev_tile(n, opt);
-    const int crev = std::min(opt.low, trev - 2);
+    auto symbols_of = [&](int gi) {
+        int k = 0;
+        for (int j = 0; j < g.gates[gi].np; j++) k += g.slot_sym[g.gates[gi].slot0 + j] >= 0;
+        return k;
+    };
     // (a group without symbolic parameters never runs its reverse passes:
     // one schedule is enough)
     bool symbolic = false;
-    for (int gi = 0; gi < G && !symbolic; gi++)
-        for (int j = 0; j < g.gates[gi].np; j++) symbolic |= g.slot_sym[g.gates[gi].slot0 + j] >= 0;
-    auto rs0 = symbolic ? schedule_best(g, ritems, n, trev, crev, opt.max_pass_gates)
-                        : schedule(g, ritems, n, trev, crev, opt.max_pass_gates, false);
-    // the reverse kernel keeps per-wave accumulators of every gradient slot of
-    // a pass in LDS: split passes that would hold too many
-    std::vector<Sched> rs;
-    for (auto &s0 : rs0) {
-        Sched cur;
-        cur.bits = s0.bits;
-        const int most = rev_max_grads(geom_from_bits(n, pass_low(s0.bits, crev), s0.bits));
-        int ng = 0;
-        for (int gi : s0.items) {
-            int k = 0;
-            for (int j = 0; j < g.gates[gi].np; j++) k += g.slot_sym[g.gates[gi].slot0 + j] >= 0;
-            if (ng + k > most && !cur.items.empty()) {
-                rs.push_back(cur);
-                cur.items.clear();
-                ng = 0;
+    for (int gi = 0; gi < G && !symbolic; gi++) symbolic = symbols_of(gi) > 0;
+    auto rev_geom = [&](const Sched &s, int t) { return geom_from_bits(n, pass_low(s.bits, std::min(opt.low, t - 2)), s.bits); };
+    auto rev_sched = [&](int t) {
+        const int c = std::min(opt.low, t - 2);
+        auto rs0 = symbolic ? schedule_best(g, ritems, n, t, c, opt.max_pass_gates)
+                            : schedule(g, ritems, n, t, c, opt.max_pass_gates, false);
+        // the reverse kernel keeps per-wave accumulators of every gradient slot of
+        // a pass in LDS: split passes that would hold too many
+        std::vector<Sched> rs;
+        for (auto &s0 : rs0) {
+            Sched cur;
+            cur.bits = s0.bits;
+            const int most = rev_max_grads(rev_geom(s0, t));
+            int ng = 0;
+            for (int gi : s0.items) {
+                const int k = symbols_of(gi);
+                if (ng + k > most && !cur.items.empty()) {
+                    rs.push_back(cur);
+                    cur.items.clear();
+                    ng = 0;
+                }
+                cur.items.push_back(gi);
+                ng += k;
             }
-            cur.items.push_back(gi);
-            ng += k;
+            if (!cur.items.empty() || rs.empty()) rs.push_back(cur);
         }
-        if (!cur.items.empty() || rs.empty()) rs.push_back(cur);
+        return rs;
+    };
+    // a gate's op, W^dagger with the structure of W, without its matrices
+    auto rev_op = [&](const TileGeom &gm, int gi, const Member &m, TaskExtra *ex) {
+        PassOp op = base_op(g, gm, gi, n);
+        op.hint = op_hint(g, op, {m});
+        *ex = opt.specialize ? op_shears(g, op, {m}) : BX_NONE;
+        if (*ex != BX_NONE) op.hint |= kHintRot;
+        op.ngrad = 0;
+        return op;
+    };
+    auto member_of = [&](int gi) {
+        return Member{gi, 0, (uint8_t)(classify(g.gates[gi].op) == C_CTRL ? FORM_CBLOCK : FORM_FULL), {0, 0}};
+    };
+    const int dispatch = opt.specialize ? kOpDispatchCostSpec : kOpDispatchCost;
+    int trev = std::min(opt.tile, 12);
+    std::vector<Sched> rs = rev_sched(trev);
+    if (symbolic && opt.specialize && opt.auto_tile && n == 13) {
+        const std::vector<Sched> whole = rev_sched(n);
+        auto nstages = [&] {
+            int k = 0;
+            for (const Sched &s : whole) {
+                Pass ps;
+                ps.geom = rev_geom(s, n);
+                for (int gi : s.items) {
+                    TaskExtra ex;
+                    ps.ops.push_back(rev_op(ps.geom, gi, member_of(gi), &ex));
+                    ps.ops.back().ngrad = (uint8_t)symbols_of(gi);
+                }
+                k += (int)stages::best(ps, rev_stage_bits(n, opt), kRevDense2Bits, false, dispatch).st.size();
+            }
+            return k;
+        };
+        if (whole_rev_pays((int64_t)g.rows.size(), (int)rs.size() - (int)whole.size(), nstages)) {
+            rs = whole;
+            trev = n;
+        }
     }
     for (auto &s : rs) {
         Pass ps;
-        ps.geom = geom_from_bits(n, pass_low(s.bits, crev), s.bits);
+        ps.geom = rev_geom(s, trev);
         ps.mat_begin = g.mat_block;
         for (int gi : s.items) {
-            int cls = classify(g.gates[gi].op);
-            PassOp op = base_op(g, ps.geom, gi, n);
+            const Member m = member_of(gi);
+            TaskExtra ex;
+            PassOp op = rev_op(ps.geom, gi, m, &ex);
             const int dim = op_dim(op), diag = storage_of(op);
-            Member m{gi, 0, (uint8_t)(cls == C_CTRL ? FORM_CBLOCK : FORM_FULL), {0, 0}};
-            op.hint = op_hint(g, op, {m});  // W^dagger keeps the structure of W
-            const TaskExtra ex = opt.specialize ? op_shears(g, op, {m}) : BX_NONE;
-            if (ex != BX_NONE) op.hint |= kHintRot;
             int ti = P.add_task(BT_DAGGER, dim, diag, ex, {m});
             op.mat = g.tasks[ti].out;
-            op.ngrad = 0;
             for (int j = 0; j < g.gates[gi].np; j++) {
                 int slot = g.gates[gi].slot0 + j;
                 if (g.slot_sym[slot] < 0) continue;
@@ -1303,7 +1346,6 @@ void plan_group(Group &g, const Options &opt, int S)
     std::map<int32_t, int> task_at;
     for (int i = 0; i < (int)g.tasks.size(); i++) task_at[g.tasks[i].out] = i;
     int off = 0;
-    const int dispatch = opt.specialize ? kOpDispatchCostSpec : kOpDispatchCost;
     for (Pass &ps : g.fwd) {
         ps.op_offset = off;
         // generated tile passes (states too large to run resident) hold

@@ -17,7 +17,7 @@ struct Error {
 };
 
 struct Options {
-    bool auto_tile = false;   // the caller left the tile size open (see rev_tile)
+    bool auto_tile = false;   // the caller left the tile size open (see whole_rev_pays)
     int tile = 12;    // forward tile bits
     int low = 6;      // contiguous low bits per tile
     bool fuse = true;
@@ -156,15 +156,31 @@ inline int rev_stage_bits(int n, const Options &opt)
     return opt.specialize && n <= kWideRevQubits ? kStageBitsRev : kStageBitsRevResident;
 }
 
-// Generated reverse passes of 13 qubits take both states (128 KB of a CU's 160
-// KB of LDS) as one tile when the caller left the tile size open, so that the
-// whole sweep is one pass; larger states keep tiles of 2^12, two workgroups per
-// CU.  (A forward state of 2^14 amplitudes as one tile measured no faster than
+// Generated reverse passes of 13 qubits can take both states (128 KB of a CU's
+// 160 KB of LDS) as one tile when the caller left the tile size open: `saved`
+// passes less (each a launch and a round trip of both states), but one
+// workgroup per row and CU, whose eight wavefronts share the LDS and the issue
+// that two workgroups of four have on two CUs while there are CUs to spare,
+// which costs each of the stages() (1.4 us per stage against 7 us per pass at
+// one row).  The line follows from both sides measured over twenty circuits of
+// 7 to 163 stages (gradients, time with tiles of 2^12 over time with whole
+// states): up to 128 rows 1.01-1.13 at up to 5.7 stages per saved pass, about
+// 1.0 at 6 to 9, 0.85-0.93 from 16 on; 129 to 256 rows, one round of one
+// workgroup per CU either way, 0.99-1.36 for all; beyond, rounds that fill the
+// chip 1.01-1.32 for all but one (0.96, a single saved pass), a last round that
+// is partly empty 1.07-1.21 at up to 5.7, about 1.0 to 1.05 at 6 to 11,
+// 0.88-0.99 from 16 on.  (Larger states keep tiles of 2^12, two workgroups per
+// CU.  A forward state of 2^14 amplitudes as one tile measured no faster than
 // two passes over tiles of 2^13: 1.38 ms against 1.36 ms for 5040 derived rows
 // of a 14-qubit QAOA circuit, bound by VALU issue and LDS either way.)
-inline int rev_tile(int n, const Options &opt)
+template <class Count> bool whole_rev_pays(int64_t rows, int saved, Count &&stages)
 {
-    return opt.specialize && opt.auto_tile && n == 13 ? 13 : std::min(opt.tile, 12);
+    constexpr int64_t kCus = 256;
+    if (saved <= 0) return false;
+    if (rows <= kCus / 2) return stages() <= 6 * saved;
+    const int64_t rounds = (rows + kCus - 1) / kCus;
+    if (rounds == 1 || 20 * rows >= 17 * kCus * rounds) return true;
+    return stages() <= 11 * saved;
 }
 // Workgroups of the generated reverse passes: 256 threads, 512 for tiles whose
 // LDS leaves room for one workgroup on a CU (two states of 2^13 amplitudes), so

@@ -52,3 +52,38 @@ def test_whole_state_tile_fits_the_lds(low, over):
     assert got == slots
     # one pass where one fits
     assert len(g["rev"]) == -(-slots // limit(h))
+
+
+def rev_tile(c, rows, **kw):
+    w = wl.Workload("rows", [c] * rows, 7, None, None, None)
+    rev = tq.describe(tq.Program(w.program_blob(), specialize=True, **kw))["groups"][0]["rev"]
+    return rev[0]["t"], len(rev), sum(len(ps["stages"]) for ps in rev)
+
+
+# rows: up to 128, one round of the chip's 256 CUs, full rounds, a last round mostly empty
+ROWS = [1, 128, 129, 256, 257, 352, 448, 512, 600, 1024]
+
+
+@pytest.mark.parametrize("kind,wholes", [
+    ("layers", ROWS),                            # few stages per pass saved
+    ("dense", [129, 256, 448, 512, 1024]),       # many
+    ("one pass", []),                            # none saved
+])
+def test_whole_state_tiles_where_they_pay(kind, wholes):
+    if kind == "layers":
+        c = ansatz(130)
+    elif kind == "dense":
+        c = wl.random_circuit(wl.rng_for(13), 13, 150, 7)
+    else:
+        c = Circuit(13)
+        for q in range(13):
+            c.add("RZ", q, [sym(q % 7)]).add("CZPOW", (q, (q + 1) % 13), [sym((q + 1) % 7)])
+    t12, p12, _ = rev_tile(c, 1, max_tile_qubits=13)
+    assert t12 == 12
+    for rows in ROWS:
+        t, passes, stages = rev_tile(c, rows)
+        assert t == (13 if rows in wholes else 12), rows
+        assert passes == (1 if t == 13 else p12)
+    if kind != "one pass":
+        _, _, stages = rev_tile(c, 256)
+        assert (stages <= 6 * (p12 - 1)) == (kind == "layers") and (stages > 11 * (p12 - 1)) == (kind == "dense")
