@@ -627,17 +627,29 @@ template <bool FULL> __device__ __forceinline__ int build_task(const BuildTask &
 }
 
 // --------------------------------------------------------- Pauli frames
-// The frame of group row `src` (batch row b) into LDS, by one wavefront: the
-// lanes draw the channels (64 at a time), and the table rows of the few Paulis
-// drawn are xored word by word (lane w holds the words w, w + 64, ...), while
-// every lane keeps the frame itself, F = i^k X^x Z^z, in channel order: F <-
-// P F with P the drawn Pauli moved to the end.
+// The frame of batch row b into LDS, by one wavefront: the lanes draw the
+// channels, 64 at a time, and the table rows of the Paulis drawn are xored, the
+// bits of the angles and the X and Z masks alike.  A group of channels side by
+// side, one word to a lane, is one step (as many channels as their words fit 64
+// lanes), two groups' loads in flight together, and groups without a drawn
+// Pauli are passed over: a step per Pauli where few are drawn, and at most as
+// many as a frame has words per 64 channels where many are.  The power of i,
+// which only rows that keep their phase show, follows from the order: F <- P F
+// with P the drawn Pauli moved to the end, F = i^k X^x Z^z.  Expectation of a
+// row of 4 qubits and 280 channels (of 512 rows of 11 qubits and 420): one
+// Pauli after another 65 us (181), groups one at a time 39.8 (107), two 38.0
+// (97), four 37.0 (92) where a channel draws one with probability 0.4, but four
+// are 0.4 to 1 us slower than two where it is 0.01.
+constexpr int kFrameGroups = 2;
 template <class A>
 __device__ __forceinline__ void frame_row(const A &a, const double *off, uint64_t noise_seed, int b, uint32_t *acc)
 {
-    const int lane = threadIdx.x & 63, nw = a.frame_words - 3;
-    for (int w = lane; w < nw; w += 64) acc[w] = 0u;
-    uint32_t x = 0, z = 0, k = 0;
+    const int lane = threadIdx.x & 63, fw = a.frame_words, W = fw - 1;
+    const bool phased = a.phase_out >= 0;
+    for (int w = lane; w < fw; w += 64) acc[w] = 0u;
+    const int lw = W > 32 ? 6 : 32 - __clz(W - 1);  // (W >= 2: the X and Z masks)
+    const int each = 64 >> lw, sub = lane >> lw, word = min(lane & ((1 << lw) - 1), W - 1);
+    uint32_t v = 0, x = 0, k = 0;
     for (int c0 = 0; c0 < a.nchan; c0 += 64) {
         int pick = 0;
         if (c0 + lane < a.nchan) {
@@ -645,22 +657,69 @@ __device__ __forceinline__ void frame_row(const A &a, const double *off, uint64_
             const double p[3] = {off[gd.slot0], off[gd.slot0 + 1], off[gd.slot0 + 2]};
             pick = channel_pick(noise_seed, b, gd.chan, p);
         }
-        for (uint64_t m = __ballot(pick != 0); m; m &= m - 1) {
-            const int l = __ffsll((unsigned long long)m) - 1;
-            const int d = __builtin_amdgcn_readlane(pick, l);
-            for (int t = 1; t >= 0; t--) {  // Y = i X Z: Z first
-                if (d == (t ? 1 : 3)) continue;
-                const uint32_t *r = a.frame_table + (int64_t)(2 * (c0 + l) + t) * a.frame_words;
-                for (int w = lane; w < nw; w += 64) acc[w] ^= r[w];
-                const uint32_t rx = r[nw], rz = r[nw + 1];
-                k += r[nw + 2] + 2u * (uint32_t)__popc(rz & x);
-                x ^= rx;
-                z ^= rz;
+        uint64_t m = __ballot(pick != 0);
+        while (m) {
+            const uint32_t *r[kFrameGroups];
+            int d[kFrameGroups];
+#pragma unroll
+            for (int i = 0; i < kFrameGroups; i++) {
+                // (none left: no Pauli, and a row that is there to be read)
+                const int first = m ? (__ffsll((unsigned long long)m) - 1) & -each : 0;
+                d[i] = m ? __shfl(pick, first + sub) : 0;
+                m &= ~(((1ull << each) - 1) << first);
+                r[i] = a.frame_table + (int64_t)2 * min(c0 + first + sub, a.nchan - 1) * fw;
             }
-            if (d == 2) k += 1;
+            // X and Y take a channel's first row, Y and Z its second
+            auto rows = [&](int w) {
+                uint32_t rx[kFrameGroups], rz[kFrameGroups], t = 0;
+#pragma unroll
+                for (int i = 0; i < kFrameGroups; i++) {
+                    rx[i] = r[i][w];
+                    rz[i] = r[i][fw + w];
+                }
+#pragma unroll
+                for (int i = 0; i < kFrameGroups; i++)
+                    t ^= (d[i] == 1 || d[i] == 2 ? rx[i] : 0u) ^ (d[i] >= 2 ? rz[i] : 0u);
+                return t;
+            };
+            if (W <= 64) v ^= rows(word);
+            else
+                for (int w = lane; w < W; w += 64) acc[w] ^= rows(w);
+        }
+        if (phased) {
+            // this lane's Pauli (Y = i X Z: Z first), then what it meets: the
+            // X mask of those before it
+            uint32_t px = 0, pz = 0, pk = 0;
+            if (pick) {
+                const uint32_t *r = a.frame_table + (int64_t)2 * (c0 + lane) * fw + (W - 2);
+                if (pick >= 2) {
+                    px = r[fw];
+                    pz = r[fw + 1];
+                    pk = r[fw + 2];
+                }
+                if (pick <= 2) {
+                    pk += r[2] + 2u * (uint32_t)__popc(r[1] & px) + (pick == 2);
+                    px ^= r[0];
+                    pz ^= r[1];
+                }
+            }
+            uint32_t upto = px;
+            for (int s = 1; s < 64; s *= 2) {
+                const uint32_t o = __shfl_up(upto, s);
+                if (lane >= s) upto ^= o;
+            }
+            k += pk + 2u * (uint32_t)__popc(pz & (x ^ upto ^ px));
+            x ^= __shfl(upto, 63);
         }
     }
-    if (lane < 3) acc[nw + lane] = lane == 0 ? x : lane == 1 ? z : k & 3u;
+    if (W <= 64) {
+        for (int s = 1 << lw; s < 64; s *= 2) v ^= __shfl_xor(v, s);
+        if (lane < W) acc[lane] = v;
+    }
+    if (phased) {
+        for (int s = 1; s < 64; s *= 2) k += __shfl_xor(k, s);
+        if (lane == 0) acc[W] = k & 3u;
+    }
 }
 
 // --------------------------------------------------- matrix build kernel
@@ -1248,8 +1307,9 @@ __global__ __launch_bounds__(256) void k_pauli_batch(const void *table, const Ba
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const BatchBlock bb = cget(blocks, blockIdx.x);
-    // (1: the workgroup keeps its number; a structure's tiles share an XCD's
-    // L2 only by chance, its few rows fit any)
+    // (1: the workgroup keeps its number, so the tiles of a row share an XCD's
+    // L2 only by chance; two states of 24 qubits are no slower for it, 1025 us
+    // against 1087 in two launches that number them by XCD)
     run_pauli<P, kPhi>(table_arg<PauliArgs>(table, bb.arg), c.upstream, bb.block, 1, smem);
 }
 __global__ __launch_bounds__(256) void k_pauli_reduce_batch(const void *table, const BatchBlock *blocks, ResCall c)

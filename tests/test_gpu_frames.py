@@ -81,6 +81,18 @@ def test_many_rotations_and_per_row_constants(specialize):
     check(w, 9, specialize=specialize)
 
 
+@pytest.mark.parametrize("gates", [30, 60, 130, 400, 900, 2000, 2300, 3700])
+def test_frame_widths(gates):
+    # a frame's words side by side in a wavefront: from 32 channels of two words
+    # to one of 64, and in strips; most channels draw a Pauli
+    rng = wl.rng_for(6600 + gates)
+    c = noisy_circuit(rng, 2, gates, 3)
+    for q in (0, 1):
+        for _ in range(40):
+            c.add("PCHAN", q, [0.3, 0.3, 0.3])
+    check(workload(rng, [c] * 3, 3), 11, specialize=gates < 200)
+
+
 def test_several_structures():
     rng = wl.rng_for(6300)
     w = workload(rng, [noisy_circuit(rng, n, 30, 3) for n in (2, 5, 9, 13)], 3)
