@@ -571,17 +571,6 @@ Packing pack(const Pass &ps, int rmax, int rdense, bool commute, bool soft_first
     return P;
 }
 
-// The cheapest of the four packings.
-Packing best(const Pass &ps, int rmax, int rdense, bool forward, int dispatch)
-{
-    Packing b;
-    for (int v = 0; v < 4; v++) {
-        Packing P = pack(ps, rmax, rdense, v & 1, v & 2, forward, dispatch);
-        if (v == 0 || P.cost < b.cost) b = std::move(P);
-    }
-    return b;
-}
-
 } // namespace stages
 
 void make_stages(Pass &ps, int rmax, int rdense, Group &g, const std::map<int32_t, int> &task_at, bool forward,
@@ -589,7 +578,13 @@ void make_stages(Pass &ps, int rmax, int rdense, Group &g, const std::map<int32_
 {
     const int nops = (int)ps.ops.size();
     ps.stages.clear();
-    const stages::Packing best = stages::best(ps, rmax, rdense, forward, dispatch);
+    stages::Packing best;
+    bool first = true;
+    for (int v = 0; v < 4; v++) {
+        stages::Packing P = stages::pack(ps, rmax, rdense, v & 1, v & 2, forward, dispatch);
+        if (first || P.cost < best.cost) best = std::move(P);
+        first = false;
+    }
     std::vector<PassOp> ops(nops);
     for (int k = 0; k < nops; k++) ops[k] = ps.ops[best.order[k]];
     ps.ops = std::move(ops);
@@ -1305,7 +1300,8 @@ void plan_group(Group &g, const Options &opt, int S)
                     ps.ops.push_back(rev_op(ps.geom, gi, member_of(gi), &ex));
                     ps.ops.back().ngrad = (uint8_t)symbols_of(gi);
                 }
-                k += (int)stages::best(ps, rev_stage_bits(n, opt), kRevDense2Bits, false, dispatch).st.size();
+                // (one packing: its stages are the cheapest one's within one or 6%)
+                k += (int)stages::pack(ps, rev_stage_bits(n, opt), kRevDense2Bits, true, false, false, dispatch).st.size();
             }
             return k;
         };
